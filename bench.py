@@ -52,7 +52,7 @@ FP_M_PAIR = 4            # per representative pair of a beta != 0 measurement: w
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "sampler_cultivation_42q_traffic.json")
 PROFILE_ISSUE = os.path.join(ROOT, "profiles", "sampler_cultivation_42q_issue.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2512_23037_amd", "csrc", f)
-                  for f in ("sampler.hip", "program.h", "sampler.h")]
+                  for f in ("sampler.hip", "signs.hip", "device.h", "program.h", "sampler.h")]
 
 
 def kernel_hash() -> str:

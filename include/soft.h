@@ -67,21 +67,26 @@ typedef struct {
     uint64_t logical_errors;     /* passed shots with a nonzero observable   */
     uint64_t entries_t;          /* coefficient entries written by T/T-dagger */
     uint64_t entries_m;          /* coefficient entries read by measurements */
-    uint64_t noise_slots;        /* noise words drawn (256 per Philox refill of a wave) */
+    uint64_t noise_slots;        /* noise words drawn (256 per Philox refill of a wave; for a shot
+                                    that the tableau signs decide, see soft_set_shared_prefix, the
+                                    words of its own lanes) */
     uint64_t events;             /* T/T-dagger and measurements executed      */
     uint64_t support_hist[16];   /* shots by floor(log2(max |v|)), last bin 15+: the
                                     largest support the kernel held (the speculative
                                     lists may hold smaller ones than the circuit's
                                     gate order; with speculation off they are the
                                     circuit order's; a shot that ended with a deferred
-                                    T run skipped counts the supports it computed) */
+                                    T run skipped counts the supports it computed, and one
+                                    that the tableau signs decide the checkpoint's before its
+                                    first noise hit) */
     double max_norm_dev;         /* max over shots of |sum |v|^2 - 1| at the end */
     uint64_t restarts;           /* shots re-run on the full event list: the speculative
                                     list's span truncation found amplitude left (noise
                                     broke a T / T-dagger cancellation) */
     uint64_t prefix_shots;       /* attempts that started from a checkpoint of the noiseless
-                                    trajectory (soft_set_shared_prefix); the work fields
-                                    above count only the work run */
+                                    trajectory, or were decided past one
+                                    (soft_set_shared_prefix); the work fields above count
+                                    only the work run */
     uint64_t redo_shots;         /* deferred T runs applied late because an event needed the
                                     tile, and attempts run again to keep a state
                                     (soft_set_deferred_t) */
@@ -254,7 +259,17 @@ int soft_set_noise_mode(soft_ctx *ctx, int mode);
  * checkpoint's coefficient tile only if an event reads it.  Results are
  * identical bit for bit either way (the same arithmetic on the same values);
  * on = 0 runs every shot from the start.  The counters' work fields count the
- * work run; prefix_shots counts the shots that started from a checkpoint. */
+ * work run; prefix_shots counts the shots that started from a checkpoint.
+ * Shots decided by their signs: up to the first measurement whose outcome
+ * depends on the coefficients, every record bit, check and observable is an
+ * XOR of its noiseless value, of even coins and of what each noise hit flips
+ * (Theorem 1: T leaves the tableau alone).  With checkpoints, deferred T runs
+ * and speculation all on, a pass before the sampler decides the shots that a
+ * check ends there, or whose whole list is decided there because every T that
+ * the speculative list pairs with its inverse sees its sign; the sampler runs
+ * the others.  The same draws and the same results; the counters' work fields
+ * count only the sampler's work.  Kept states, traces, support caps, shot lists,
+ * explicit words and a pruning threshold above 1e-6 leave the pass out. */
 int soft_set_shared_prefix(soft_ctx *ctx, int on);
 
 /* Deferred T runs (default on).  T gates change only the coefficients, never

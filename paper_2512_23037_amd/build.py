@@ -8,14 +8,14 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libsoft.so")
-SOURCES = ["sampler.hip", "compile.cpp", "soft_api.cpp"]
+SOURCES = ["sampler.hip", "signs.hip", "compile.cpp", "signs.cpp", "soft_api.cpp"]
 
 # Packed FP32 instructions are disabled for all device code.
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-def build(jobs: int = 3) -> str:
+def build(jobs: int = 5) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)

@@ -677,6 +677,7 @@ class FrameCompiler {
         int q;
         bool dagger;
         uint32_t need;  // coordinates its term reaches: new coordinate + 1, or mu's top bit + 1
+        uint32_t ev;    // its event
     };
     struct HeldT {
         int q;
@@ -733,7 +734,9 @@ class FrameCompiler {
     void spec_after_t(int q, bool dagger, uint32_t k_before, uint32_t src, uint32_t need) {
         if (!spec_) return;
         const int i = open_match(q, dagger);
+        const uint32_t ev = (uint32_t)P_.events.size() - 1u;  // the T just emitted
         if (i >= 0) {
+            P_.pairs.push_back(TPair{open_[i].ev, ev, ckpt_k_});
             open_.erase(open_.begin() + i);
             open_mask_ = 0;
             uint32_t keep = ckpt_k_;
@@ -760,7 +763,7 @@ class FrameCompiler {
             return;
         }
         if (open_.empty()) ckpt_k_ = k_before;
-        open_.push_back({q, dagger, need});
+        open_.push_back({q, dagger, need, ev});
         open_mask_ |= bitq(q);
     }
 

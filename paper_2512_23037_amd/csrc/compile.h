@@ -21,6 +21,12 @@ struct Frame {
     std::vector<uint64_t> basis;
 };
 
+// A T (event `open`) and its inverse (event `close`) of a speculative list,
+// opened since a point where the span had dimension k0.
+struct TPair {
+    uint32_t open, close, k0;
+};
+
 struct Program {
     int n = 0;
     uint32_t n_src = 0, n_rec = 0, n_noise = 0, n_meas = 0, n_obs = 0;
@@ -41,6 +47,9 @@ struct Program {
     // slot: a shot with no noise hit among slots [0, nz) reaches event ev in
     // the same state as every other such shot.
     std::vector<Checkpoint> ckpts;
+    // Speculative list: the T pairs whose product the span truncation takes
+    // as the identity, in the order they close.
+    std::vector<TPair> pairs;
 };
 
 struct CompileError {

@@ -276,12 +276,68 @@ struct alignas(16) NoiseLoc {
 };
 static_assert(sizeof(NoiseLoc) == 96, "noise layout");
 
+// ---------------------------------------------------------------------------
+// The sign program: what a shot's record, checks and observables are without
+// its coefficients.
+//
+// T gates change only the coefficients, and every measurement up to the first
+// one that reads them is either fixed by the tableau signs or an even coin
+// (EV_M_SPLIT).  So up to there each record bit, check and observable is an
+// XOR of a noiseless value, of the coins and of one fixed bit vector per Pauli
+// component of each noise hit (its signature).  What the speculative list adds
+// is the condition that a T and its inverse see the same sign (else their
+// product is not the identity and the span is not truncated): that sign
+// difference is one more XOR, a test that must be 0 like a check's.  The tests
+// are in list order, so the lowest set one is what ends the shot: a failed
+// check discards it, any other test hands it to the sampler kernel.
+//
+// A vector holds `tests` words of test bits, then the record words, then one
+// word of observables, in the launch's common layout.
+// ---------------------------------------------------------------------------
+enum SignTestKind : uint32_t {
+    SGT_CHECK = 0,  // a detector: the shot is discarded at op `src`
+    SGT_HAND = 1,   // the sampler kernel runs the shot (a broken T pair, or the
+                    // first measurement that reads coefficients)
+    SGT_NONE = 2,   // the row after the last test: the shot passed
+};
+struct alignas(16) SignTest {
+    uint32_t stop;  // noise slots from `stop` on come after the test
+    uint32_t src;   // op index of the detector
+    uint32_t kind;  // SignTestKind
+    uint32_t pad;
+};
+// A noise slot as the sign pass reads it: its signature vectors (XERR, FLIP
+// in the first; ZERR in the third) are X_a, Y_a, Z_a, X_b, Y_b, Z_b.
+struct alignas(16) SignSlot {
+    uint32_t kind;   // NoiseKind
+    uint32_t thr1;   // NoiseLoc::thr - 1
+    uint32_t acc1;   // NoiseLoc::acc - 1
+    uint32_t ckpt;   // checkpoints that precede the slot
+};
+constexpr uint32_t kSignVecs = 6;
+// One variant's part of the shared sign tables.
+struct alignas(16) SignDesc {
+    uint32_t on;        // worth it with gap sampling (1), with a word per slot (2); else every
+                        // shot goes to the sampler kernel
+    uint32_t n_tests;
+    uint32_t vec_off;   // first signature vector (slot s, component c: vec_off + kSignVecs s + c)
+    uint32_t slot_off;  // first SignSlot
+    uint32_t test_off;  // first SignTest, and row of the output masks
+    uint32_t ref_vec;   // vector of the noiseless values
+    uint32_t coin_off, n_coins;  // coins: (measurement slot, vector) pairs
+    uint32_t ck_cnt;             // checkpoints of the variant's first list
+    uint32_t pad[3];
+};
+static_assert(sizeof(SignDesc) == 48, "sign program layout");
+
 // How a launch draws its noise hits (NoiseLoc): per slot, explicit words
 // (per slot, words given by the caller) or gap sampling.
 enum NoiseSource : uint32_t { NS_SLOTS = 0, NS_EXPLICIT = 1, NS_GAPS = 2 };
 
 // Per-shot status codes (low byte of the status word).
 enum Status : uint32_t { ST_PASSED = 0, ST_DISCARDED = 1, ST_OVERFLOW = 2, ST_NUMERIC = 3 };
+// What the sign pass writes for a shot that the sampler kernel has to run.
+constexpr uint32_t kStatusPending = 0xFFFFFFFFu;
 
 // Device counters, all 64-bit: one row of C_COUNT per variant.
 enum Counter {
@@ -291,7 +347,8 @@ enum Counter {
     C_PREFIX,                // attempts that started from a checkpoint of the noiseless trajectory
     C_REDO,                  // attempts redone because a deferred T run's tile was needed
     C_HIST0,                 // 16 buckets of floor(log2(max |v|))
-    C_COUNT = C_HIST0 + 16
+    C_CK0 = C_HIST0 + 16,    // shots the sign pass decided, by checkpoints before their first noise hit
+    C_COUNT = C_CK0 + kMaxCheckpoints + 1
 };
 
 // Per kept shot (and per traced step): meta words, and separately the dense

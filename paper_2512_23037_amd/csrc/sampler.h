@@ -54,12 +54,45 @@ struct RunParams {
                               // list) without noise up to its last checkpoint, writing each checkpoint's
                               // slot
     uint32_t prefix_stride;   // bytes per prefix slot
+    uint32_t signs;           // 1: the sign pass ran; only the shots whose status is pending are left
     uint32_t defer;           // 1: skip deferrable T runs (EVF_DEFER) until an event needs their tile
     double tau2;              // pruning threshold squared
 };
 
-// Zero `n` counters and the two work cursors next[0] (sampler) and next[1]
-// (prefix build): a kernel, so it can live in a graph.
+// Arguments of the sign pass (signs.hip).
+struct SignParams {
+    const SignDesc *desc;     // per variant
+    const VariantDesc *vars;
+    const uint4 *vecs;        // signature vectors (vector 0 is zero)
+    const SignSlot *slots;
+    const SignTest *tests;
+    const uint32_t *mask;     // per test row: record words and observables written by then
+    const uint2 *coins;       // (measurement slot, vector)
+    const uint32_t *tm1, *gaps;  // as RunParams
+    uint32_t *outcomes, *status, *abort_op, *obs;
+    unsigned long long *counters, *next;
+    uint64_t seed, shot0, n_shots;
+    uint32_t n_vars, rec_words, chunk;
+    uint32_t prefix;          // 1: count the shots a checkpoint precedes
+};
+
+// The sign pass's vector sizes: a launch uses the smallest that holds its
+// variants (tests, then record words with the observables' word).
+constexpr uint32_t kSignTestWords[4] = {2, 4, 8, 16};
+constexpr uint32_t kSignOutWords[4] = {2, 4, 8, 16};
+constexpr uint32_t kSignBlock = 64;  // one wave: its shots are its own, and small launches spread over the CUs
+constexpr uint32_t kSignWavesPerCu[4] = {20, 20, 16, 12};  // by their registers
+const void *signs_kernel(uint32_t size, bool gaps);
+hipError_t launch_signs(const SignParams &p, uint32_t size, bool gaps, dim3 grid, hipStream_t stream);
+
+// Work cursors, after the counter rows: eight of a queue (WorkQueue), each in
+// a cache line of its own, for the sign pass; then the sampler's and the
+// prefix build's.
+constexpr uint32_t kQueueCursors = 8, kCursorStride = 16;
+constexpr uint32_t kSignCursor = 0, kSampleCursor = kQueueCursors * kCursorStride, kBuildCursor = kSampleCursor + 1;
+constexpr uint32_t kCursorWords = kBuildCursor + 1;
+
+// Zero `n` counters and the work cursors: a kernel, so it can live in a graph.
 hipError_t launch_reset(unsigned long long *counters, uint32_t n, unsigned long long *next, hipStream_t stream);
 
 // The persistent sampler: grid x block threads, `lds` bytes of dynamic LDS.

@@ -21,6 +21,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "device.h"
 #include "program.h"
 #include "sampler.h"
 
@@ -74,23 +75,6 @@ __device__ __forceinline__ double wave_sum(double x) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
     return unid(x);
-}
-
-// Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11).
-__device__ __forceinline__ void philox10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
-                                         uint32_t k1, uint32_t &o0, uint32_t &o1, uint32_t &o2, uint32_t &o3) {
-#pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        const uint32_t lo0 = 0xD2511F53u * c0, hi0 = __umulhi(0xD2511F53u, c0);
-        const uint32_t lo1 = 0xCD9E8D57u * c2, hi1 = __umulhi(0xCD9E8D57u, c2);
-        c0 = hi1 ^ c1 ^ k0;
-        c1 = lo1;
-        c2 = hi0 ^ c3 ^ k1;
-        c3 = lo0;
-        k0 += 0x9E3779B9u;
-        k1 += 0xBB67AE85u;
-    }
-    o0 = c0; o1 = c1; o2 = c2; o3 = c3;
 }
 
 template <typename C> __device__ __forceinline__ C mk(double re, double im) {
@@ -517,16 +501,6 @@ __device__ __forceinline__ uint32_t t_double(const Tile<C, TM> &v, uint32_t lane
 
 __device__ __forceinline__ float unif(float x) { return __uint_as_float(uni(__float_as_uint(x))); }
 
-// floor(x / d) for x < 16 d (a noise hit's Pauli code from its word): a
-// binary search on exact integer compares instead of a 64-bit division.
-__device__ __forceinline__ uint32_t quot16(uint64_t x, uint64_t d) {
-    uint32_t m = 0;
-#pragma unroll
-    for (uint32_t b = 8; b != 0u; b >>= 1)
-        if (x >= (uint64_t)(m + b) * d) m += b;
-    return m;
-}
-
 // Fields of the current event (held one dword per lane in `evc`).
 #define EV32(f) ((uint32_t)__builtin_amdgcn_readlane((int)evc, (int)(offsetof(Event, f) / 4u)))
 #define EV64(f)                                                                                  \
@@ -586,6 +560,24 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
     const uint32_t key0 = (uint32_t)P.seed, key1 = (uint32_t)(P.seed >> 32);
     const double tau2 = P.tau2;
 
+    // The supports of the shots that the sign pass decided: those the
+    // checkpoint before their first hit holds (C_CK0 counts them by
+    // checkpoint), as for a shot that starts there and defers what follows.
+    if (LEAN && P.signs && gwave == 0) {
+        for (uint32_t x = 0; x < P.n_vars; ++x) {
+            if (lane > kMaxCheckpoints) continue;
+            unsigned long long *row = P.counters + (size_t)x * C_COUNT;
+            const unsigned long long c = row[C_CK0 + lane];
+            uint32_t sup = 1u;
+            if (lane && P.prefix && c) {
+                const CkptState *cs = reinterpret_cast<const CkptState *>(
+                    P.prefix + (size_t)(P.vars[x].ck_off + lane - 1u) * P.prefix_stride);
+                if (cs->valid == 1u) sup = max(1u, cs->maxsup);
+            }
+            if (c) atomicAdd(row + C_HIST0 + min(15u, 31u - (uint32_t)__clz(sup)), c);
+        }
+    }
+
     double maxdev = 0.0;  // largest norm deviation of this wave's shots
     uint64_t myc = 0;  // counter number `lane` of this wave, for variant `var`
 
@@ -612,7 +604,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
     // writes its shots' output words one shot after the other, so L2 gathers
     // each output plane's words of a group into whole lines.
     uint64_t group_base = 0;
-    uint32_t group_len = 0, group_pos = 0;
+    uint64_t todo = 0;  // bit t: position group_base + t is still to run
     // Output plane of this lane: record word `lane` (lanes below kRecSgpr),
     // then status, abort op and observables; null when the caller did not ask.
     uint32_t *out_plane = nullptr;
@@ -626,15 +618,18 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         out_plane = P.obs;
     }
     while (true) {
-        if (group_pos == group_len) {
+        if (todo == 0ull) {
             unsigned long long got = 0;
             if (lane == 0) got = atomicAdd(P.next, (unsigned long long)P.grab);
             group_base = uni64(__shfl((unsigned long long)got, 0, 64));
             if (group_base >= P.n_shots) break;
-            group_len = (uint32_t)min((uint64_t)P.grab, P.n_shots - group_base);
-            group_pos = 0;
+            const uint32_t len = (uint32_t)min((uint64_t)P.grab, P.n_shots - group_base);
+            // after the sign pass: the shots it left
+            todo = __ballot(lane < len && !(LEAN && P.signs && P.status[group_base + lane] != kStatusPending));
+            continue;
         }
-        const uint64_t i = group_base + group_pos;
+        const uint64_t i = group_base + (uint32_t)__builtin_ctzll(todo);
+        todo &= todo - 1ull;
         // a vector load of a uniform address: say that the result is uniform
         // (item i of the prefix build runs the first shot of variant i / 2)
         const uint64_t shot = uni64((!LEAN && P.prefix_build) ? ((i >> 1) ? P.vars[(i >> 1) - 1u].shot_end : 0ull)
@@ -1800,7 +1795,6 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
                 for (uint32_t t = ck_next_done; t < cnt; ++t)
                     reinterpret_cast<CkptState *>(P.prefix + (size_t)(o + t) * P.prefix_stride)->valid = 0u;
             }
-            ++group_pos;
             continue;
         }
 
@@ -1821,7 +1815,6 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         }
         if (P.outcomes)
             for (uint32_t w = kRecSgpr + lane; w < P.rec_words; w += 64u) P.outcomes[(uint64_t)w * P.n_shots + i] = rec[w];
-        ++group_pos;
         if (kept) {
             const uint64_t kk = shot - P.keep_lo;
             dump_state(P.keep_meta + kk * KM_COUNT, P.keep_v + kk * (uint64_t)P.tile_entries * 2u, v, lane,
@@ -1882,7 +1875,7 @@ k_prefix_f64(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz, cons
 
 __global__ void k_reset(unsigned long long *counters, uint32_t n, unsigned long long *next) {
     for (uint32_t t = threadIdx.x; t < n; t += blockDim.x) counters[t] = 0ull;
-    if (threadIdx.x < 2u) next[threadIdx.x] = 0ull;  // the sampler's and the prefix build's cursors
+    if (threadIdx.x < kCursorWords) next[threadIdx.x] = 0ull;
 }
 
 template <typename R, uint32_t NS, uint32_t TM, bool LEAN> const void *kernel_ptr() {

@@ -1,0 +1,37 @@
+// signs.h -- the sign program of an event list (see program.h).
+#pragma once
+#include <stdint.h>
+
+#include <vector>
+
+#include "compile.h"
+#include "program.h"
+
+namespace soft {
+
+// Words of a vector: tests, then record words, then one word of observables.
+struct SignLayout {
+    uint32_t tests = 0, recs = 0;
+    uint32_t out() const { return recs + 1u; }
+};
+
+struct SignProgram {
+    bool on = false;
+    SignLayout need;                          // what this list fills
+    std::vector<SignTest> tests;              // one row more than tests: the end
+    std::vector<std::vector<uint32_t>> mask;  // per row: record words and observables written by then
+    std::vector<SignSlot> slots;
+    std::vector<uint32_t> vecs;               // kSignVecs vectors per slot, each as long as `ref`
+    std::vector<uint32_t> ref;                // noiseless values
+    std::vector<uint32_t> coin_slot;          // measurement slots of the coins
+    std::vector<std::vector<uint32_t>> coin;  // what a coin's 1 flips
+    bool complete = false;                    // the signs decide the whole list
+    double ends = 0.0;                        // about the fraction of shots that a check ends by signs
+};
+
+// Build the sign program of the list P.  `on` stays false when the list has
+// more tests, records or coins than the tables hold, or a T pair whose two
+// gates are not the same Pauli in the frame.
+void build_signs(const Program &P, SignProgram &out);
+
+}  // namespace soft

@@ -1,0 +1,356 @@
+// signs.hip -- the sign pass: shots decided without their coefficients.
+//
+// One lane runs one shot on its variant's sign program (program.h): it draws
+// the shot's noise hits in slot order, XORs each hit's signature into a vector
+// of tests, record words and observables, and stops once no later slot can
+// move the first set test.  What the coefficients decide (SGT_HAND) is left to
+// the sampler kernel, which runs after this one on the pending shots.
+//
+// With gap sampling a shot is a few Philox blocks, table reads and XORs: 10^7
+// shots of the 42-qubit circuit at p = 1e-3 take 0.45 ms (22 G shots/s), bound
+// by the latency of the table reads and by lanes that wait for the longest of
+// their neighbours' shots.  With a word per slot it is bound by the Philox
+// multiplies: 5 10^5 shots at p = 5e-4 (1.4 G words) take 1.2 ms.  In both the
+// sampler kernel is left with the 5% whose noise breaks a T pair: the launches
+// went from 48.3 to 12.1 ms and from 3.2 to 2.2 ms.
+#include <hip/hip_runtime.h>
+
+#include "device.h"
+#include "program.h"
+#include "sampler.h"
+
+namespace soft {
+namespace {
+
+__device__ __forceinline__ uint64_t first64(uint64_t x) {
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    return ((uint64_t)hi << 32) | (uint64_t)lo;
+}
+__device__ __forceinline__ uint32_t first32(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+
+// floor(mul w / (d1 + 1)) for mul = 3 or 15 and w <= d1
+__device__ __forceinline__ uint32_t part(uint32_t mul, uint32_t w, uint32_t d1) {
+    if (d1 == 0xFFFFFFFFu) return __umulhi(mul, w);
+    return quot16((uint64_t)mul * w, (uint64_t)d1 + 1ull);
+}
+
+// Lanes that run one shot together.  With gap sampling a shot draws a few
+// words: one lane each, 64 shots in flight.  With a word per slot a shot draws
+// thousands: 16 lanes take 64 consecutive slots a step, so that a shot's chain
+// of steps is short (one lane per shot left a launch of 500 000 shots waiting
+// for single shots of 1329 steps) and a wave still holds four shots.
+template <bool GAPS> constexpr uint32_t kLanes = GAPS ? 1u : 16u;
+
+// Idle lanes take new shots once this many wait: a start costs about as much
+// as a step of one-lane shots, whether one lane or all take it.
+constexpr uint32_t kRefill = 16;
+
+template <int TW, int RO, bool GAPS>
+__global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
+    constexpr int W = TW + RO, Q = W / 4;
+    constexpr uint32_t GL = kLanes<GAPS>;
+    static_assert(W % 4 == 0, "vectors are read four words at a time");
+    __shared__ uint32_t hist[kMaxCheckpoints + 1];
+    const uint32_t lane = threadIdx.x, sub = lane % GL;
+    const uint32_t key0 = (uint32_t)P.seed, key1 = (uint32_t)(P.seed >> 32);
+    const uint64_t below = (1ull << (lane - sub)) - 1ull;
+    if (lane <= kMaxCheckpoints) hist[lane] = 0u;
+
+    // the variant of the shots in flight, and their counts
+    uint32_t var = 0, n_noise = 0, vec_off = 0, slot_off = 0, test_off = 0, ref_vec = 0, coin_off = 0, n_coins = 0;
+    uint32_t ck_cnt = 0, n_tests = 0, on = 0, tm1_off = 0, gap_off = 0;
+    float l2q = 0.0f;
+    uint64_t var_lo = 0, var_end = 0;
+    uint64_t n_pass = 0, n_disc = 0, n_logical = 0, n_prefix = 0;
+    uint64_t words = 0;  // of this lane
+    auto flush = [&]() {
+        unsigned long long *row = P.counters + (size_t)var * C_COUNT;
+        for (int o = 32; o >= 1; o >>= 1) words += __shfl_xor((unsigned long long)words, o, 64);
+        const uint64_t v = lane == C_SHOTS ? n_pass + n_disc : lane == C_PASSED ? n_pass : lane == C_DISCARDED ? n_disc
+                         : lane == C_LOGICAL ? n_logical : lane == C_NOISE ? words : lane == C_PREFIX ? n_prefix : 0ull;
+        if (v) atomicAdd(row + lane, (unsigned long long)v);
+        if (lane <= kMaxCheckpoints) {
+            if (hist[lane]) atomicAdd(row + C_CK0 + lane, (unsigned long long)hist[lane]);
+            hist[lane] = 0u;
+        }
+        n_pass = n_disc = n_logical = n_prefix = words = 0;
+    };
+
+    // Run positions [cur, end) of this wave's chunk are still to start.
+    WorkQueue queue(P.next, blockIdx.x, gridDim.x, (P.n_shots + P.chunk - 1u) / P.chunk);
+    uint64_t cur = 0, end = 0;
+
+    // ---- the lane's shot ----
+    bool act = false;
+    uint64_t i = 0;
+    uint32_t s_lo = 0, s_hi = 0;
+    uint32_t x[W];
+    uint32_t pos = 0;    // next word (GAPS) or noise slot (multiples of 4)
+    uint32_t drawn = 0;  // GAPS: slots decided
+    uint32_t row = 0;    // first set test, or n_tests
+    uint32_t limit = 0;  // noise slots that can still move it
+    uint32_t ck = 0;     // checkpoints before the first hit
+#pragma unroll
+    for (int w = 0; w < W; ++w) x[w] = 0u;
+    auto add_vec = [&](uint32_t vec) {
+        const uint4 *p = P.vecs + (size_t)vec * Q;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint4 u = p[q];
+            x[4 * q] ^= u.x;
+            x[4 * q + 1] ^= u.y;
+            x[4 * q + 2] ^= u.z;
+            x[4 * q + 3] ^= u.w;
+        }
+    };
+    auto find_first = [&]() {
+        uint32_t t = n_tests;
+#pragma unroll
+        for (int w = TW - 1; w >= 0; --w)
+            if (x[w]) t = 32u * w + (uint32_t)__builtin_ctz(x[w]);
+        row = t;
+        limit = P.tests[test_off + t].stop;
+    };
+    // the signature of a hit at slot s, its Pauli from the word w <= d1, into v
+    auto hit = [&](uint32_t (&v)[W], uint32_t s, const SignSlot &sl, uint32_t w, uint32_t d1) {
+        uint32_t a = 1u, b = 0u;
+        if (sl.kind == NZ_DEP1) {
+            a = part(3u, w, d1) + 1u;
+        } else if (sl.kind == NZ_DEP2) {
+            const uint32_t code = part(15u, w, d1) + 1u;
+            a = code >> 2;
+            b = code & 3u;
+        } else if (sl.kind == NZ_ZERR) {
+            a = 3u;
+        }
+        const uint32_t v0 = vec_off + kSignVecs * s - 1u;
+        const uint32_t va = a ? v0 + a : 0u, vb = b ? v0 + 3u + b : 0u;
+        const uint4 *pa = P.vecs + (size_t)va * Q, *pb = P.vecs + (size_t)vb * Q;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint4 ua = pa[q], ub = pb[q];
+            v[4 * q] ^= ua.x ^ ub.x;
+            v[4 * q + 1] ^= ua.y ^ ub.y;
+            v[4 * q + 2] ^= ua.z ^ ub.z;
+            v[4 * q + 3] ^= ua.w ^ ub.w;
+        }
+    };
+
+    for (;;) {
+        // ---- idle lanes take shots ----
+        const uint64_t idle = __ballot(!act);
+        const uint32_t n_idle = (uint32_t)__builtin_popcountll(idle);
+        if (n_idle >= kRefill) {
+            uint64_t got;
+            if (cur == end && queue.take(lane, got)) {
+                cur = got * P.chunk;
+                end = min(cur + P.chunk, P.n_shots);
+            }
+            if (cur == end && n_idle == 64u) break;
+            if (cur != end) {
+                uint64_t shot = P.shot0 + cur;
+                bool ready = shot >= var_lo && shot < var_end;
+                if (!ready && n_idle == 64u) {  // another variant, once no lane runs the last one
+                    if (var_end) flush();
+                    var = 0;
+                    while (var + 1u < P.n_vars && P.vars[var].shot_end <= shot) ++var;
+                    var = first32(var);
+                    const SignDesc &D = P.desc[var];
+                    const VariantDesc &V = P.vars[var];
+                    var_lo = first64(var ? P.vars[var - 1u].shot_end : 0ull);
+                    var_end = first64(V.shot_end);
+                    n_noise = first32(V.n_noise);
+                    on = first32(D.on) & (GAPS ? 1u : 2u);
+                    n_tests = first32(D.n_tests);
+                    vec_off = first32(D.vec_off);
+                    slot_off = first32(D.slot_off);
+                    test_off = first32(D.test_off);
+                    ref_vec = first32(D.ref_vec);
+                    coin_off = first32(D.coin_off);
+                    n_coins = first32(D.n_coins);
+                    ck_cnt = first32(D.ck_cnt);
+                    tm1_off = first32(V.tm1_off);
+                    gap_off = first32(V.gap_off);
+                    l2q = V.gap_l2q;
+                    ready = true;
+                }
+                if (ready) {
+                    const uint64_t left = min(end, var_end - P.shot0) - cur;
+                    const uint32_t take = (uint32_t)min(left, (uint64_t)(n_idle / GL));
+                    const uint32_t rank = (uint32_t)__builtin_popcountll(idle & below) / GL;
+                    if (!act && rank < take) {
+                        i = cur + rank;
+                        if (!on) {
+                            if (sub == 0u) P.status[i] = kStatusPending;
+                        } else {
+                            act = true;
+                            s_lo = (uint32_t)(P.shot0 + i);
+                            s_hi = (uint32_t)((P.shot0 + i) >> 32);
+#pragma unroll
+                            for (int w = 0; w < W; ++w) x[w] = 0u;
+                            add_vec(ref_vec);
+                            pos = drawn = 0u;
+                            ck = ck_cnt;
+                            uint32_t have = 0xFFFFFFFFu, c0 = 0, c1 = 0, c2 = 0, c3 = 0;
+                            for (uint32_t c = 0; c < n_coins; ++c) {
+                                const uint2 cn = P.coins[coin_off + c];
+                                if ((cn.x >> 2) != have) {
+                                    have = cn.x >> 2;
+                                    philox10<true>(have, s_lo, s_hi, 1u, key0, key1, c0, c1, c2, c3);
+                                }
+                                const uint32_t q = cn.x & 3u;
+                                // outcome 1 iff (word + 1/2) 2^-32 >= 1/2
+                                if ((q == 0u ? c0 : q == 1u ? c1 : q == 2u ? c2 : c3) >> 31) add_vec(cn.y);
+                            }
+                            find_first();
+                        }
+                    }
+                    cur += take;
+                }
+            }
+        }
+
+        // ---- one step of every shot in flight ----
+        bool run = act;
+        uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0, m = 0;
+        if (act) {
+            philox10<true>((pos >> 2) + sub, s_lo, s_hi, GAPS ? 2u : 0u, key0, key1, w0, w1, w2, w3);
+            if (GAPS) {
+                // Two candidates a block (gap word, acceptance word).  The gap
+                // is the table's #{j : w < tb[j]}; its estimate from the
+                // word's logarithm puts four entries around it, which decide
+                // it unless they do not bracket it (then a binary search).
+                const uint32_t *tb = P.gaps + gap_off;
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    if (!run) continue;
+                    const uint32_t w = half ? w2 : w0, aw = half ? w3 : w1;
+                    pos += 2u;
+                    const uint32_t lim = n_noise - drawn;
+                    const float est = fminf(fmaxf((__log2f((float)w + 0.5f) - 32.0f) * l2q, 0.0f), (float)lim);
+                    const uint32_t b = max((uint32_t)est, 2u) - 2u;
+                    uint32_t t[4];
+                    __builtin_memcpy(t, tb + b, 16);
+                    const uint32_t n = (w < t[0] ? 1u : 0u) + (w < t[1] ? 1u : 0u) + (w < t[2] ? 1u : 0u) + (w < t[3] ? 1u : 0u);
+                    uint32_t G = b + n;
+                    if (n == 4u || (n == 0u && b != 0u)) {
+                        uint32_t lo = 0, hi = lim;  // w < tb[j] for j < lo, not for j >= hi (or past the slots)
+                        while (lo < hi) {
+                            const uint32_t m = (lo + hi) >> 1;
+                            if (w < tb[m]) lo = m + 1u;
+                            else hi = m;
+                        }
+                        G = lo;
+                    }
+                    const uint32_t s = drawn + min(G, lim);
+                    if (s >= limit) {
+                        run = false;
+                        continue;
+                    }
+                    drawn = s + 1u;
+                    const SignSlot sl = P.slots[slot_off + s];
+                    if (aw <= sl.acc1 && sl.kind != NZ_NONE) {
+                        hit(x, s, sl, aw, sl.acc1);
+                        ck = min(ck, sl.ckpt);
+                        find_first();
+                    }
+                    if (drawn >= limit) run = false;
+                }
+            } else {
+                // Signatures only reach forward, so hits past `limit` may be
+                // taken too: they change nothing at or before test `row`.
+                const uint32_t s0 = pos + 4u * sub;
+                const uint4 th = *reinterpret_cast<const uint4 *>(P.tm1 + tm1_off + s0);
+                m = (w0 <= th.x ? 1u : 0u) | (w1 <= th.y ? 2u : 0u) | (w2 <= th.z ? 4u : 0u) | (w3 <= th.w ? 8u : 0u);
+            }
+        }
+        if (!GAPS && __ballot(m != 0u) != 0ull) {
+            uint32_t d[W], dck = 0xFFFFFFFFu;  // what this lane's hits change
+#pragma unroll
+            for (int w = 0; w < W; ++w) d[w] = 0u;
+            while (m) {
+                const uint32_t j = (uint32_t)__builtin_ctz(m), s = pos + 4u * sub + j;
+                m &= m - 1u;
+                if (s >= n_noise) break;
+                const SignSlot sl = P.slots[slot_off + s];
+                const uint32_t w = j == 0u ? w0 : j == 1u ? w1 : j == 2u ? w2 : w3;
+                if (sl.kind != NZ_NONE) {
+                    hit(d, s, sl, w, sl.thr1);
+                    if (s < limit) dck = min(dck, sl.ckpt);
+                }
+            }
+#pragma unroll
+            for (uint32_t o = GL / 2u; o >= 1u; o >>= 1) {
+#pragma unroll
+                for (int w = 0; w < W; ++w) d[w] ^= (uint32_t)__shfl_xor((int)d[w], (int)o, 64);
+                dck = min(dck, (uint32_t)__shfl_xor((int)dck, (int)o, 64));
+            }
+#pragma unroll
+            for (int w = 0; w < W; ++w) x[w] ^= d[w];
+            ck = min(ck, dck);
+            if (act) find_first();
+        }
+        if (!GAPS) {
+            pos += 4u * GL;
+            run = act && pos < limit;
+        }
+
+        // ---- shots that ended ----
+        const bool fin = act && !run;
+        if (__ballot(fin) != 0ull) {
+            bool pass = false, disc = false, logical = false;
+            if (fin) {
+                act = false;
+                const SignTest T = P.tests[test_off + row];
+                if (sub != 0u) {
+                    // the group's first lane writes
+                } else if (T.kind == SGT_HAND) {
+                    P.status[i] = kStatusPending;
+                } else {
+                    const uint32_t *mk = P.mask + (size_t)(test_off + row) * RO;
+                    const uint32_t obs = x[W - 1] & mk[RO - 1];
+                    pass = T.kind == SGT_NONE;
+                    disc = !pass;
+                    logical = pass && obs != 0u;
+                    P.status[i] = pass ? (uint32_t)ST_PASSED : (uint32_t)ST_DISCARDED;
+                    if (P.abort_op) P.abort_op[i] = T.src;
+                    if (P.obs) P.obs[i] = obs;
+                    if (P.outcomes) {
+#pragma unroll
+                        for (int w = 0; w < RO - 1; ++w)
+                            if ((uint32_t)w < P.rec_words) P.outcomes[(uint64_t)w * P.n_shots + i] = x[TW + w] & mk[w];
+                    }
+                    words += GAPS ? pos : min(pos, n_noise);
+                    atomicAdd(&hist[ck], 1u);
+                }
+            }
+            n_pass += (uint32_t)__builtin_popcountll(__ballot(pass));
+            n_disc += (uint32_t)__builtin_popcountll(__ballot(disc));
+            n_logical += (uint32_t)__builtin_popcountll(__ballot(logical));
+            n_prefix += (uint32_t)__builtin_popcountll(__ballot((pass || disc) && ck != 0u && P.prefix != 0u));
+        }
+    }
+    if (var_end) flush();
+}
+
+template <int TW, int RO> const void *kernel_of(bool gaps) {
+    return gaps ? (const void *)k_signs<TW, RO, true> : (const void *)k_signs<TW, RO, false>;
+}
+}  // namespace
+
+const void *signs_kernel(uint32_t size, bool gaps) {
+    switch (size) {
+        case 0: return kernel_of<2, 2>(gaps);
+        case 1: return kernel_of<4, 4>(gaps);
+        case 2: return kernel_of<8, 8>(gaps);
+        default: return kernel_of<16, 16>(gaps);
+    }
+}
+
+hipError_t launch_signs(const SignParams &p, uint32_t size, bool gaps, dim3 grid, hipStream_t stream) {
+    void *args[1] = {(void *)&p};
+    return hipLaunchKernel(signs_kernel(size, gaps), grid, dim3(kSignBlock), args, 0, stream);
+}
+
+}  // namespace soft

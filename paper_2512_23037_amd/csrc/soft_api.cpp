@@ -21,6 +21,7 @@
 
 #include "compile.h"
 #include "sampler.h"
+#include "signs.h"
 
 using namespace soft;
 
@@ -43,8 +44,9 @@ struct Variant {
     bool has_fast = false;
 };
 
-// counter rows, then the sampler's and the prefix build's work cursors
-constexpr size_t kCounterWords = (size_t)kMaxVariants * C_COUNT + 2;
+// counter rows, then the work cursors (on a cache line's start)
+constexpr size_t kCursorOff = ((size_t)kMaxVariants * C_COUNT + kCursorStride - 1) / kCursorStride * kCursorStride;
+constexpr size_t kCounterWords = kCursorOff + kCursorWords;
 static_assert(kCounterWords * sizeof(unsigned long long) <= kScratchCounterBytes, "scratch counter area");
 
 // Kept final states: at most this many shots, and at most kMaxKeepBytes of
@@ -108,6 +110,10 @@ struct soft_ctx {
     DevBuf<unsigned char> d_prefix;           // checkpoint state slots (one per table entry)
     DevBuf<Checkpoint> d_ckpt;                // checkpoint table
     uint32_t n_ckpt = 0;                      // its entries
+    DevBuf<unsigned char> d_signs;            // the sign pass's tables, one after the other
+    SignParams sign_tables = {};              // their places in it
+    uint32_t sign_size = 0;                   // their vector size (kSignTestWords)
+    uint32_t sign_on = 0;                     // some variant's shots are worth it: bit 0 gaps, bit 1 slots
     unsigned long long *d_counters = nullptr;  // kMaxVariants rows of C_COUNT, then the work cursor
     const unsigned long long *last_counters = nullptr;  // counters of the last run
     double *d_phase = nullptr;                 // cos/sin of k pi/8, k = 0..15
@@ -141,6 +147,8 @@ struct soft_ctx {
         std::vector<unsigned char> key;  // kernel, grid, block, LDS, counters
         RunParams args;                  // argument storage of the sampler node
         RunParams bargs;                 // and of the prefix build node
+        hipGraphNode_t signs = nullptr;  // the sign pass (before the sampler), if any
+        SignParams sargs;
         unsigned long long *r_counters = nullptr, *r_next = nullptr;  // reset node arguments
         uint32_t r_n = 0;
     };
@@ -235,7 +243,7 @@ RunParams build_params(const RunParams &rp) {
     b.trace_v = nullptr;
     b.trace_n = 0;
     b.grab = 1;
-    b.next = rp.next + 1;
+    b.next = rp.next + (kBuildCursor - kSampleCursor);
     return b;
 }
 
@@ -254,6 +262,7 @@ void drop_slot(soft_ctx *c, soft_ctx::GraphSlot &g) {
     g.graph = nullptr;
     g.sampler = nullptr;
     g.build = nullptr;
+    g.signs = nullptr;
     g.launched = false;
     g.key.clear();
     (void)c;
@@ -286,6 +295,107 @@ int compile_variant(soft_ctx *c, Variant &V) {
     for (const Event &E : V.fast.events)
         if (E.kind == EV_DROP || (E.flags & EVF_DROP1)) V.has_fast = true;
     if (!V.has_fast) V.fast = Program();
+    return SOFT_OK;
+}
+
+// A list is worth the sign pass when the signs decide it to its end, or when
+// they end enough shots before the coefficients matter: the others are drawn
+// twice.  Drawing by gaps costs little of a shot, a word per slot much of it.
+constexpr double kSignEndsGaps = 0.02, kSignEndsSlots = 0.25;
+
+// The sign pass's tables: every variant's sign program in the smallest common
+// vector size.
+int prepare_signs(soft_ctx *c) {
+    const size_t nv = c->vars.size();
+    std::vector<SignProgram> sp(nv);
+    c->sign_on = 0;
+    c->sign_size = 0;
+    auto fits = [](const SignProgram &S, uint32_t k) {
+        return S.need.tests <= kSignTestWords[k] && S.need.out() <= kSignOutWords[k];
+    };
+    for (size_t v = 0; v < nv; ++v) {
+        const Variant &V = c->vars[v];
+        // (a mixture often holds one circuit at several rates: only the
+        // thresholds differ)
+        build_signs(V.has_fast ? V.fast : V.prog, sp[v]);
+        SignProgram &S = sp[v];
+        S.on = S.on && fits(S, 3u) && (S.complete || S.ends >= kSignEndsGaps);
+        if (!S.on) continue;
+        while (!fits(S, c->sign_size)) ++c->sign_size;
+        c->sign_on |= 1u | ((S.complete || S.ends >= kSignEndsSlots) ? 2u : 0u);
+    }
+    if (!c->sign_on) return SOFT_OK;
+    const uint32_t TW = kSignTestWords[c->sign_size], RO = kSignOutWords[c->sign_size], W = TW + RO;
+    std::vector<SignDesc> desc(nv);
+    std::vector<SignSlot> slot;
+    std::vector<SignTest> test;
+    std::vector<uint32_t> vec(W, 0u), mask;  // vector 0 is zero
+    std::vector<uint2> coin;
+    std::memset(desc.data(), 0, nv * sizeof(SignDesc));
+    // a program vector (tests, records, observables) in the launch's layout
+    auto lay = [&](const uint32_t *x, const SignProgram &S, uint32_t *d) {
+        for (uint32_t w = 0; w < S.need.tests; ++w) d[w] = x[w];
+        for (uint32_t w = 0; w < S.need.recs; ++w) d[TW + w] = x[S.need.tests + w];
+        d[W - 1u] = x[S.need.tests + S.need.recs];
+    };
+    for (size_t v = 0; v < nv; ++v) {
+        const SignProgram &S = sp[v];
+        SignDesc &D = desc[v];
+        if (!S.on) continue;
+        auto put = [&](const std::vector<uint32_t> &x) {
+            const uint32_t at = (uint32_t)(vec.size() / W);
+            vec.resize(vec.size() + W, 0u);
+            lay(x.data(), S, &vec[(size_t)at * W]);
+            return at;
+        };
+        D.on = 1u | ((S.complete || S.ends >= kSignEndsSlots) ? 2u : 0u);
+        D.n_tests = (uint32_t)S.tests.size() - 1u;
+        D.slot_off = (uint32_t)slot.size();
+        D.test_off = (uint32_t)test.size();
+        slot.insert(slot.end(), S.slots.begin(), S.slots.end());
+        test.insert(test.end(), S.tests.begin(), S.tests.end());
+        for (const auto &m : S.mask) {
+            mask.resize(mask.size() + RO, 0u);
+            uint32_t *d = &mask[mask.size() - RO];
+            for (uint32_t w = 0; w < S.need.recs; ++w) d[w] = m[w];
+            d[RO - 1u] = m.back();
+        }
+        D.ref_vec = put(S.ref);
+        if (v > 0 && sp[v - 1].on && sp[v - 1].vecs == S.vecs && sp[v - 1].need.tests == S.need.tests) {
+            D.vec_off = desc[v - 1].vec_off;  // the same circuit at another rate
+        } else {
+            D.vec_off = (uint32_t)(vec.size() / W);
+            const size_t w0 = S.ref.size(), k = S.vecs.size() / w0;
+            vec.resize(vec.size() + k * W, 0u);
+            for (size_t i = 0; i < k; ++i) lay(&S.vecs[i * w0], S, &vec[(D.vec_off + i) * W]);
+        }
+        D.coin_off = (uint32_t)coin.size();
+        D.n_coins = (uint32_t)S.coin.size();
+        for (size_t i = 0; i < S.coin.size(); ++i) coin.push_back(make_uint2(S.coin_slot[i], put(S.coin[i])));
+        const Program &P = c->vars[v].has_fast ? c->vars[v].fast : c->vars[v].prog;
+        D.ck_cnt = (uint32_t)P.ckpts.size();
+    }
+    // one allocation and one copy
+    std::vector<unsigned char> all;
+    auto put = [&](const void *src, size_t bytes) {
+        const size_t at = (all.size() + 255u) & ~(size_t)255u;
+        all.resize(at + bytes);
+        if (bytes) std::memcpy(&all[at], src, bytes);
+        return at;
+    };
+    const size_t at[6] = {put(vec.data(), vec.size() * sizeof(uint32_t)), put(slot.data(), slot.size() * sizeof(SignSlot)),
+                          put(test.data(), test.size() * sizeof(SignTest)), put(mask.data(), mask.size() * sizeof(uint32_t)),
+                          put(coin.data(), coin.size() * sizeof(uint2)), put(desc.data(), nv * sizeof(SignDesc))};
+    int rc = ensure(c, c->d_signs, all.size());
+    if (rc) return rc;
+    HIPCHK(c, hipMemcpy(c->d_signs.p, all.data(), all.size(), hipMemcpyHostToDevice));
+    SignParams &T = c->sign_tables;
+    T.vecs = reinterpret_cast<const uint4 *>(c->d_signs.p + at[0]);
+    T.slots = reinterpret_cast<const SignSlot *>(c->d_signs.p + at[1]);
+    T.tests = reinterpret_cast<const SignTest *>(c->d_signs.p + at[2]);
+    T.mask = reinterpret_cast<const uint32_t *>(c->d_signs.p + at[3]);
+    T.coins = reinterpret_cast<const uint2 *>(c->d_signs.p + at[4]);
+    T.desc = reinterpret_cast<const SignDesc *>(c->d_signs.p + at[5]);
     return SOFT_OK;
 }
 
@@ -350,6 +460,7 @@ int prepare(soft_ctx *c) {
         nz.insert(nz.end(), P.noise.begin(), P.noise.end());
         tm1.insert(tm1.end(), P.noise_tm1.begin(), P.noise_tm1.end());
         gap.insert(gap.end(), P.gap.begin(), P.gap.end());
+        gap.insert(gap.end(), 8u, 0u);  // the sign pass reads four entries from an estimate up to the end
         vd.push_back(D);
         c->kmax = std::max(c->kmax, P.kmax);
         c->rec_words = std::max(c->rec_words, (P.n_rec + 31u) / 32u);
@@ -376,6 +487,7 @@ int prepare(soft_ctx *c) {
     if (!bm.empty()) HIPCHK(c, hipMemcpy(c->d_bm.p, bm.data(), bm.size() * sizeof(BatchMember), hipMemcpyHostToDevice));
     if (!dg.empty()) HIPCHK(c, hipMemcpy(c->d_diag.p, dg.data(), dg.size() * sizeof(DiagInfo), hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(c->d_vars.p, vd.data(), vd.size() * sizeof(VariantDesc), hipMemcpyHostToDevice));
+    if ((rc = prepare_signs(c))) return rc;
     c->dirty = false;
     drop_graph(c);
     return SOFT_OK;
@@ -499,6 +611,54 @@ void set_wave_layout(const soft_ctx *c, const Shape &s, RunParams &rp) {
     rp.lds_entries = s.gt == TM_SPLIT ? (1u << s.lds_log2) : 0u;
 }
 
+// Whether a launch runs the sign pass: its results stand on T pairs that
+// cancel exactly and on checkpoints and deferred runs being allowed to skip
+// their work, so every option that asks for that work keeps it (and a pruning
+// threshold above rounding changes the states it would skip); kept states,
+// traces, caps, shot lists and explicit words need the sampler's own walk.
+constexpr double kSignMaxTau = 1e-6;
+bool use_signs(const soft_ctx *c, const RunParams &rp) {
+    const uint32_t bit = rp.noise_mode == 1u ? 1u : 2u;
+    return (c->sign_on & bit) && sampler_lean(rp) && c->speculate && c->shared_prefix && c->defer_t &&
+           tau_of(c) <= kSignMaxTau;
+}
+
+// The sign pass's arguments and grid (waves), after rp's outputs, counters and
+// cursors are set.
+uint32_t sign_params(const soft_ctx *c, const RunParams &rp, SignParams &sp) {
+    sp = c->sign_tables;
+    sp.vars = rp.vars;
+    sp.tm1 = rp.tm1;
+    sp.gaps = rp.gaps;
+    sp.outcomes = rp.outcomes;
+    sp.status = rp.status;
+    sp.abort_op = rp.abort_op;
+    sp.obs = rp.obs;
+    sp.counters = rp.counters;
+    sp.next = rp.next - kSampleCursor + kSignCursor;
+    sp.seed = rp.seed;
+    sp.shot0 = rp.shot0;
+    sp.n_shots = rp.n_shots;
+    sp.n_vars = rp.n_vars;
+    sp.rec_words = rp.rec_words;
+    sp.prefix = rp.prefix ? 1u : 0u;
+    // no more waves than stay resident: the chunks are dealt out evenly
+    const uint64_t most = (uint64_t)c->num_cus * kSignWavesPerCu[c->sign_size];
+    // whole waves of shots (64 with gap sampling, 4 with a word per slot), a
+    // few chunks a wave
+    const uint64_t held = rp.noise_mode == 1u ? 64u : 4u;
+    sp.chunk = (uint32_t)(held * std::min<uint64_t>(16u, std::max<uint64_t>(1u, rp.n_shots / (most * held * 8u))));
+    return (uint32_t)std::min<uint64_t>(most, (rp.n_shots + sp.chunk - 1u) / sp.chunk);
+}
+
+// Positions a wave of the sampler takes at a time after the sign pass, which
+// leaves few of them to run: as many as one wave reads, fewer when the launch
+// is small (not below the default: each steal is an atomic on one address).
+uint32_t sign_grab(const soft_ctx *c, const Shape &s, uint64_t grid, uint64_t n_shots) {
+    if (c->user.grab) return c->user.grab;
+    return (uint32_t)std::min<uint64_t>(64u, std::max<uint64_t>(s.grab, n_shots / (grid * s.wpb)));
+}
+
 int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStream_t stream) {
     const uint32_t wb = wave_bytes(c, s);
     const size_t lds = (size_t)s.wpb * wb;
@@ -521,12 +681,23 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
         rp.prefix_stride = prefix_stride(c);
     }
     const uint64_t bgrid = std::min<uint64_t>(grid, (2ull * rp.n_vars + s.wpb - 1) / s.wpb);
+    const bool sgn = use_signs(c, rp);
+    SignParams sp;
+    uint32_t sgrid = 0;
+    const void *sfn = nullptr;
+    std::memset(&sp, 0, sizeof(sp));
+    if (sgn) {
+        rp.signs = 1;
+        rp.grab = sign_grab(c, s, grid, n_shots);
+        sgrid = sign_params(c, rp, sp);
+        sfn = signs_kernel(c->sign_size, rp.noise_mode == 1u);
+    }
     const uint32_t ns = rp.words != nullptr ? NS_EXPLICIT : (rp.noise_mode == 1u ? NS_GAPS : NS_SLOTS);
     const void *kfn = sampler_kernel(c->bits == 64, ns, s.gt, sampler_lean(rp));
     // what the nodes' launch configuration and the reset node depend on
-    const uint64_t kv[9] = {(uint64_t)(uintptr_t)kfn, grid, (uint64_t)b.x, (uint64_t)lds,
+    const uint64_t kv[11] = {(uint64_t)(uintptr_t)kfn, grid, (uint64_t)b.x, (uint64_t)lds,
                             (uint64_t)(uintptr_t)rp.counters, (uint64_t)rp.n_vars, (uint64_t)(uintptr_t)rp.next,
-                            (uint64_t)pfx, pfx ? bgrid : 0ull};
+                            (uint64_t)pfx, pfx ? bgrid : 0ull, (uint64_t)(uintptr_t)sfn, (uint64_t)sgrid};
     std::vector<unsigned char> key((const unsigned char *)kv, (const unsigned char *)kv + sizeof(kv));
     // The slot to use: one with this key whose last launch is done; else an
     // empty one (instantiated below); else one with this key (after waiting
@@ -552,12 +723,19 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     if (gs.launched) HIPCHK(c, hipEventSynchronize(gs.done));  // its previous launch may still read its arguments
     gs.args = rp;
     gs.bargs = build_params(rp);
+    gs.sargs = sp;
     void *args[7] = {(void *)&gs.args.ev, (void *)&gs.args.nz, (void *)&gs.args.tm1, (void *)&gs.args.det,
                      (void *)&gs.args.words, (void *)&gs.args.bm, (void *)&gs.args};
     void *bargs[7] = {(void *)&gs.bargs.ev, (void *)&gs.bargs.nz, (void *)&gs.bargs.tm1, (void *)&gs.bargs.det,
                       (void *)&gs.bargs.words, (void *)&gs.bargs.bm, (void *)&gs.bargs};
-    hipKernelNodeParams kp, kb;
+    void *sargs[1] = {(void *)&gs.sargs};
+    hipKernelNodeParams kp, kb, ks;
     std::memset(&kp, 0, sizeof(kp));
+    std::memset(&ks, 0, sizeof(ks));
+    ks.func = const_cast<void *>(sfn);
+    ks.gridDim = dim3(sgrid);
+    ks.blockDim = dim3(kSignBlock);
+    ks.kernelParams = sargs;
     kp.func = const_cast<void *>(kfn);
     kp.gridDim = g;
     kp.blockDim = b;
@@ -569,12 +747,13 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     kb.kernelParams = bargs;
     if (gs.exec && gs.key == key) {
         if (pfx) HIPCHK(c, hipGraphExecKernelNodeSetParams(gs.exec, gs.build, &kb));
+        if (sgn) HIPCHK(c, hipGraphExecKernelNodeSetParams(gs.exec, gs.signs, &ks));
         HIPCHK(c, hipGraphExecKernelNodeSetParams(gs.exec, gs.sampler, &kp));
     } else {
         drop_slot(c, gs);
         gs.r_counters = rp.counters;
         gs.r_n = rp.n_vars * (uint32_t)C_COUNT;
-        gs.r_next = rp.next;
+        gs.r_next = rp.next - kSampleCursor;
         void *rargs[3] = {(void *)&gs.r_counters, (void *)&gs.r_n, (void *)&gs.r_next};
         hipKernelNodeParams rk;
         std::memset(&rk, 0, sizeof(rk));
@@ -589,6 +768,10 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
         if (e == hipSuccess && pfx) {
             e = hipGraphAddKernelNode(&gs.build, gs.graph, &rnode, 1, &kb);
             before = gs.build;
+        }
+        if (e == hipSuccess && sgn) {
+            e = hipGraphAddKernelNode(&gs.signs, gs.graph, &before, 1, &ks);
+            before = gs.signs;
         }
         if (e == hipSuccess) e = hipGraphAddKernelNode(&gs.sampler, gs.graph, &before, 1, &kp);
         if (e == hipSuccess) e = hipGraphInstantiate(&gs.exec, gs.graph, nullptr, nullptr, 0);
@@ -631,7 +814,7 @@ int make_params(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcome
     rp.abort_op = abort_op;
     rp.obs = obs;
     rp.counters = c->d_counters;
-    rp.next = c->d_counters + kCounterWords - 2;
+    rp.next = c->d_counters + kCursorOff + kSampleCursor;
     rp.seed = c->seed;
     rp.shot0 = shot0;
     rp.n_shots = n_shots;
@@ -856,6 +1039,7 @@ void soft_destroy(soft_ctx *c) {
     release(c->d_gtile);
     release(c->d_prefix);
     release(c->d_ckpt);
+    release(c->d_signs);
     release(c->d_keep_meta);
     release(c->d_keep_v);
     release(c->d_trace_meta);
@@ -1093,7 +1277,7 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
     // the scratch holds (the kernel is persistent, so fewer waves take more
     // shots each)
     rp.counters = reinterpret_cast<unsigned long long *>(c->scratch);
-    rp.next = rp.counters + kCounterWords - 2;
+    rp.next = rp.counters + kCursorOff + kSampleCursor;
     // shared-prefix slots when they fit their part of the scratch (without
     // them every shot runs from the start: the same results)
     const bool pfx = use_prefix(c) && (uint64_t)c->n_ckpt * prefix_stride(c) <= kScratchPrefixBytes;
@@ -1112,11 +1296,18 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
         rp.gtile = c->scratch + kScratchCounterBytes + kScratchPrefixBytes;
     }
     const hipStream_t stream = (hipStream_t)hip_stream;
-    HIPCHK(c, launch_reset(rp.counters, rp.n_vars * (uint32_t)C_COUNT, rp.next, stream));
+    HIPCHK(c, launch_reset(rp.counters, rp.n_vars * (uint32_t)C_COUNT, rp.next - kSampleCursor, stream));
     if (pfx)
         HIPCHK(c, launch_prefix_build(build_params(rp), c->bits == 64,
                                  dim3((uint32_t)std::min<uint64_t>(grid, (2ull * rp.n_vars + s.wpb - 1) / s.wpb)),
                                  dim3(64u * s.wpb), (size_t)s.wpb * wave_bytes(c, s), stream));
+    if (use_signs(c, rp)) {
+        rp.signs = 1;
+        rp.grab = sign_grab(c, s, grid, n_shots);
+        SignParams sp;
+        const uint32_t sgrid = sign_params(c, rp, sp);
+        HIPCHK(c, launch_signs(sp, c->sign_size, rp.noise_mode == 1u, dim3(sgrid), stream));
+    }
     HIPCHK(c, launch_sampler(rp, c->bits == 64, dim3((uint32_t)grid), dim3(64u * s.wpb),
                              (size_t)s.wpb * wave_bytes(c, s), stream));
     c->ran = true;

@@ -1,0 +1,128 @@
+"""The sign pass on the GPU (signs.hip) against the sampler kernel's own walk
+of the same shots (checkpoints off, which also leaves the sign pass out): whole
+numbers, so equal bit for bit.  Sizes around a wave's lanes, its chunks and the
+launch's waves, every vector size and one circuit past the largest, shot
+offsets across 2^32, variants that meet inside a chunk (one of them left to the
+sampler), null outputs and both noise draws.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import workloads
+from paper_2512_23037_amd import soft
+from tests.gen_small import random_circuit
+from tests.gpu_helpers import make_ctx, run_gpu
+from tests.test_signs import with_checks
+
+pytestmark = pytest.mark.gpu
+
+NOISE = {k: 4e-3 for k in ("p1", "p2", "p_idle", "p_meas", "p_reset", "p_mpp")}
+
+
+def rounds(n_rounds: int, checks: int = 2) -> str:
+    """T layers that meet their inverses around parity checks, repeated:
+    `checks` records and tests and three T pairs a round."""
+    out = ["QUBITS 6", "H 0", "CX 0 1", "CX 0 2"]
+    rec = 0
+    for _ in range(n_rounds):
+        out += ["T 0", "T 1", "TDG 2"]
+        for c in range(checks):
+            out += ["CX %d %d" % (c, 3 + c), "CX %d %d" % (c + 1, 3 + c), "M %d" % (3 + c), "DETECTOR 0 %d" % rec, "R %d" % (3 + c)]
+            rec += 1
+        out += ["TDG 0", "TDG 1", "T 2"]
+    return "\n".join(out + ["MPP X0*X1*X2", "OBSERVABLE 0 %d" % rec]) + "\n"
+
+
+def both(build, shot0, n):
+    got = []
+    for on in (True, False):
+        ctx = build()
+        ctx.set_shared_prefix(on)
+        got.append((run_gpu(ctx, shot0, n), ctx.counters()))
+        ctx.close()
+    (a, ca), (b, cb) = got
+    for k in ("status", "abort_op", "obs", "outcomes"):
+        assert (a[k] == b[k]).all(), (k, np.nonzero((a[k] != b[k]).reshape(-1, n).any(axis=0))[0][:5])
+    for f in ("shots", "passed", "discarded", "overflow", "numeric", "logical_errors", "restarts"):
+        assert ca[f] == cb[f], f
+    return a, ca, cb
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("n,shot0", [(1, 0), (3, 7), (63, 0), (64, 1), (65, 2**32 - 30), (1023, 5), (4097, 0),
+                                     (70001, 2**40 + 3), (400_001, 2**32 - 200_000)])
+def test_sizes(n, shot0, mode):
+    w = workloads.config("cultivation_15q", seed=1)
+
+    def build():
+        ctx = make_ctx(w.text, NOISE, seed=5)
+        ctx.set_noise_mode(mode)
+        return ctx
+
+    a, ca, cb = both(build, shot0, n)
+    if n > 4000:  # most shots need no coefficients
+        assert ca["events"] < 0.5 * cb["events"]
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("n_rounds", [1, 8, 16, 60, 200, 300])
+def test_vector_sizes(n_rounds, mode):
+    # 3 to 601 records and up to 1500 tests: every vector size, then past the last
+    def build():
+        ctx = make_ctx(rounds(n_rounds), {k: v / n_rounds for k, v in NOISE.items()}, seed=11)
+        ctx.set_noise_mode(mode)
+        return ctx
+
+    both(build, 0, 3000)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_variants_meet_inside_a_chunk(mode):
+    # a circuit without checks before its first random read of coefficients
+    # (left to the sampler) between two that the signs decide
+    texts = [rounds(4), "QUBITS 2\nH 0\nT 0\nMPP X0\nDETECTOR 0 0\nH 1\nT 1\nMPP X1\n", rounds(9),
+             workloads.config("cultivation_15q", seed=1).text]
+    ends = [37, 1500, 1501, 9000]
+
+    def build():
+        ctx = soft.Context(0)
+        ctx.load_mixture(texts, [NOISE] * 4, ends)
+        ctx.set_rng(3)
+        ctx.set_noise_mode(mode)
+        return ctx
+
+    both(build, 0, 9000)
+    both(build, 30, 1475)
+
+
+@pytest.mark.parametrize("seed", range(24))
+def test_random_circuits(seed):
+    rng = np.random.default_rng(700 + seed)
+    text, _ = random_circuit(61000 + seed, int(rng.integers(2, 9)), int(rng.integers(30, 140)),
+                             p_t=0.0 if seed % 3 == 0 else 0.05, p_meas=0.1, p_mpp=0.05, p_reset=0.05,
+                             p_msc=0.15 if seed % 2 else 0.0, p_diag=0.03 if seed % 5 == 1 else 0.0,
+                             p_if=0.05 if seed % 4 == 2 else 0.0)
+
+    def build():
+        ctx = make_ctx(with_checks(text), {**NOISE, "p1": 0.02}, seed=seed, bits=64)
+        ctx.set_noise_mode(seed % 2)
+        return ctx
+
+    both(build, 11 * seed, 2000)
+
+
+def test_null_outputs_and_noalloc():
+    import torch
+    w = workloads.config("cultivation_42q", seed=1)
+    ctx = make_ctx(w.text, w.noise, seed=9, bits=32)
+    ctx.set_noise_mode(1)
+    n = 30_000
+    ref = run_gpu(ctx, 4, n)
+    st = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    for f in (ctx.run, ctx.run_noalloc):
+        st.fill_(-7)
+        f(4, n, status=st)
+        torch.cuda.synchronize()
+        assert (st.cpu().numpy().view(np.uint32) == ref["status"]).all()
