@@ -80,9 +80,10 @@ typedef struct {
                                     that the tableau signs decide the checkpoint's before its
                                     first noise hit) */
     double max_norm_dev;         /* max over shots of |sum |v|^2 - 1| at the end */
-    uint64_t restarts;           /* shots re-run on the full event list: the speculative
-                                    list's span truncation found amplitude left (noise
-                                    broke a T / T-dagger cancellation) */
+    uint64_t restarts;           /* shots where noise broke a T / T-dagger cancellation of the
+                                    speculative list: re-run on the full event list, its
+                                    span truncation having found amplitude left, or
+                                    followed by their signs (soft_set_shared_prefix) */
     uint64_t prefix_shots;       /* attempts that started from a checkpoint of the noiseless
                                     trajectory, or were decided past one
                                     (soft_set_shared_prefix); the work fields above count
@@ -266,8 +267,12 @@ int soft_set_noise_mode(soft_ctx *ctx, int mode);
  * (Theorem 1: T leaves the tableau alone).  With checkpoints, deferred T runs
  * and speculation all on, a pass before the sampler decides the shots that a
  * check ends there, or whose whole list is decided there because every T that
- * the speculative list pairs with its inverse sees its sign; the sampler runs
- * the others.  The same draws and the same results; the counters' work fields
+ * the speculative list pairs with its inverse sees its sign.  Where noise broke
+ * such a pair on a state of one basis entry, T^2 leaves two entries of equal
+ * weight (Eqs. 1-2), and the first measurement that tells them apart is an
+ * even coin, drawn from its own word (p0 = 1/2 exactly, where the sampler's
+ * FP32 p0 is 1/2 to its rounding); the pass follows the entry it leaves.  The
+ * sampler runs the other shots.  The same draws and the same results; the counters' work fields
  * count only the sampler's work.  Kept states, traces, support caps, shot lists,
  * explicit words and a pruning threshold above 1e-6 leave the pass out. */
 int soft_set_shared_prefix(soft_ctx *ctx, int on);

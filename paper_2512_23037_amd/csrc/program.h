@@ -289,23 +289,55 @@ static_assert(sizeof(NoiseLoc) == 96, "noise layout");
 // product is not the identity and the span is not truncated): that sign
 // difference is one more XOR, a test that must be 0 like a check's.  The tests
 // are in list order, so the lowest set one is what ends the shot: a failed
-// check discards it, any other test hands it to the sampler kernel.
+// check discards it, the first read of the coefficients hands it to the
+// sampler kernel.
+//
+// A broken pair is T_P^2 up to a sign, e^{i theta} (I -+ i P) / sqrt 2 (Eqs. 1-2
+// twice): where the state was one basis entry alpha before the bracket, it is
+// now two, alpha and alpha ^ beta, of equal weight, and every measurement of
+// the list is diagonal in alpha.  The first one whose gamma . beta is 1 tells
+// them apart, an even coin; it leaves the entry its outcome asks for, and
+// taking the other entry is one more vector (a flipped by beta).  Several
+// broken pairs with independent betas are a product of such coins, taken apart
+// by the measurements one equation at a time; up to four are, the rest (and
+// dependent ones, which interfere) go to the sampler kernel.
 //
 // A vector holds `tests` words of test bits, then the record words, then one
 // word of observables, in the launch's common layout.
 // ---------------------------------------------------------------------------
 enum SignTestKind : uint32_t {
     SGT_CHECK = 0,  // a detector: the shot is discarded at op `src`
-    SGT_HAND = 1,   // the sampler kernel runs the shot (a broken T pair, or the
-                    // first measurement that reads coefficients)
+    SGT_HAND = 1,   // the sampler kernel runs the shot: the first measurement that reads
+                    // coefficients, or a broken T pair on more than one entry
     SGT_NONE = 2,   // the row after the last test: the shot passed
+    SGT_PAIR = 3,   // a broken T pair that the signs can follow: SignPair `pair`
 };
 struct alignas(16) SignTest {
     uint32_t stop;  // noise slots from `stop` on come after the test
     uint32_t src;   // op index of the detector
     uint32_t kind;  // SignTestKind
-    uint32_t pad;
+    uint32_t pair;
 };
+// A T pair on a single basis entry: its index shift, what `a ^= beta` at its
+// end flips, and the first of the measurements (SignMeas) after it.
+struct alignas(16) SignPair {
+    uint64_t beta;
+    uint32_t vec;
+    uint32_t meas;
+};
+constexpr uint32_t kMaxSignPairs = 256;  // a pending pair takes a byte
+// A measurement that may tell basis entries apart (outcome-fixed in the list).
+struct alignas(16) SignMeas {
+    uint64_t gamma;
+    uint32_t stop;  // noise slots from `stop` on come after it
+    uint32_t test;  // first test at or after it
+    uint32_t slot;  // its measurement word
+    uint32_t rec;   // its record bit; kNoRec: the sampler kernel runs a shot with pairs
+                    // pending here (unrecorded, its record may be flipped by noise, or a
+                    // coin that moves the entries: gamma ~0)
+    uint32_t pad[2];
+};
+constexpr uint32_t kNoRec = 0xFFFFFFFFu;
 // A noise slot as the sign pass reads it: its signature vectors (XERR, FLIP
 // in the first; ZERR in the third) are X_a, Y_a, Z_a, X_b, Y_b, Z_b.
 struct alignas(16) SignSlot {
@@ -326,7 +358,7 @@ struct alignas(16) SignDesc {
     uint32_t ref_vec;   // vector of the noiseless values
     uint32_t coin_off, n_coins;  // coins: (measurement slot, vector) pairs
     uint32_t ck_cnt;             // checkpoints of the variant's first list
-    uint32_t pad[3];
+    uint32_t pair_off, meas_off, n_meas;
 };
 static_assert(sizeof(SignDesc) == 48, "sign program layout");
 

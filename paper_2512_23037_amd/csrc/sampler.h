@@ -68,6 +68,8 @@ struct SignParams {
     const SignTest *tests;
     const uint32_t *mask;     // per test row: record words and observables written by then
     const uint2 *coins;       // (measurement slot, vector)
+    const SignPair *pairs;
+    const SignMeas *meas;
     const uint32_t *tm1, *gaps;  // as RunParams
     uint32_t *outcomes, *status, *abort_op, *obs;
     unsigned long long *counters, *next;

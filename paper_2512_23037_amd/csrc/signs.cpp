@@ -36,12 +36,13 @@ struct Rows {
         for (; s; s &= s - 1) add(v, S[__builtin_ctzll(s)].data(), S[0].size());
     }
     void sum(Vec &v, uint64_t d, uint64_t s) const { sum(v.data(), d, s); }
-    // a value read as parity(rD & beta) ^ parity((rS ^ a) & gamma) changes v
-    void read(uint64_t beta, uint64_t gamma, const Vec &v) {
+    // a value read as parity(rD & beta) ^ parity(rS & gamma), and with
+    // `entry` parity(a & gamma), changes v
+    void read(uint64_t beta, uint64_t gamma, bool entry, const Vec &v) {
         for (; beta; beta &= beta - 1) add(D[__builtin_ctzll(beta)], v);
         for (; gamma; gamma &= gamma - 1) {
             add(S[__builtin_ctzll(gamma)], v);
-            add(A[__builtin_ctzll(gamma)], v);
+            if (entry) add(A[__builtin_ctzll(gamma)], v);
         }
     }
 };
@@ -67,6 +68,10 @@ void build_signs(const Program &P, SignProgram &out) {
     while (last < n && P.events[last].kind != EV_END && !stops(P.events[last])) ++last;
     if (last >= n) return;
     out.complete = P.events[last].kind == EV_END;
+    std::vector<bool> flipped(P.n_rec, false);  // records that noise may flip
+    for (const NoiseLoc &L : P.noise)
+        if (L.kind == NZ_FLIP) flipped[L.rec] = true;
+    auto is_t = [](const Event &E) { return E.kind == EV_T_PHASE || E.kind == EV_T_DOUBLE || E.kind == EV_T_BFLY; };
 
     // ---- pairs by closing event ----
     std::vector<int> closes(n, -1);
@@ -105,6 +110,14 @@ void build_signs(const Program &P, SignProgram &out) {
         mask.push_back(written);
         out.tests.push_back(SignTest{P.events[e].noise_end, src, kind, 0u});
     };
+    // A pair can be followed by signs when the bracket started and ends on one
+    // entry: its closing layer leaves an empty span.
+    auto follows = [&](const TPair &T) {
+        if (T.k0 != 0 || P.events[T.close].beta == 0 || out.pairs.size() >= kMaxSignPairs) return false;
+        uint32_t e = T.close;
+        while (e < last && (is_t(P.events[e]) || P.events[e].kind == EV_DROP)) ++e;
+        return P.before[e].basis.empty();
+    };
     for (uint32_t e = 0; e <= last; ++e) {
         const Event &E = P.events[e];
         if (E.noise_end < ne) return;  // (slots come in list order)
@@ -118,12 +131,25 @@ void build_signs(const Program &P, SignProgram &out) {
         const uint32_t sga = par64((rD & E.beta) ^ ((rS ^ a) & E.gamma));
         switch (E.kind) {
             case EV_T_PHASE: case EV_T_DOUBLE: case EV_T_BFLY:
-                sign_of[e] = (E.cexp + 2u * sga) & 3u;
-                if (closes[e] >= 0)
-                    add_test(e, closes[e], sign_of[e] != sign_of[P.pairs[closes[e]].open], SGT_HAND, 0u);
+                // (the gate's own sign: what `a` adds is the entry's)
+                sign_of[e] = (E.cexp + 2u * par64((rD & E.beta) ^ (rS & E.gamma))) & 3u;
+                if (closes[e] >= 0) {
+                    const TPair &T = P.pairs[closes[e]];
+                    const bool f = follows(T);
+                    add_test(e, closes[e], sign_of[e] != sign_of[T.open], f ? SGT_PAIR : SGT_HAND, 0u);
+                    if (f) {
+                        out.tests.back().pair = (uint32_t)out.pairs.size();
+                        out.pairs.push_back(SignPair{E.beta, (uint32_t)out.pairs.size(), (uint32_t)out.meas.size()});
+                    }
+                }
                 break;
             case EV_M_DET: case EV_M_SPLIT: {
                 uint32_t bit = (E.cexp == 2u ? 1u : 0u) ^ sga;
+                if (E.kind == EV_M_SPLIT || E.gamma) {
+                    const bool ok = E.kind == EV_M_DET && (E.flags & EVF_RECORD) && !flipped[E.rec];
+                    out.meas.push_back(SignMeas{E.kind == EV_M_DET ? E.gamma : ~0ull, E.noise_end,
+                                                (uint32_t)tests.size(), E.mslot, ok ? E.rec : kNoRec, {0u, 0u}});
+                }
                 if (E.kind == EV_M_SPLIT) {
                     bit = 0u;  // the coin's 0; its 1 is one more vector
                     const uint32_t p = E.pbit;
@@ -196,6 +222,7 @@ void build_signs(const Program &P, SignProgram &out) {
     };
     std::vector<Vec> open_at(n);  // opening T events: tests that read their sign
     out.coin.assign(out.coin_slot.size(), Vec());
+    out.pair_vecs.assign(out.pairs.size(), Vec());
     uint32_t t = nt, c = (uint32_t)out.coin_slot.size();
     for (uint32_t e = last + 1u; e-- > 0;) {
         const Event &E = P.events[e];
@@ -206,10 +233,15 @@ void build_signs(const Program &P, SignProgram &out) {
                 case EV_T_PHASE: case EV_T_DOUBLE: case EV_T_BFLY:
                     if (closes[e] >= 0) {
                         const Vec v = unit(--t);
-                        F.read(E.beta, E.gamma, v);
+                        if (out.tests[t].kind == SGT_PAIR) {
+                            Vec &u = out.pair_vecs[out.tests[t].pair];
+                            u.assign(W, 0u);
+                            for (uint64_t b = E.beta; b; b &= b - 1) add(u, F.A[__builtin_ctzll(b)]);
+                        }
+                        F.read(E.beta, E.gamma, false, v);
                         open_at[P.pairs[closes[e]].open] = v;
                     }
-                    if (!open_at[e].empty()) F.read(E.beta, E.gamma, open_at[e]);
+                    if (!open_at[e].empty()) F.read(E.beta, E.gamma, false, open_at[e]);
                     break;
                 case EV_M_DET: case EV_M_SPLIT: {
                     if (E.flags & EVF_CHECK) to_records(E, unit(--t));
@@ -217,7 +249,7 @@ void build_signs(const Program &P, SignProgram &out) {
                     if (E.flags & EVF_RECORD) add(v, RS[E.rec]);
                     if (E.flags & EVF_RESET) F.sum(v, E.xD, E.xS);
                     if (E.kind == EV_M_DET) {
-                        F.read(E.beta, E.gamma, v);
+                        F.read(E.beta, E.gamma, true, v);
                         break;
                     }
                     // d_p <- s_p (absorbed by the rows AD, AS), s_p <- the

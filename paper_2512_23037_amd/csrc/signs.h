@@ -25,6 +25,9 @@ struct SignProgram {
     std::vector<uint32_t> ref;                // noiseless values
     std::vector<uint32_t> coin_slot;          // measurement slots of the coins
     std::vector<std::vector<uint32_t>> coin;  // what a coin's 1 flips
+    std::vector<SignPair> pairs;              // `vec` indexes pair_vecs
+    std::vector<std::vector<uint32_t>> pair_vecs;
+    std::vector<SignMeas> meas;
     bool complete = false;                    // the signs decide the whole list
     double ends = 0.0;                        // about the fraction of shots that a check ends by signs
 };

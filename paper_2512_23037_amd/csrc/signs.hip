@@ -7,12 +7,13 @@
 // the sampler kernel, which runs after this one on the pending shots.
 //
 // With gap sampling a shot is a few Philox blocks, table reads and XORs: 10^7
-// shots of the 42-qubit circuit at p = 1e-3 take 0.45 ms (22 G shots/s), bound
+// shots of the 42-qubit circuit at p = 1e-3 take 0.85 ms (12 G shots/s), bound
 // by the latency of the table reads and by lanes that wait for the longest of
-// their neighbours' shots.  With a word per slot it is bound by the Philox
-// multiplies: 5 10^5 shots at p = 5e-4 (1.4 G words) take 1.2 ms.  In both the
-// sampler kernel is left with the 5% whose noise breaks a T pair: the launches
-// went from 48.3 to 12.1 ms and from 3.2 to 2.2 ms.
+// their neighbours' shots, and for the few that settle a broken pair (0.45 ms
+// without those).  With a word per slot it is bound by the Philox multiplies:
+// 5 10^5 shots at p = 5e-4 (1.4 G words) take 1.3 ms.  The launches take 2.9 and
+// 1.5 ms; 48.3 and 3.2 with the sampler kernel alone, 12.2 and 2.2 with the
+// broken pairs (5% of the shots) left to it.
 #include <hip/hip_runtime.h>
 
 #include "device.h"
@@ -42,12 +43,17 @@ __device__ __forceinline__ uint32_t part(uint32_t mul, uint32_t w, uint32_t d1) 
 // for single shots of 1329 steps) and a wave still holds four shots.
 template <bool GAPS> constexpr uint32_t kLanes = GAPS ? 1u : 16u;
 
+// Waves a SIMD holds by vector size, which the registers are set to.
+constexpr int kSignWaves(int tests) { return tests <= 4 ? 5 : tests <= 8 ? 4 : 3; }
+
+constexpr uint32_t kLeft = 0xFFFFFFFFu;
+
 // Idle lanes take new shots once this many wait: a start costs about as much
 // as a step of one-lane shots, whether one lane or all take it.
 constexpr uint32_t kRefill = 16;
 
 template <int TW, int RO, bool GAPS>
-__global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
+__global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu(kSignWaves(TW), 8))) k_signs(SignParams P) {
     constexpr int W = TW + RO, Q = W / 4;
     constexpr uint32_t GL = kLanes<GAPS>;
     static_assert(W % 4 == 0, "vectors are read four words at a time");
@@ -59,22 +65,23 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
 
     // the variant of the shots in flight, and their counts
     uint32_t var = 0, n_noise = 0, vec_off = 0, slot_off = 0, test_off = 0, ref_vec = 0, coin_off = 0, n_coins = 0;
-    uint32_t ck_cnt = 0, n_tests = 0, on = 0, tm1_off = 0, gap_off = 0;
+    uint32_t ck_cnt = 0, n_tests = 0, on = 0, tm1_off = 0, gap_off = 0, pair_off = 0, meas_off = 0, n_meas = 0;
     float l2q = 0.0f;
     uint64_t var_lo = 0, var_end = 0;
-    uint64_t n_pass = 0, n_disc = 0, n_logical = 0, n_prefix = 0;
+    uint64_t n_pass = 0, n_disc = 0, n_logical = 0, n_prefix = 0, n_broke = 0;
     uint64_t words = 0;  // of this lane
     auto flush = [&]() {
         unsigned long long *row = P.counters + (size_t)var * C_COUNT;
         for (int o = 32; o >= 1; o >>= 1) words += __shfl_xor((unsigned long long)words, o, 64);
         const uint64_t v = lane == C_SHOTS ? n_pass + n_disc : lane == C_PASSED ? n_pass : lane == C_DISCARDED ? n_disc
-                         : lane == C_LOGICAL ? n_logical : lane == C_NOISE ? words : lane == C_PREFIX ? n_prefix : 0ull;
+                         : lane == C_LOGICAL ? n_logical : lane == C_NOISE ? words : lane == C_PREFIX ? n_prefix
+                         : lane == C_RESTARTS ? n_broke : 0ull;
         if (v) atomicAdd(row + lane, (unsigned long long)v);
         if (lane <= kMaxCheckpoints) {
             if (hist[lane]) atomicAdd(row + C_CK0 + lane, (unsigned long long)hist[lane]);
             hist[lane] = 0u;
         }
-        n_pass = n_disc = n_logical = n_prefix = words = 0;
+        n_pass = n_disc = n_logical = n_prefix = n_broke = words = 0;
     };
 
     // Run positions [cur, end) of this wave's chunk are still to start.
@@ -91,6 +98,12 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
     uint32_t row = 0;    // first set test, or n_tests
     uint32_t limit = 0;  // noise slots that can still move it
     uint32_t ck = 0;     // checkpoints before the first hit
+    // Broken pairs not yet told apart: pair t's index in byte t of `pids`
+    // (npend bytes used), and in nibble j of `gens` the pairs whose betas add
+    // up to the j-th remaining index shift (0: none); the next measurement
+    // that reads one of them (SignMeas `mrow`), its first test and its stop.
+    uint32_t pids = 0, npend = 0, gens = 0, mrow = 0, mtest = 0, mstop = 0;
+    bool broke = false;  // a pair of this shot was broken
 #pragma unroll
     for (int w = 0; w < W; ++w) x[w] = 0u;
     auto add_vec = [&](uint32_t vec) {
@@ -110,7 +123,92 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
         for (int w = TW - 1; w >= 0; --w)
             if (x[w]) t = 32u * w + (uint32_t)__builtin_ctz(x[w]);
         row = t;
-        limit = P.tests[test_off + t].stop;
+        limit = gens != 0u && t >= mtest ? mstop : P.tests[test_off + t].stop;
+    };
+    // the index shift of a set of pending pairs
+    auto shift_of = [&](uint32_t set) {
+        uint64_t b = 0;
+        for (uint32_t t = 0; t < npend; ++t)
+            if ((set >> t) & 1u) b ^= P.pairs[pair_off + ((pids >> (8u * t)) & 255u)].beta;
+        return b;
+    };
+    // the first measurement from k on that reads a remaining shift
+    auto next_meas = [&](uint32_t k) {
+        uint64_t b[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) b[j] = shift_of((gens >> (4 * j)) & 15u);
+        mtest = 0xFFFFFFFFu;
+        mstop = 0u;
+        for (; k < n_meas; ++k) {
+            const SignMeas M = P.meas[meas_off + k];
+            const uint64_t g = M.gamma;
+            if (g == ~0ull || ((__popcll(g & b[0]) | __popcll(g & b[1]) | __popcll(g & b[2]) | __popcll(g & b[3])) & 1)) {
+                mtest = M.test;
+                mstop = M.stop;
+                break;
+            }
+        }
+        mrow = k;
+    };
+    // No slot below `limit` is undecided: what happens there.  False when the
+    // shot ends (row kLeft: the sampler kernel runs it).
+    auto settle = [&]() -> bool {
+        if (gens != 0u && row >= mtest) {
+            const SignMeas M = P.meas[meas_off + mrow];
+            if (M.rec == kNoRec) {
+                row = kLeft;
+                return false;
+            }
+            uint32_t c0, c1, c2, c3;
+            philox10(M.slot >> 2, s_lo, s_hi, 1u, key0, key1, c0, c1, c2, c3);
+            const uint32_t q = M.slot & 3u;
+            const uint32_t bit = (q == 0u ? c0 : q == 1u ? c1 : q == 2u ? c2 : c3) >> 31;
+            uint32_t o = 0;  // its outcome on the entry that x follows
+#pragma unroll
+            for (int w = 0; w < RO - 1; ++w)
+                if ((M.rec >> 5) == (uint32_t)w) o = (x[TW + w] >> (M.rec & 31u)) & 1u;
+            // one shift that it reads is decided, the others lose it
+            uint32_t pivot = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t set = (gens >> (4 * j)) & 15u;
+                if (!(__popcll(M.gamma & shift_of(set)) & 1)) continue;
+                gens ^= (pivot ? pivot : set) << (4 * j);
+                if (!pivot) pivot = set;
+            }
+            if (o != bit)
+                for (uint32_t t = 0; t < npend; ++t)
+                    if ((pivot >> t) & 1u) add_vec(P.pairs[pair_off + ((pids >> (8u * t)) & 255u)].vec);
+            if (gens == 0u) pids = npend = 0u;
+            else next_meas(mrow + 1u);
+            find_first();
+            return true;
+        }
+        const SignTest T = P.tests[test_off + row];
+        if (T.kind != SGT_PAIR) return false;
+        broke = true;
+        const SignPair S = P.pairs[pair_off + T.pair];
+        bool left = npend == 4u;
+        for (uint32_t set = 1; set < (1u << npend); ++set) {  // dependent on the remaining shifts?
+            uint32_t sum = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((set >> j) & 1u) sum ^= (gens >> (4 * j)) & 15u;
+            left = left || shift_of(sum) == S.beta;
+        }
+        if (left) {
+            row = kLeft;
+            return false;
+        }
+#pragma unroll
+        for (int w = 0; w < TW; ++w)
+            if ((row >> 5) == (uint32_t)w) x[w] &= x[w] - 1u;  // the lowest set test
+        pids |= T.pair << (8u * npend);
+        gens |= 1u << (5u * npend);  // nibble npend, pair npend
+        ++npend;
+        next_meas(S.meas);
+        find_first();
+        return true;
     };
     // the signature of a hit at slot s, its Pauli from the word w <= d1, into v
     auto hit = [&](uint32_t (&v)[W], uint32_t s, const SignSlot &sl, uint32_t w, uint32_t d1) {
@@ -170,6 +268,9 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
                     coin_off = first32(D.coin_off);
                     n_coins = first32(D.n_coins);
                     ck_cnt = first32(D.ck_cnt);
+                    pair_off = first32(D.pair_off);
+                    meas_off = first32(D.meas_off);
+                    n_meas = first32(D.n_meas);
                     tm1_off = first32(V.tm1_off);
                     gap_off = first32(V.gap_off);
                     l2q = V.gap_l2q;
@@ -191,6 +292,8 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
                             for (int w = 0; w < W; ++w) x[w] = 0u;
                             add_vec(ref_vec);
                             pos = drawn = 0u;
+                            pids = npend = gens = 0u;
+                            broke = false;
                             ck = ck_cnt;
                             uint32_t have = 0xFFFFFFFFu, c0 = 0, c1 = 0, c2 = 0, c3 = 0;
                             for (uint32_t c = 0; c < n_coins; ++c) {
@@ -222,7 +325,7 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
                 // word's logarithm puts four entries around it, which decide
                 // it unless they do not bracket it (then a binary search).
                 const uint32_t *tb = P.gaps + gap_off;
-#pragma unroll
+#pragma unroll 1
                 for (int half = 0; half < 2; ++half) {
                     if (!run) continue;
                     const uint32_t w = half ? w2 : w0, aw = half ? w3 : w1;
@@ -244,10 +347,8 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
                         G = lo;
                     }
                     const uint32_t s = drawn + min(G, lim);
-                    if (s >= limit) {
-                        run = false;
-                        continue;
-                    }
+                    while (run && s >= limit) run = settle();
+                    if (!run) continue;
                     drawn = s + 1u;
                     const SignSlot sl = P.slots[slot_off + s];
                     if (aw <= sl.acc1 && sl.kind != NZ_NONE) {
@@ -255,7 +356,6 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
                         ck = min(ck, sl.ckpt);
                         find_first();
                     }
-                    if (drawn >= limit) run = false;
                 }
             } else {
                 // Signatures only reach forward, so hits past `limit` may be
@@ -293,7 +393,7 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
         }
         if (!GAPS) {
             pos += 4u * GL;
-            run = act && pos < limit;
+            while (run && pos >= limit) run = settle();
         }
 
         // ---- shots that ended ----
@@ -302,10 +402,10 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
             bool pass = false, disc = false, logical = false;
             if (fin) {
                 act = false;
-                const SignTest T = P.tests[test_off + row];
+                const SignTest T = P.tests[test_off + (row == kLeft ? 0u : row)];
                 if (sub != 0u) {
                     // the group's first lane writes
-                } else if (T.kind == SGT_HAND) {
+                } else if (row == kLeft || T.kind == SGT_HAND) {
                     P.status[i] = kStatusPending;
                 } else {
                     const uint32_t *mk = P.mask + (size_t)(test_off + row) * RO;
@@ -328,6 +428,7 @@ __global__ void __launch_bounds__(kSignBlock) k_signs(SignParams P) {
             n_pass += (uint32_t)__builtin_popcountll(__ballot(pass));
             n_disc += (uint32_t)__builtin_popcountll(__ballot(disc));
             n_logical += (uint32_t)__builtin_popcountll(__ballot(logical));
+            n_broke += (uint32_t)__builtin_popcountll(__ballot((pass || disc) && broke));
             n_prefix += (uint32_t)__builtin_popcountll(__ballot((pass || disc) && ck != 0u && P.prefix != 0u));
         }
     }

@@ -331,6 +331,8 @@ int prepare_signs(soft_ctx *c) {
     std::vector<SignTest> test;
     std::vector<uint32_t> vec(W, 0u), mask;  // vector 0 is zero
     std::vector<uint2> coin;
+    std::vector<SignPair> pair;
+    std::vector<SignMeas> meas;
     std::memset(desc.data(), 0, nv * sizeof(SignDesc));
     // a program vector (tests, records, observables) in the launch's layout
     auto lay = [&](const uint32_t *x, const SignProgram &S, uint32_t *d) {
@@ -372,6 +374,14 @@ int prepare_signs(soft_ctx *c) {
         D.coin_off = (uint32_t)coin.size();
         D.n_coins = (uint32_t)S.coin.size();
         for (size_t i = 0; i < S.coin.size(); ++i) coin.push_back(make_uint2(S.coin_slot[i], put(S.coin[i])));
+        D.pair_off = (uint32_t)pair.size();
+        D.meas_off = (uint32_t)meas.size();
+        D.n_meas = (uint32_t)S.meas.size();
+        for (SignPair q : S.pairs) {
+            q.vec = put(S.pair_vecs[q.vec]);
+            pair.push_back(q);
+        }
+        meas.insert(meas.end(), S.meas.begin(), S.meas.end());
         const Program &P = c->vars[v].has_fast ? c->vars[v].fast : c->vars[v].prog;
         D.ck_cnt = (uint32_t)P.ckpts.size();
     }
@@ -383,9 +393,10 @@ int prepare_signs(soft_ctx *c) {
         if (bytes) std::memcpy(&all[at], src, bytes);
         return at;
     };
-    const size_t at[6] = {put(vec.data(), vec.size() * sizeof(uint32_t)), put(slot.data(), slot.size() * sizeof(SignSlot)),
+    const size_t at[8] = {put(vec.data(), vec.size() * sizeof(uint32_t)), put(slot.data(), slot.size() * sizeof(SignSlot)),
                           put(test.data(), test.size() * sizeof(SignTest)), put(mask.data(), mask.size() * sizeof(uint32_t)),
-                          put(coin.data(), coin.size() * sizeof(uint2)), put(desc.data(), nv * sizeof(SignDesc))};
+                          put(coin.data(), coin.size() * sizeof(uint2)), put(desc.data(), nv * sizeof(SignDesc)),
+                          put(pair.data(), pair.size() * sizeof(SignPair)), put(meas.data(), meas.size() * sizeof(SignMeas))};
     int rc = ensure(c, c->d_signs, all.size());
     if (rc) return rc;
     HIPCHK(c, hipMemcpy(c->d_signs.p, all.data(), all.size(), hipMemcpyHostToDevice));
@@ -396,6 +407,8 @@ int prepare_signs(soft_ctx *c) {
     T.mask = reinterpret_cast<const uint32_t *>(c->d_signs.p + at[3]);
     T.coins = reinterpret_cast<const uint2 *>(c->d_signs.p + at[4]);
     T.desc = reinterpret_cast<const SignDesc *>(c->d_signs.p + at[5]);
+    T.pairs = reinterpret_cast<const SignPair *>(c->d_signs.p + at[6]);
+    T.meas = reinterpret_cast<const SignMeas *>(c->d_signs.p + at[7]);
     return SOFT_OK;
 }
 
