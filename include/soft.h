@@ -203,7 +203,8 @@ int soft_set_prune(soft_ctx *ctx, double tau);
  * ends as OVERFLOW (0 = no cap).  waves_per_block (1..4), blocks_per_cu
  * (1..32), grab (1..64, consecutive shots a wave takes per steal; their
  * outputs are written together): launch shape, 0 = the autotuned or default
- * value.  One wave runs one shot at a time, so shots in flight per block =
+ * value (for grab its upper end: launches of few shots a wave take fewer at a
+ * time).  One wave runs one shot at a time, so shots in flight per block =
  * waves_per_block; the coefficient tile is not a free size (it holds the
  * circuit's whole span, 2^k_max entries) -- where it lives is
  * soft_set_tile_memory.  EINVAL for values out of range. */

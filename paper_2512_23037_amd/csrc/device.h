@@ -47,35 +47,29 @@ __device__ __forceinline__ uint32_t quot16(uint64_t x, uint64_t d) {
 
 // A launch's items [0, n) dealt out to its waves.  Wave w starts with item w,
 // without a cursor, so a launch of at most one item a wave has no atomics;
-// the rest come from eight cursors, wave w's being w mod 8 (consecutive blocks
-// go to the eight XCDs in turn).  Atomics on one address follow each other
-// every 16 ns: with one cursor for all, 25 000 items of four shots took 0.43 ms
-// where the work in them took 0.14.
-struct WorkQueue {
-    unsigned long long *cursor;
-    uint64_t n, item, first;  // first: items of this cursor that waves start with
-    uint32_t id;
-    bool left, more;
-    __device__ __forceinline__ WorkQueue(unsigned long long *cursors, uint32_t wave, uint32_t waves, uint64_t items)
-        : n(items), item(wave), id(wave % kQueueCursors), left(wave < items), more(items > waves) {
-        cursor = cursors + id * kCursorStride;
-        first = (waves - id + kQueueCursors - 1u) / kQueueCursors;
+// the rest come from eight cursors, wave w's being w mod 8 (of one-wave blocks,
+// consecutive ones go to the eight XCDs in turn).  Atomics on one address
+// follow each other every 16 ns: with one cursor for all, 25 000 items of four
+// shots took 0.43 ms where the work in them took 0.14, and the 5120 waves of a
+// small launch of the sampler spent 80 us finding that nothing was left.
+// The next item of the wave (all lanes active); false when there is none.
+// `started` is its state, false at first.
+__device__ __forceinline__ bool take_item(unsigned long long *cursors, uint64_t n, uint32_t wave, uint32_t waves,
+                                          uint32_t lane, bool &started, uint64_t &item) {
+    if (!started) {
+        started = true;
+        item = wave;
+        return item < n;
     }
-    // The next item, for the whole wave (all lanes active); false when there is none.
-    __device__ __forceinline__ bool take(uint32_t lane, uint64_t &got) {
-        if (!left) return false;
-        got = item;
-        left = false;
-        if (more) {
-            unsigned long long c = 0;
-            if (lane == 0) c = atomicAdd(cursor, 1ull);
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)c);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(c >> 32));
-            item = (first + (((uint64_t)hi << 32) | lo)) * kQueueCursors + id;
-            left = item < n;
-        }
-        return true;
-    }
-};
+    if (n <= waves) return false;
+    const uint32_t id = wave % kQueueCursors;
+    unsigned long long c = 0;
+    if (lane == 0) c = atomicAdd(cursors + id * kCursorStride, 1ull);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)c);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(c >> 32));
+    const uint32_t first = (waves - id + kQueueCursors - 1u) / kQueueCursors;  // items of this cursor that waves start with
+    item = (first + (((uint64_t)hi << 32) | lo)) * kQueueCursors + id;
+    return item < n;
+}
 
 }  // namespace soft

@@ -28,7 +28,7 @@ struct RunParams {
     uint32_t *abort_op;       // [n_shots] or null
     uint32_t *obs;            // [n_shots] or null
     unsigned long long *counters;  // [variants][C_COUNT]
-    unsigned long long *next;      // work-stealing cursor
+    unsigned long long *next;      // work-stealing cursors
     unsigned long long *keep_meta; // [keep_n][KM_COUNT] or null
     double *keep_v;                // [keep_n][tile_entries][2] or null
     unsigned long long *trace_meta;  // [trace_n][KM_COUNT] or null
@@ -87,12 +87,12 @@ constexpr uint32_t kSignWavesPerCu[4] = {20, 20, 16, 12};  // by their registers
 const void *signs_kernel(uint32_t size, bool gaps);
 hipError_t launch_signs(const SignParams &p, uint32_t size, bool gaps, dim3 grid, hipStream_t stream);
 
-// Work cursors, after the counter rows: eight of a queue (WorkQueue), each in
-// a cache line of its own, for the sign pass; then the sampler's and the
-// prefix build's.
-constexpr uint32_t kQueueCursors = 8, kCursorStride = 16;
-constexpr uint32_t kSignCursor = 0, kSampleCursor = kQueueCursors * kCursorStride, kBuildCursor = kSampleCursor + 1;
-constexpr uint32_t kCursorWords = kBuildCursor + 1;
+// Work cursors, after the counter rows: the eight of a queue (take_item), each
+// in a cache line of its own, for the sampler, the sign pass and the prefix
+// build.
+constexpr uint32_t kQueueCursors = 8, kCursorStride = 16, kQueueWords = kQueueCursors * kCursorStride;
+constexpr uint32_t kSampleCursor = 0, kSignCursor = kQueueWords, kBuildCursor = 2 * kQueueWords;
+constexpr uint32_t kCursorWords = 3 * kQueueWords;
 
 // Zero `n` counters and the work cursors: a kernel, so it can live in a graph.
 hipError_t launch_reset(unsigned long long *counters, uint32_t n, unsigned long long *next, hipStream_t stream);

@@ -600,11 +600,14 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         maxdev = 0.0;
     };
 
-    // Work stealing by groups of `grab` (<= 64) consecutive shots.  A wave
-    // writes its shots' output words one shot after the other, so L2 gathers
-    // each output plane's words of a group into whole lines.
+    // Work stealing by groups of `grab` consecutive shots, at most 64 of them
+    // at a time.  A wave writes its shots' output words one shot after the
+    // other, so L2 gathers each output plane's words of a group into whole
+    // lines.
     uint64_t group_base = 0;
-    uint64_t todo = 0;  // bit t: position group_base + t is still to run
+    uint32_t group_rest = 0;  // of the group, past the ones in `todo`
+    bool started = false;
+    uint64_t todo = 0;        // bit t: position group_base + t is still to run
     // Output plane of this lane: record word `lane` (lanes below kRecSgpr),
     // then status, abort op and observables; null when the caller did not ask.
     uint32_t *out_plane = nullptr;
@@ -619,11 +622,18 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
     }
     while (true) {
         if (todo == 0ull) {
-            unsigned long long got = 0;
-            if (lane == 0) got = atomicAdd(P.next, (unsigned long long)P.grab);
-            group_base = uni64(__shfl((unsigned long long)got, 0, 64));
-            if (group_base >= P.n_shots) break;
-            const uint32_t len = (uint32_t)min((uint64_t)P.grab, P.n_shots - group_base);
+            if (group_rest == 0u) {
+                uint64_t item;
+                if (!take_item(P.next, (P.n_shots + P.grab - 1u) / P.grab, uni((uint32_t)gwave),
+                               gridDim.x * (blockDim.x >> 6), lane, started, item))
+                    break;
+                group_base = item * P.grab;
+                group_rest = (uint32_t)min((uint64_t)P.grab, P.n_shots - group_base);
+            } else {
+                group_base += 64u;
+            }
+            const uint32_t len = min(group_rest, 64u);
+            group_rest -= len;
             // after the sign pass: the shots it left
             todo = __ballot(lane < len && !(LEAN && P.signs && P.status[group_base + lane] != kStatusPending));
             continue;
@@ -1875,7 +1885,7 @@ k_prefix_f64(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz, cons
 
 __global__ void k_reset(unsigned long long *counters, uint32_t n, unsigned long long *next) {
     for (uint32_t t = threadIdx.x; t < n; t += blockDim.x) counters[t] = 0ull;
-    if (threadIdx.x < kCursorWords) next[threadIdx.x] = 0ull;
+    for (uint32_t t = threadIdx.x; t < kCursorWords; t += blockDim.x) next[t] = 0ull;
 }
 
 template <typename R, uint32_t NS, uint32_t TM, bool LEAN> const void *kernel_ptr() {

@@ -85,8 +85,8 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
     };
 
     // Run positions [cur, end) of this wave's chunk are still to start.
-    WorkQueue queue(P.next, blockIdx.x, gridDim.x, (P.n_shots + P.chunk - 1u) / P.chunk);
     uint64_t cur = 0, end = 0;
+    bool started = false;
 
     // ---- the lane's shot ----
     bool act = false;
@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
         const uint32_t n_idle = (uint32_t)__builtin_popcountll(idle);
         if (n_idle >= kRefill) {
             uint64_t got;
-            if (cur == end && queue.take(lane, got)) {
+            if (cur == end && take_item(P.next, (P.n_shots + P.chunk - 1u) / P.chunk, blockIdx.x, gridDim.x, lane, started, got)) {
                 cur = got * P.chunk;
                 end = min(cur + P.chunk, P.n_shots);
             }

@@ -243,7 +243,7 @@ RunParams build_params(const RunParams &rp) {
     b.trace_v = nullptr;
     b.trace_n = 0;
     b.grab = 1;
-    b.next = rp.next + (kBuildCursor - kSampleCursor);
+    b.next = rp.next + kBuildCursor;
     return b;
 }
 
@@ -648,7 +648,7 @@ uint32_t sign_params(const soft_ctx *c, const RunParams &rp, SignParams &sp) {
     sp.abort_op = rp.abort_op;
     sp.obs = rp.obs;
     sp.counters = rp.counters;
-    sp.next = rp.next - kSampleCursor + kSignCursor;
+    sp.next = rp.next + kSignCursor;
     sp.seed = rp.seed;
     sp.shot0 = rp.shot0;
     sp.n_shots = rp.n_shots;
@@ -664,12 +664,17 @@ uint32_t sign_params(const soft_ctx *c, const RunParams &rp, SignParams &sp) {
     return (uint32_t)std::min<uint64_t>(most, (rp.n_shots + sp.chunk - 1u) / sp.chunk);
 }
 
-// Positions a wave of the sampler takes at a time after the sign pass, which
-// leaves few of them to run: as many as one wave reads, fewer when the launch
-// is small (not below the default: each steal is an atomic on one address).
-uint32_t sign_grab(const soft_ctx *c, const Shape &s, uint64_t grid, uint64_t n_shots) {
+// Positions a wave of the sampler takes at a time.  A launch of a few shots a
+// wave deals them out evenly (16 at a time, 256 shots ran on 16 waves); a
+// larger one leaves at least four groups a wave to even out their lengths, up
+// to the shape's.  After the sign pass few positions are left to run: whole
+// reads of 64 statuses, about four groups a wave, since each group is an
+// atomic (10^7 shots in groups of 64 took 1.9 ms to find none left).
+uint32_t group_size(const soft_ctx *c, const Shape &s, uint64_t grid, uint64_t n_shots, bool signs) {
     if (c->user.grab) return c->user.grab;
-    return (uint32_t)std::min<uint64_t>(64u, std::max<uint64_t>(s.grab, n_shots / (grid * s.wpb)));
+    const uint64_t waves = grid * s.wpb, each = (n_shots + waves - 1u) / waves;
+    if (signs) return (uint32_t)(each <= 64u ? each : std::min<uint64_t>(1024u, (each / 4u + 63u) / 64u * 64u));
+    return (uint32_t)(each < 4u ? each : std::min<uint64_t>(s.grab, each / 4u));
 }
 
 int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStream_t stream) {
@@ -695,13 +700,13 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     }
     const uint64_t bgrid = std::min<uint64_t>(grid, (2ull * rp.n_vars + s.wpb - 1) / s.wpb);
     const bool sgn = use_signs(c, rp);
+    rp.grab = group_size(c, s, grid, n_shots, sgn);
     SignParams sp;
     uint32_t sgrid = 0;
     const void *sfn = nullptr;
     std::memset(&sp, 0, sizeof(sp));
     if (sgn) {
         rp.signs = 1;
-        rp.grab = sign_grab(c, s, grid, n_shots);
         sgrid = sign_params(c, rp, sp);
         sfn = signs_kernel(c->sign_size, rp.noise_mode == 1u);
     }
@@ -766,7 +771,7 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
         drop_slot(c, gs);
         gs.r_counters = rp.counters;
         gs.r_n = rp.n_vars * (uint32_t)C_COUNT;
-        gs.r_next = rp.next - kSampleCursor;
+        gs.r_next = rp.next;
         void *rargs[3] = {(void *)&gs.r_counters, (void *)&gs.r_n, (void *)&gs.r_next};
         hipKernelNodeParams rk;
         std::memset(&rk, 0, sizeof(rk));
@@ -827,7 +832,7 @@ int make_params(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcome
     rp.abort_op = abort_op;
     rp.obs = obs;
     rp.counters = c->d_counters;
-    rp.next = c->d_counters + kCursorOff + kSampleCursor;
+    rp.next = c->d_counters + kCursorOff;
     rp.seed = c->seed;
     rp.shot0 = shot0;
     rp.n_shots = n_shots;
@@ -1290,7 +1295,7 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
     // the scratch holds (the kernel is persistent, so fewer waves take more
     // shots each)
     rp.counters = reinterpret_cast<unsigned long long *>(c->scratch);
-    rp.next = rp.counters + kCursorOff + kSampleCursor;
+    rp.next = rp.counters + kCursorOff;
     // shared-prefix slots when they fit their part of the scratch (without
     // them every shot runs from the start: the same results)
     const bool pfx = use_prefix(c) && (uint64_t)c->n_ckpt * prefix_stride(c) <= kScratchPrefixBytes;
@@ -1309,14 +1314,15 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
         rp.gtile = c->scratch + kScratchCounterBytes + kScratchPrefixBytes;
     }
     const hipStream_t stream = (hipStream_t)hip_stream;
-    HIPCHK(c, launch_reset(rp.counters, rp.n_vars * (uint32_t)C_COUNT, rp.next - kSampleCursor, stream));
+    HIPCHK(c, launch_reset(rp.counters, rp.n_vars * (uint32_t)C_COUNT, rp.next, stream));
     if (pfx)
         HIPCHK(c, launch_prefix_build(build_params(rp), c->bits == 64,
                                  dim3((uint32_t)std::min<uint64_t>(grid, (2ull * rp.n_vars + s.wpb - 1) / s.wpb)),
                                  dim3(64u * s.wpb), (size_t)s.wpb * wave_bytes(c, s), stream));
-    if (use_signs(c, rp)) {
+    const bool sgn = use_signs(c, rp);
+    rp.grab = group_size(c, s, grid, n_shots, sgn);
+    if (sgn) {
         rp.signs = 1;
-        rp.grab = sign_grab(c, s, grid, n_shots);
         SignParams sp;
         const uint32_t sgrid = sign_params(c, rp, sp);
         HIPCHK(c, launch_signs(sp, c->sign_size, rp.noise_mode == 1u, dim3(sgrid), stream));
