@@ -319,7 +319,8 @@ struct alignas(16) SignTest {
     uint32_t pair;
 };
 // A T pair on a single basis entry: its index shift, what `a ^= beta` at its
-// end flips, and the first of the measurements (SignMeas) after it.
+// end flips, and the first of the measurements (SignMeas) after it that reads
+// its shift.
 struct alignas(16) SignPair {
     uint64_t beta;
     uint32_t vec;

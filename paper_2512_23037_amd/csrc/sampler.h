@@ -83,7 +83,7 @@ struct SignParams {
 constexpr uint32_t kSignTestWords[4] = {2, 4, 8, 16};
 constexpr uint32_t kSignOutWords[4] = {2, 4, 8, 16};
 constexpr uint32_t kSignBlock = 64;  // one wave: its shots are its own, and small launches spread over the CUs
-constexpr uint32_t kSignWavesPerCu[4] = {20, 20, 16, 12};  // by their registers
+constexpr uint32_t kSignWavesPerCu[4] = {24, 24, 20, 12};  // by their registers
 const void *signs_kernel(uint32_t size, bool gaps);
 hipError_t launch_signs(const SignParams &p, uint32_t size, bool gaps, dim3 grid, hipStream_t stream);
 

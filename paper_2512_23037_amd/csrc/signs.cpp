@@ -186,6 +186,9 @@ void build_signs(const Program &P, SignProgram &out) {
             default: break;  // T, DROP and diagonal gates leave the signs alone
         }
     }
+    for (SignPair &S : out.pairs)  // so far: the first measurement after the pair
+        while (S.meas < out.meas.size() && out.meas[S.meas].gamma != ~0ull && !par64(out.meas[S.meas].gamma & S.beta))
+            ++S.meas;
     const uint32_t nt = (uint32_t)tests.size(), tw = (nt + 31u) / 32u;
     if (tw > kMaxTestWords || rw + 1u > kMaxOutWords || out.coin_slot.size() > kMaxCoins) return;
     out.tests.push_back(SignTest{P.n_noise, 0xFFFFFFFFu, SGT_NONE, 0u});

@@ -23,11 +23,6 @@
 namespace soft {
 namespace {
 
-__device__ __forceinline__ uint64_t first64(uint64_t x) {
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
-    return ((uint64_t)hi << 32) | (uint64_t)lo;
-}
 __device__ __forceinline__ uint32_t first32(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 
 // floor(mul w / (d1 + 1)) for mul = 3 or 15 and w <= d1
@@ -50,28 +45,44 @@ constexpr uint32_t kLeft = 0xFFFFFFFFu;
 
 // Idle lanes take new shots once this many wait: a start costs about as much
 // as a step of one-lane shots, whether one lane or all take it.
-constexpr uint32_t kRefill = 16;
+constexpr uint32_t kRefill = 32;
+
+// The launch's arguments, read again where they are used: everything outside
+// the step is rare, and kept in scalar registers across it its pointers
+// spilled (60 of them; the reloads hit the scalar cache).
+typedef const __attribute__((address_space(4))) SignParams ConstParams;
+typedef const __attribute__((address_space(4))) SignDesc ConstDesc;
+typedef const __attribute__((address_space(4))) VariantDesc ConstVariant;
+__device__ __forceinline__ ConstParams *args() {
+    ConstParams *p = (ConstParams *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
 
 template <int TW, int RO, bool GAPS>
-__global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu(kSignWaves(TW), 8))) k_signs(SignParams P) {
+__global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu(kSignWaves(TW), 8))) k_signs(SignParams P0) {
     constexpr int W = TW + RO, Q = W / 4;
     constexpr uint32_t GL = kLanes<GAPS>;
     static_assert(W % 4 == 0, "vectors are read four words at a time");
     __shared__ uint32_t hist[kMaxCheckpoints + 1];
+    __shared__ uint32_t stops[32 * TW + 1];  // SignTest::stop of the variant's rows
     const uint32_t lane = threadIdx.x, sub = lane % GL;
-    const uint32_t key0 = (uint32_t)P.seed, key1 = (uint32_t)(P.seed >> 32);
-    const uint64_t below = (1ull << (lane - sub)) - 1ull;
+    const uint32_t key0 = (uint32_t)P0.seed, key1 = (uint32_t)(P0.seed >> 32);
     if (lane <= kMaxCheckpoints) hist[lane] = 0u;
 
-    // the variant of the shots in flight, and their counts
-    uint32_t var = 0, n_noise = 0, vec_off = 0, slot_off = 0, test_off = 0, ref_vec = 0, coin_off = 0, n_coins = 0;
-    uint32_t ck_cnt = 0, n_tests = 0, on = 0, tm1_off = 0, gap_off = 0, pair_off = 0, meas_off = 0, n_meas = 0;
+    // The variant of the shots in flight: what the step reads of it, and the
+    // shots' counts.
+    uint32_t var = 0xFFFFFFFFu, n_noise = 0, n_tests = 0;
     float l2q = 0.0f;
-    uint64_t var_lo = 0, var_end = 0;
-    uint64_t n_pass = 0, n_disc = 0, n_logical = 0, n_prefix = 0, n_broke = 0;
+    const uint32_t *draws = nullptr;   // its gap table, or its thresholds
+    const SignSlot *slots = nullptr;
+    const uint4 *vecs = nullptr;       // its first slot's signatures
+    uint32_t zero_vec = 0;             // the zero vector, from there
+    uint32_t n_pass = 0, n_disc = 0, n_logical = 0, n_prefix = 0, n_broke = 0;
     uint64_t words = 0;  // of this lane
+    auto desc = [&]() { return (ConstDesc *)args()->desc + var; };
     auto flush = [&]() {
-        unsigned long long *row = P.counters + (size_t)var * C_COUNT;
+        unsigned long long *row = args()->counters + (size_t)var * C_COUNT;
         for (int o = 32; o >= 1; o >>= 1) words += __shfl_xor((unsigned long long)words, o, 64);
         const uint64_t v = lane == C_SHOTS ? n_pass + n_disc : lane == C_PASSED ? n_pass : lane == C_DISCARDED ? n_disc
                          : lane == C_LOGICAL ? n_logical : lane == C_NOISE ? words : lane == C_PREFIX ? n_prefix
@@ -81,20 +92,25 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
             if (hist[lane]) atomicAdd(row + C_CK0 + lane, (unsigned long long)hist[lane]);
             hist[lane] = 0u;
         }
-        n_pass = n_disc = n_logical = n_prefix = n_broke = words = 0;
+        n_pass = n_disc = n_logical = n_prefix = n_broke = 0;
+        words = 0;
     };
 
-    // Run positions [cur, end) of this wave's chunk are still to start.
-    uint64_t cur = 0, end = 0;
-    bool started = false;
+    // Run positions [cur, cur + rest) of this wave's chunk are still to start.
+    uint64_t cur = 0;
+    uint32_t rest = 0;
+    bool started = false, dry = false;
 
     // ---- the lane's shot ----
-    bool act = false;
+    bool act = false;    // it has one
+    bool stop = false;   // no slot below `limit` is undecided: to be settled
     uint64_t i = 0;
     uint32_t s_lo = 0, s_hi = 0;
     uint32_t x[W];
-    uint32_t pos = 0;    // next word (GAPS) or noise slot (multiples of 4)
+    uint32_t pos = 0;    // next word (GAPS) or noise slot (of the lane's group)
     uint32_t drawn = 0;  // GAPS: slots decided
+    uint32_t next_s = 0, next_w = 0;  // GAPS: the candidate that stopped at `limit`, and its acceptance word
+    bool held = false;                // GAPS: that candidate is still to be taken
     uint32_t row = 0;    // first set test, or n_tests
     uint32_t limit = 0;  // noise slots that can still move it
     uint32_t ck = 0;     // checkpoints before the first hit
@@ -106,15 +122,14 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
     bool broke = false;  // a pair of this shot was broken
 #pragma unroll
     for (int w = 0; w < W; ++w) x[w] = 0u;
-    auto add_vec = [&](uint32_t vec) {
-        const uint4 *p = P.vecs + (size_t)vec * Q;
+    auto add_to = [&](uint32_t (&v)[W], const uint4 *p) {
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const uint4 u = p[q];
-            x[4 * q] ^= u.x;
-            x[4 * q + 1] ^= u.y;
-            x[4 * q + 2] ^= u.z;
-            x[4 * q + 3] ^= u.w;
+            v[4 * q] ^= u.x;
+            v[4 * q + 1] ^= u.y;
+            v[4 * q + 2] ^= u.z;
+            v[4 * q + 3] ^= u.w;
         }
     };
     auto find_first = [&]() {
@@ -123,44 +138,65 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
         for (int w = TW - 1; w >= 0; --w)
             if (x[w]) t = 32u * w + (uint32_t)__builtin_ctz(x[w]);
         row = t;
-        limit = gens != 0u && t >= mtest ? mstop : P.tests[test_off + t].stop;
+        limit = stops[t];
+        if (gens != 0u && t >= mtest) limit = mstop;
     };
+    // the signature of a hit at slot s, its Pauli from the word w <= d1, into v
+    auto hit = [&](uint32_t (&v)[W], uint32_t s, uint32_t kind, uint32_t w, uint32_t d1) {
+        uint32_t a = 1u, b = 0u;
+        if (kind == NZ_DEP1) {
+            a = part(3u, w, d1) + 1u;
+        } else if (kind == NZ_DEP2) {
+            const uint32_t code = part(15u, w, d1) + 1u;
+            a = code >> 2;
+            b = code & 3u;
+        } else if (kind == NZ_ZERR) {
+            a = 3u;
+        }
+        const uint32_t v0 = kSignVecs * s - 1u;
+        const int32_t va = (int32_t)(a ? v0 + a : zero_vec), vb = (int32_t)(b ? v0 + 3u + b : zero_vec);
+        const uint4 *pa = vecs + (int64_t)va * Q, *pb = vecs + (int64_t)vb * Q;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint4 ua = pa[q], ub = pb[q];
+            v[4 * q] ^= ua.x ^ ub.x;
+            v[4 * q + 1] ^= ua.y ^ ub.y;
+            v[4 * q + 2] ^= ua.z ^ ub.z;
+            v[4 * q + 3] ^= ua.w ^ ub.w;
+        }
+    };
+
     // the index shift of a set of pending pairs
-    auto shift_of = [&](uint32_t set) {
+    auto shift_of = [&](const SignPair *pairs, uint32_t set) {
         uint64_t b = 0;
         for (uint32_t t = 0; t < npend; ++t)
-            if ((set >> t) & 1u) b ^= P.pairs[pair_off + ((pids >> (8u * t)) & 255u)].beta;
+            if ((set >> t) & 1u) b ^= pairs[(pids >> (8u * t)) & 255u].beta;
         return b;
     };
-    // the first measurement from k on that reads a remaining shift
-    auto next_meas = [&](uint32_t k) {
-        uint64_t b[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = shift_of((gens >> (4 * j)) & 15u);
-        mtest = 0xFFFFFFFFu;
-        mstop = 0u;
-        for (; k < n_meas; ++k) {
-            const SignMeas M = P.meas[meas_off + k];
-            const uint64_t g = M.gamma;
-            if (g == ~0ull || ((__popcll(g & b[0]) | __popcll(g & b[1]) | __popcll(g & b[2]) | __popcll(g & b[3])) & 1)) {
-                mtest = M.test;
-                mstop = M.stop;
-                break;
-            }
-        }
+    // the next measurement that reads a remaining shift is k
+    auto set_meas = [&](ConstParams *A, ConstDesc *D, uint32_t k) {
         mrow = k;
+        mtest = 0xFFFFFFFFu;
+        if (k < D->n_meas) {
+            const SignMeas M = A->meas[D->meas_off + k];
+            mtest = M.test;
+            mstop = M.stop;
+        }
     };
-    // No slot below `limit` is undecided: what happens there.  False when the
-    // shot ends (row kLeft: the sampler kernel runs it).
+    // What happens where no slot below `limit` is undecided.  False when the
+    // shot ends there (row kLeft: the sampler kernel runs it).
     auto settle = [&]() -> bool {
+        ConstParams *A = args();
+        ConstDesc *D = desc();
+        const SignPair *pairs = A->pairs + D->pair_off;
         if (gens != 0u && row >= mtest) {
-            const SignMeas M = P.meas[meas_off + mrow];
+            const SignMeas M = A->meas[D->meas_off + mrow];
             if (M.rec == kNoRec) {
                 row = kLeft;
                 return false;
             }
             uint32_t c0, c1, c2, c3;
-            philox10(M.slot >> 2, s_lo, s_hi, 1u, key0, key1, c0, c1, c2, c3);
+            philox10<true>(M.slot >> 2, s_lo, s_hi, 1u, key0, key1, c0, c1, c2, c3);
             const uint32_t q = M.slot & 3u;
             const uint32_t bit = (q == 0u ? c0 : q == 1u ? c1 : q == 2u ? c2 : c3) >> 31;
             uint32_t o = 0;  // its outcome on the entry that x follows
@@ -172,29 +208,42 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t set = (gens >> (4 * j)) & 15u;
-                if (!(__popcll(M.gamma & shift_of(set)) & 1)) continue;
+                if (!(__popcll(M.gamma & shift_of(pairs, set)) & 1)) continue;
                 gens ^= (pivot ? pivot : set) << (4 * j);
                 if (!pivot) pivot = set;
             }
             if (o != bit)
                 for (uint32_t t = 0; t < npend; ++t)
-                    if ((pivot >> t) & 1u) add_vec(P.pairs[pair_off + ((pids >> (8u * t)) & 255u)].vec);
-            if (gens == 0u) pids = npend = 0u;
-            else next_meas(mrow + 1u);
+                    if ((pivot >> t) & 1u) add_to(x, A->vecs + (size_t)pairs[(pids >> (8u * t)) & 255u].vec * Q);
+            if (gens == 0u) {
+                pids = npend = 0u;
+            } else {  // (a remaining shift may now be a sum of pairs')
+                uint64_t b[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) b[j] = shift_of(pairs, (gens >> (4 * j)) & 15u);
+                const SignMeas *meas = A->meas + D->meas_off;
+                const uint32_t n = D->n_meas;
+                uint32_t k = mrow + 1u;
+                for (; k < n; ++k) {
+                    const uint64_t g = meas[k].gamma;
+                    if (g == ~0ull || ((__popcll(g & b[0]) | __popcll(g & b[1]) | __popcll(g & b[2]) | __popcll(g & b[3])) & 1)) break;
+                }
+                set_meas(A, D, k);
+            }
             find_first();
             return true;
         }
-        const SignTest T = P.tests[test_off + row];
+        const SignTest T = A->tests[D->test_off + row];
         if (T.kind != SGT_PAIR) return false;
         broke = true;
-        const SignPair S = P.pairs[pair_off + T.pair];
+        const SignPair S = pairs[T.pair];
         bool left = npend == 4u;
         for (uint32_t set = 1; set < (1u << npend); ++set) {  // dependent on the remaining shifts?
             uint32_t sum = 0;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if ((set >> j) & 1u) sum ^= (gens >> (4 * j)) & 15u;
-            left = left || shift_of(sum) == S.beta;
+            left = left || shift_of(pairs, sum) == S.beta;
         }
         if (left) {
             row = kLeft;
@@ -203,223 +252,53 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
         for (int w = 0; w < TW; ++w)
             if ((row >> 5) == (uint32_t)w) x[w] &= x[w] - 1u;  // the lowest set test
+        // (what was pending is not read before this pair's end: it would have
+        // been settled first)
+        set_meas(A, D, gens ? min(mrow, S.meas) : S.meas);
         pids |= T.pair << (8u * npend);
         gens |= 1u << (5u * npend);  // nibble npend, pair npend
         ++npend;
-        next_meas(S.meas);
         find_first();
         return true;
     };
-    // the signature of a hit at slot s, its Pauli from the word w <= d1, into v
-    auto hit = [&](uint32_t (&v)[W], uint32_t s, const SignSlot &sl, uint32_t w, uint32_t d1) {
-        uint32_t a = 1u, b = 0u;
-        if (sl.kind == NZ_DEP1) {
-            a = part(3u, w, d1) + 1u;
-        } else if (sl.kind == NZ_DEP2) {
-            const uint32_t code = part(15u, w, d1) + 1u;
-            a = code >> 2;
-            b = code & 3u;
-        } else if (sl.kind == NZ_ZERR) {
-            a = 3u;
-        }
-        const uint32_t v0 = vec_off + kSignVecs * s - 1u;
-        const uint32_t va = a ? v0 + a : 0u, vb = b ? v0 + 3u + b : 0u;
-        const uint4 *pa = P.vecs + (size_t)va * Q, *pb = P.vecs + (size_t)vb * Q;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const uint4 ua = pa[q], ub = pb[q];
-            v[4 * q] ^= ua.x ^ ub.x;
-            v[4 * q + 1] ^= ua.y ^ ub.y;
-            v[4 * q + 2] ^= ua.z ^ ub.z;
-            v[4 * q + 3] ^= ua.w ^ ub.w;
-        }
-    };
 
     for (;;) {
-        // ---- idle lanes take shots ----
-        const uint64_t idle = __ballot(!act);
-        const uint32_t n_idle = (uint32_t)__builtin_popcountll(idle);
-        if (n_idle >= kRefill) {
-            uint64_t got;
-            if (cur == end && take_item(P.next, (P.n_shots + P.chunk - 1u) / P.chunk, blockIdx.x, gridDim.x, lane, started, got)) {
-                cur = got * P.chunk;
-                end = min(cur + P.chunk, P.n_shots);
+        // ---- stopped shots are settled and end, idle lanes take new ones ----
+        const uint64_t busy = __ballot(act && !stop), stopped = __ballot(stop);
+        const uint32_t waiting = 64u - (uint32_t)__builtin_popcountll(dry ? busy | ~stopped : busy);
+        if (waiting >= kRefill || busy == 0ull) {
+            bool fin = false;
+            if (stop) {
+                bool on = settle();
+                while (on && (GAPS ? next_s : pos) >= limit) on = settle();
+                fin = !on;
+                stop = false;
+                held = on;
             }
-            if (cur == end && n_idle == 64u) break;
-            if (cur != end) {
-                uint64_t shot = P.shot0 + cur;
-                bool ready = shot >= var_lo && shot < var_end;
-                if (!ready && n_idle == 64u) {  // another variant, once no lane runs the last one
-                    if (var_end) flush();
-                    var = 0;
-                    while (var + 1u < P.n_vars && P.vars[var].shot_end <= shot) ++var;
-                    var = first32(var);
-                    const SignDesc &D = P.desc[var];
-                    const VariantDesc &V = P.vars[var];
-                    var_lo = first64(var ? P.vars[var - 1u].shot_end : 0ull);
-                    var_end = first64(V.shot_end);
-                    n_noise = first32(V.n_noise);
-                    on = first32(D.on) & (GAPS ? 1u : 2u);
-                    n_tests = first32(D.n_tests);
-                    vec_off = first32(D.vec_off);
-                    slot_off = first32(D.slot_off);
-                    test_off = first32(D.test_off);
-                    ref_vec = first32(D.ref_vec);
-                    coin_off = first32(D.coin_off);
-                    n_coins = first32(D.n_coins);
-                    ck_cnt = first32(D.ck_cnt);
-                    pair_off = first32(D.pair_off);
-                    meas_off = first32(D.meas_off);
-                    n_meas = first32(D.n_meas);
-                    tm1_off = first32(V.tm1_off);
-                    gap_off = first32(V.gap_off);
-                    l2q = V.gap_l2q;
-                    ready = true;
-                }
-                if (ready) {
-                    const uint64_t left = min(end, var_end - P.shot0) - cur;
-                    const uint32_t take = (uint32_t)min(left, (uint64_t)(n_idle / GL));
-                    const uint32_t rank = (uint32_t)__builtin_popcountll(idle & below) / GL;
-                    if (!act && rank < take) {
-                        i = cur + rank;
-                        if (!on) {
-                            if (sub == 0u) P.status[i] = kStatusPending;
-                        } else {
-                            act = true;
-                            s_lo = (uint32_t)(P.shot0 + i);
-                            s_hi = (uint32_t)((P.shot0 + i) >> 32);
-#pragma unroll
-                            for (int w = 0; w < W; ++w) x[w] = 0u;
-                            add_vec(ref_vec);
-                            pos = drawn = 0u;
-                            pids = npend = gens = 0u;
-                            broke = false;
-                            ck = ck_cnt;
-                            uint32_t have = 0xFFFFFFFFu, c0 = 0, c1 = 0, c2 = 0, c3 = 0;
-                            for (uint32_t c = 0; c < n_coins; ++c) {
-                                const uint2 cn = P.coins[coin_off + c];
-                                if ((cn.x >> 2) != have) {
-                                    have = cn.x >> 2;
-                                    philox10<true>(have, s_lo, s_hi, 1u, key0, key1, c0, c1, c2, c3);
-                                }
-                                const uint32_t q = cn.x & 3u;
-                                // outcome 1 iff (word + 1/2) 2^-32 >= 1/2
-                                if ((q == 0u ? c0 : q == 1u ? c1 : q == 2u ? c2 : c3) >> 31) add_vec(cn.y);
-                            }
-                            find_first();
-                        }
-                    }
-                    cur += take;
-                }
-            }
-        }
-
-        // ---- one step of every shot in flight ----
-        bool run = act;
-        uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0, m = 0;
-        if (act) {
-            philox10<true>((pos >> 2) + sub, s_lo, s_hi, GAPS ? 2u : 0u, key0, key1, w0, w1, w2, w3);
-            if (GAPS) {
-                // Two candidates a block (gap word, acceptance word).  The gap
-                // is the table's #{j : w < tb[j]}; its estimate from the
-                // word's logarithm puts four entries around it, which decide
-                // it unless they do not bracket it (then a binary search).
-                const uint32_t *tb = P.gaps + gap_off;
-#pragma unroll 1
-                for (int half = 0; half < 2; ++half) {
-                    if (!run) continue;
-                    const uint32_t w = half ? w2 : w0, aw = half ? w3 : w1;
-                    pos += 2u;
-                    const uint32_t lim = n_noise - drawn;
-                    const float est = fminf(fmaxf((__log2f((float)w + 0.5f) - 32.0f) * l2q, 0.0f), (float)lim);
-                    const uint32_t b = max((uint32_t)est, 2u) - 2u;
-                    uint32_t t[4];
-                    __builtin_memcpy(t, tb + b, 16);
-                    const uint32_t n = (w < t[0] ? 1u : 0u) + (w < t[1] ? 1u : 0u) + (w < t[2] ? 1u : 0u) + (w < t[3] ? 1u : 0u);
-                    uint32_t G = b + n;
-                    if (n == 4u || (n == 0u && b != 0u)) {
-                        uint32_t lo = 0, hi = lim;  // w < tb[j] for j < lo, not for j >= hi (or past the slots)
-                        while (lo < hi) {
-                            const uint32_t m = (lo + hi) >> 1;
-                            if (w < tb[m]) lo = m + 1u;
-                            else hi = m;
-                        }
-                        G = lo;
-                    }
-                    const uint32_t s = drawn + min(G, lim);
-                    while (run && s >= limit) run = settle();
-                    if (!run) continue;
-                    drawn = s + 1u;
-                    const SignSlot sl = P.slots[slot_off + s];
-                    if (aw <= sl.acc1 && sl.kind != NZ_NONE) {
-                        hit(x, s, sl, aw, sl.acc1);
-                        ck = min(ck, sl.ckpt);
-                        find_first();
-                    }
-                }
-            } else {
-                // Signatures only reach forward, so hits past `limit` may be
-                // taken too: they change nothing at or before test `row`.
-                const uint32_t s0 = pos + 4u * sub;
-                const uint4 th = *reinterpret_cast<const uint4 *>(P.tm1 + tm1_off + s0);
-                m = (w0 <= th.x ? 1u : 0u) | (w1 <= th.y ? 2u : 0u) | (w2 <= th.z ? 4u : 0u) | (w3 <= th.w ? 8u : 0u);
-            }
-        }
-        if (!GAPS && __ballot(m != 0u) != 0ull) {
-            uint32_t d[W], dck = 0xFFFFFFFFu;  // what this lane's hits change
-#pragma unroll
-            for (int w = 0; w < W; ++w) d[w] = 0u;
-            while (m) {
-                const uint32_t j = (uint32_t)__builtin_ctz(m), s = pos + 4u * sub + j;
-                m &= m - 1u;
-                if (s >= n_noise) break;
-                const SignSlot sl = P.slots[slot_off + s];
-                const uint32_t w = j == 0u ? w0 : j == 1u ? w1 : j == 2u ? w2 : w3;
-                if (sl.kind != NZ_NONE) {
-                    hit(d, s, sl, w, sl.thr1);
-                    if (s < limit) dck = min(dck, sl.ckpt);
-                }
-            }
-#pragma unroll
-            for (uint32_t o = GL / 2u; o >= 1u; o >>= 1) {
-#pragma unroll
-                for (int w = 0; w < W; ++w) d[w] ^= (uint32_t)__shfl_xor((int)d[w], (int)o, 64);
-                dck = min(dck, (uint32_t)__shfl_xor((int)dck, (int)o, 64));
-            }
-#pragma unroll
-            for (int w = 0; w < W; ++w) x[w] ^= d[w];
-            ck = min(ck, dck);
-            if (act) find_first();
-        }
-        if (!GAPS) {
-            pos += 4u * GL;
-            while (run && pos >= limit) run = settle();
-        }
-
-        // ---- shots that ended ----
-        const bool fin = act && !run;
-        if (__ballot(fin) != 0ull) {
             bool pass = false, disc = false, logical = false;
             if (fin) {
+                ConstParams *A = args();
+                ConstDesc *D = desc();
                 act = false;
-                const SignTest T = P.tests[test_off + (row == kLeft ? 0u : row)];
+                const uint32_t r = D->test_off + (row == kLeft ? 0u : row);
+                const SignTest T = A->tests[r];
                 if (sub != 0u) {
                     // the group's first lane writes
                 } else if (row == kLeft || T.kind == SGT_HAND) {
-                    P.status[i] = kStatusPending;
+                    A->status[i] = kStatusPending;
                 } else {
-                    const uint32_t *mk = P.mask + (size_t)(test_off + row) * RO;
+                    const uint32_t *mk = A->mask + (size_t)r * RO;
                     const uint32_t obs = x[W - 1] & mk[RO - 1];
                     pass = T.kind == SGT_NONE;
                     disc = !pass;
                     logical = pass && obs != 0u;
-                    P.status[i] = pass ? (uint32_t)ST_PASSED : (uint32_t)ST_DISCARDED;
-                    if (P.abort_op) P.abort_op[i] = T.src;
-                    if (P.obs) P.obs[i] = obs;
-                    if (P.outcomes) {
+                    A->status[i] = pass ? (uint32_t)ST_PASSED : (uint32_t)ST_DISCARDED;
+                    if (A->abort_op) A->abort_op[i] = T.src;
+                    if (A->obs) A->obs[i] = obs;
+                    if (A->outcomes) {
 #pragma unroll
                         for (int w = 0; w < RO - 1; ++w)
-                            if ((uint32_t)w < P.rec_words) P.outcomes[(uint64_t)w * P.n_shots + i] = x[TW + w] & mk[w];
+                            if ((uint32_t)w < A->rec_words) A->outcomes[(uint64_t)w * A->n_shots + i] = x[TW + w] & mk[w];
                     }
                     words += GAPS ? pos : min(pos, n_noise);
                     atomicAdd(&hist[ck], 1u);
@@ -429,10 +308,178 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
             n_disc += (uint32_t)__builtin_popcountll(__ballot(disc));
             n_logical += (uint32_t)__builtin_popcountll(__ballot(logical));
             n_broke += (uint32_t)__builtin_popcountll(__ballot((pass || disc) && broke));
-            n_prefix += (uint32_t)__builtin_popcountll(__ballot((pass || disc) && ck != 0u && P.prefix != 0u));
+            n_prefix += (uint32_t)__builtin_popcountll(__ballot((pass || disc) && ck != 0u && args()->prefix != 0u));
+
+            const uint64_t idle = __ballot(!act);
+            if (rest == 0u && !dry) {
+                ConstParams *A = args();
+                uint64_t got;
+                dry = !take_item(A->next, (A->n_shots + A->chunk - 1u) / A->chunk, blockIdx.x, gridDim.x, lane, started, got);
+                if (!dry) {
+                    cur = got * A->chunk;
+                    rest = (uint32_t)min((uint64_t)A->chunk, A->n_shots - cur);
+                }
+            }
+            if (dry && idle == ~0ull) break;
+            if (rest != 0u && idle != 0ull) {
+                ConstParams *A = args();
+                const uint64_t shot = A->shot0 + cur;
+                ConstVariant *V = (ConstVariant *)A->vars;
+                bool ready = var != 0xFFFFFFFFu && shot < V[var].shot_end && (var == 0u || shot >= V[var - 1u].shot_end);
+                if (!ready && idle == ~0ull) {  // another variant, once no lane runs the last one
+                    if (var != 0xFFFFFFFFu) flush();
+                    var = 0;
+                    while (var + 1u < A->n_vars && V[var].shot_end <= shot) ++var;
+                    var = first32(var);
+                    ConstDesc *D = desc();
+                    n_noise = V[var].n_noise;
+                    n_tests = D->n_tests;
+                    l2q = V[var].gap_l2q;
+                    draws = GAPS ? A->gaps + V[var].gap_off : A->tm1 + V[var].tm1_off;
+                    slots = A->slots + D->slot_off;
+                    vecs = A->vecs + (size_t)D->vec_off * Q;
+                    zero_vec = 0u - D->vec_off;
+                    if (D->on)
+                        for (uint32_t t = lane; t <= n_tests; t += 64u) stops[t] = A->tests[D->test_off + t].stop;
+                    __syncthreads();  // (one wave: its LDS writes are done)
+                    ready = true;
+                }
+                if (ready) {
+                    ConstDesc *D = desc();
+                    const uint64_t left = min((uint64_t)rest, V[var].shot_end - shot);
+                    const uint32_t take = (uint32_t)min(left, (uint64_t)((uint32_t)__builtin_popcountll(idle) / GL));
+                    const uint32_t rank = (uint32_t)__builtin_popcountll(idle & ((1ull << (lane - sub)) - 1ull)) / GL;
+                    if (!act && rank < take) {
+                        i = cur + rank;
+                        if (!(D->on & (GAPS ? 1u : 2u))) {
+                            if (sub == 0u) A->status[i] = kStatusPending;
+                        } else {
+                            act = true;
+                            s_lo = (uint32_t)(A->shot0 + i);
+                            s_hi = (uint32_t)((A->shot0 + i) >> 32);
+#pragma unroll
+                            for (int w = 0; w < W; ++w) x[w] = 0u;
+                            add_to(x, A->vecs + (size_t)D->ref_vec * Q);
+                            pos = drawn = 0u;
+                            pids = npend = gens = 0u;
+                            held = broke = false;
+                            ck = D->ck_cnt;
+                            uint32_t have = 0xFFFFFFFFu, c0 = 0, c1 = 0, c2 = 0, c3 = 0;
+                            const uint32_t n_coins = D->n_coins;
+                            for (uint32_t c = 0; c < n_coins; ++c) {
+                                const uint2 cn = A->coins[D->coin_off + c];
+                                if ((cn.x >> 2) != have) {
+                                    have = cn.x >> 2;
+                                    philox10<true>(have, s_lo, s_hi, 1u, key0, key1, c0, c1, c2, c3);
+                                }
+                                const uint32_t q = cn.x & 3u;
+                                // outcome 1 iff (word + 1/2) 2^-32 >= 1/2
+                                if ((q == 0u ? c0 : q == 1u ? c1 : q == 2u ? c2 : c3) >> 31)
+                                    add_to(x, A->vecs + (size_t)cn.y * Q);
+                            }
+                            find_first();
+                        }
+                    }
+                    cur += take;
+                    rest -= take;
+                }
+            }
+        }
+
+        // ---- one step of every shot in flight: a Philox block a lane ----
+        const bool run = act && !stop;
+        uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0, m = 0;
+        if (run) {
+            philox10<true>((pos >> 2) + sub, s_lo, s_hi, GAPS ? 2u : 0u, key0, key1, w0, w1, w2, w3);
+            if (GAPS) {
+                // Two candidates a block (gap word, acceptance word).  The gap
+                // is the table's #{j : w < tb[j]}; its estimate from the
+                // word's logarithm puts four entries around it, which decide
+                // it unless they do not bracket it (then a binary search).  A
+                // candidate that a settled shot held back goes first.
+#pragma unroll 1
+                for (uint32_t half = 0; half < 2u; ++half) {
+                    uint32_t s = next_s, aw = next_w;
+                    if (stop) continue;
+                    if (!held) {
+                        if ((pos & 2u) != 2u * half) continue;
+                        const uint32_t w = half ? w2 : w0;
+                        aw = half ? w3 : w1;
+                        pos += 2u;
+                        const uint32_t lim = n_noise - drawn;
+                        const float est = fminf(fmaxf((__log2f((float)w + 0.5f) - 32.0f) * l2q, 0.0f), (float)lim);
+                        const uint32_t b = max((uint32_t)est, 2u) - 2u;
+                        uint32_t t[4];
+                        __builtin_memcpy(t, draws + b, 16);
+                        const uint32_t n = (w < t[0] ? 1u : 0u) + (w < t[1] ? 1u : 0u) + (w < t[2] ? 1u : 0u) + (w < t[3] ? 1u : 0u);
+                        uint32_t G = b + n;
+                        if (n == 4u || (n == 0u && b != 0u)) {
+                            uint32_t lo = 0, hi = lim;  // w < draws[j] for j < lo, not for j >= hi (or past the slots)
+                            while (lo < hi) {
+                                const uint32_t h = (lo + hi) >> 1;
+                                if (w < draws[h]) lo = h + 1u;
+                                else hi = h;
+                            }
+                            G = lo;
+                        }
+                        s = drawn + min(G, lim);
+                    }
+                    if (s >= limit) {
+                        stop = true;
+                        next_s = s;
+                        next_w = aw;
+                        continue;
+                    }
+                    held = false;
+                    drawn = s + 1u;
+                    const SignSlot sl = slots[s];
+                    if (aw <= sl.acc1 && sl.kind != NZ_NONE) {
+                        hit(x, s, sl.kind, aw, sl.acc1);
+                        ck = min(ck, sl.ckpt);
+                        find_first();
+                    }
+                }
+            } else {
+                // Signatures only reach forward, so hits past `limit` may be
+                // taken too: they change nothing at or before test `row`.
+                const uint4 th = *reinterpret_cast<const uint4 *>(draws + pos + 4u * sub);
+                m = (w0 <= th.x ? 1u : 0u) | (w1 <= th.y ? 2u : 0u) | (w2 <= th.z ? 4u : 0u) | (w3 <= th.w ? 8u : 0u);
+            }
+        }
+        if (!GAPS) {
+            if (__ballot(m != 0u) != 0ull) {
+                uint32_t d[W], dck = 0xFFFFFFFFu;  // what this lane's hits change
+#pragma unroll
+                for (int w = 0; w < W; ++w) d[w] = 0u;
+                while (m) {
+                    const uint32_t j = (uint32_t)__builtin_ctz(m), s = pos + 4u * sub + j;
+                    m &= m - 1u;
+                    if (s >= n_noise) break;
+                    const SignSlot sl = slots[s];
+                    const uint32_t w = j == 0u ? w0 : j == 1u ? w1 : j == 2u ? w2 : w3;
+                    if (sl.kind != NZ_NONE) {
+                        hit(d, s, sl.kind, w, sl.thr1);
+                        if (s < limit) dck = min(dck, sl.ckpt);
+                    }
+                }
+#pragma unroll
+                for (uint32_t o = GL / 2u; o >= 1u; o >>= 1) {
+#pragma unroll
+                    for (int w = 0; w < W; ++w) d[w] ^= (uint32_t)__shfl_xor((int)d[w], (int)o, 64);
+                    dck = min(dck, (uint32_t)__shfl_xor((int)dck, (int)o, 64));
+                }
+#pragma unroll
+                for (int w = 0; w < W; ++w) x[w] ^= d[w];
+                ck = min(ck, dck);
+                if (run) find_first();
+            }
+            if (run) {
+                pos += 4u * GL;
+                stop = pos >= limit;
+            }
         }
     }
-    if (var_end) flush();
+    if (var != 0xFFFFFFFFu) flush();
 }
 
 template <int TW, int RO> const void *kernel_of(bool gaps) {

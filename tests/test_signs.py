@@ -23,6 +23,7 @@ KEYS = ("p1", "p2", "p_idle", "p_meas", "p_reset", "p_mpp")
 
 DRIVER = r"""
 #include "signs.h"
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <fstream>
@@ -57,7 +58,7 @@ int main(int argc, char **argv) {
         // shift, vector) on top of the entry that x follows.
         struct Gen { uint64_t beta; std::vector<uint32_t> v; };
         std::vector<Gen> gen;
-        uint32_t t = 0, m = 0;  // first set test; measurements passed
+        uint32_t t = 0, m = 0, m_at = 0;  // first set test; measurements passed, and the next that reads
         bool hand = false;
         auto first = [&]() { for (t = 0; t < nt && !((x[t >> 5] >> (t & 31u)) & 1u); ++t) {} };
         auto apply = [&](uint32_t s) {
@@ -83,6 +84,7 @@ int main(int argc, char **argv) {
                 if (reads) break;
                 ++c;
             }
+            m_at = c;
             const bool at_meas = !gen.empty() && c < S.meas.size() && t >= S.meas[c].test;
             const uint32_t stop = at_meas ? S.meas[c].stop : S.tests[t].stop;
             if (s < stop) { apply(s++); continue; }
@@ -114,7 +116,7 @@ int main(int argc, char **argv) {
             }
             if (hand || gen.size() == 4) { hand = true; break; }
             gen.push_back(Gen{Q.beta, S.pair_vecs[Q.vec]});
-            m = Q.meas;
+            m = gen.size() > 1 ? std::min(m_at, Q.meas) : Q.meas;
         }
         if (hand) { std::printf("-\n"); continue; }
         const SignTest &T = S.tests[t];
