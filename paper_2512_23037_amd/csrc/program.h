@@ -333,12 +333,12 @@ struct alignas(16) SignMeas {
     uint32_t stop;  // noise slots from `stop` on come after it
     uint32_t test;  // first test at or after it
     uint32_t slot;  // its measurement word
-    uint32_t rec;   // its record bit; kNoRec: the sampler kernel runs a shot with pairs
-                    // pending here (unrecorded, its record may be flipped by noise, or a
-                    // coin that moves the entries: gamma ~0)
-    uint32_t pad[2];
+    uint32_t rec;   // its record bit; kNone: the sampler kernel runs a shot with pairs
+                    // pending here (unrecorded, or a coin that moves the entries: gamma ~0)
+    uint32_t flip;  // the noise slot (after it) that flips the record bit, or kNone
+    uint32_t pad;
 };
-constexpr uint32_t kNoRec = 0xFFFFFFFFu;
+constexpr uint32_t kNone = 0xFFFFFFFFu;
 // A noise slot as the sign pass reads it: its signature vectors (XERR, FLIP
 // in the first; ZERR in the third) are X_a, Y_a, Z_a, X_b, Y_b, Z_b.
 struct alignas(16) SignSlot {

@@ -68,9 +68,13 @@ void build_signs(const Program &P, SignProgram &out) {
     while (last < n && P.events[last].kind != EV_END && !stops(P.events[last])) ++last;
     if (last >= n) return;
     out.complete = P.events[last].kind == EV_END;
-    std::vector<bool> flipped(P.n_rec, false);  // records that noise may flip
-    for (const NoiseLoc &L : P.noise)
-        if (L.kind == NZ_FLIP) flipped[L.rec] = true;
+    std::vector<uint32_t> flip_of(P.n_rec, kNone);  // the noise slot that flips a record
+    for (uint32_t s = 0; s < P.n_noise; ++s) {
+        const NoiseLoc &L = P.noise[s];
+        if (L.kind != NZ_FLIP) continue;
+        if (flip_of[L.rec] != kNone) return;  // (a record has one)
+        flip_of[L.rec] = s;
+    }
     auto is_t = [](const Event &E) { return E.kind == EV_T_PHASE || E.kind == EV_T_DOUBLE || E.kind == EV_T_BFLY; };
 
     // ---- pairs by closing event ----
@@ -146,9 +150,9 @@ void build_signs(const Program &P, SignProgram &out) {
             case EV_M_DET: case EV_M_SPLIT: {
                 uint32_t bit = (E.cexp == 2u ? 1u : 0u) ^ sga;
                 if (E.kind == EV_M_SPLIT || E.gamma) {
-                    const bool ok = E.kind == EV_M_DET && (E.flags & EVF_RECORD) && !flipped[E.rec];
-                    out.meas.push_back(SignMeas{E.kind == EV_M_DET ? E.gamma : ~0ull, E.noise_end,
-                                                (uint32_t)tests.size(), E.mslot, ok ? E.rec : kNoRec, {0u, 0u}});
+                    const bool ok = E.kind == EV_M_DET && (E.flags & EVF_RECORD);
+                    out.meas.push_back(SignMeas{E.kind == EV_M_DET ? E.gamma : ~0ull, E.noise_end, (uint32_t)tests.size(),
+                                                E.mslot, ok ? E.rec : kNone, ok ? flip_of[E.rec] : kNone, 0u});
                 }
                 if (E.kind == EV_M_SPLIT) {
                     bit = 0u;  // the coin's 0; its 1 is one more vector

@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
         const SignPair *pairs = A->pairs + D->pair_off;
         if (gens != 0u && row >= mtest) {
             const SignMeas M = A->meas[D->meas_off + mrow];
-            if (M.rec == kNoRec) {
+            if (M.rec == kNone) {
                 row = kLeft;
                 return false;
             }
@@ -203,6 +203,11 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
             for (int w = 0; w < RO - 1; ++w)
                 if ((M.rec >> 5) == (uint32_t)w) o = (x[TW + w] >> (M.rec & 31u)) & 1u;
+            if (!GAPS && M.flip < pos) {  // its record flip comes after, but x has it if it hit
+                philox10<true>(M.flip >> 2, s_lo, s_hi, 0u, key0, key1, c0, c1, c2, c3);
+                const uint32_t f = M.flip & 3u;
+                o ^= (f == 0u ? c0 : f == 1u ? c1 : f == 2u ? c2 : c3) <= draws[M.flip] && slots[M.flip].kind == NZ_FLIP ? 1u : 0u;
+            }
             // one shift that it reads is decided, the others lose it
             uint32_t pivot = 0;
 #pragma unroll

@@ -90,7 +90,7 @@ int main(int argc, char **argv) {
             if (s < stop) { apply(s++); continue; }
             if (at_meas) {
                 const SignMeas &M = S.meas[c];
-                if (M.rec == kNoRec) { hand = true; break; }
+                if (M.rec == kNone) { hand = true; break; }
                 const uint32_t bit = words[P.n_noise + M.slot] >> 31;
                 const uint32_t o = (x[tw + (M.rec >> 5)] >> (M.rec & 31u)) & 1u;
                 size_t p = gen.size();
@@ -182,7 +182,7 @@ def test_workloads(driver, name, rate):
     n = 3000
     decided, on, complete = check(driver, w.text, w.noise, 1, n, rate)
     assert on and complete == name.startswith("cultivation")
-    assert decided > (0.9 if rate or name == "clifford_t_8q" else 0.99) * n
+    assert decided > (0.9 if name == "clifford_t_8q" else 0.99) * n
     if complete:
         assert check.resolved > 20  # broken pairs whose branch a measurement took
 
