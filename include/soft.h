@@ -254,9 +254,11 @@ int soft_set_noise_mode(soft_ctx *ctx, int mode);
  * noise Paulis are the only per-shot randomness before it), so every such
  * shot is in the same state at each point there.  The compiler marks up to 16
  * checkpoints per event list (around the check rounds, and before the first
- * random measurement or the end); each run first computes the noiseless
- * trajectory once per variant and list on the GPU (the same per-shot code,
- * noise off) and stores the state at every checkpoint; a shot then starts at
+ * random measurement or the end); the first run after a load, or after a
+ * change of precision, pruning threshold or support cap, first computes the
+ * noiseless trajectory once per variant and list on the GPU (the same per-shot
+ * code, noise off) and stores the state at every checkpoint for the runs that
+ * follow (soft_run_noalloc does so in every call, in its own scratch); a shot then starts at
  * the last checkpoint before its first noise hit, and loads that
  * checkpoint's coefficient tile only if an event reads it.  Results are
  * identical bit for bit either way (the same arithmetic on the same values);

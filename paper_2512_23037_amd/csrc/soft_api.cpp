@@ -110,6 +110,9 @@ struct soft_ctx {
     DevBuf<unsigned char> d_prefix;           // checkpoint state slots (one per table entry)
     DevBuf<Checkpoint> d_ckpt;                // checkpoint table
     uint32_t n_ckpt = 0;                      // its entries
+    // What the states in d_prefix were built for (none: empty); a run that
+    // asks for the same ones leaves the build out.
+    std::vector<uint64_t> prefix_key;
     DevBuf<unsigned char> d_signs;            // the sign pass's tables, one after the other
     SignParams sign_tables = {};              // their places in it
     uint32_t sign_size = 0;                   // their vector size (kSignTestWords)
@@ -158,6 +161,8 @@ struct soft_ctx {
 
     bool ran = false;
     hipStream_t last_stream = nullptr;
+    hipStream_t graph_stream = nullptr;  // of the last graph launch, and the event after it (a slot's)
+    hipEvent_t graph_done = nullptr;
     uint64_t last_shot0 = 0, last_n = 0;
     bool last_list = false;  // the last run sampled a shot list
 };
@@ -502,6 +507,7 @@ int prepare(soft_ctx *c) {
     HIPCHK(c, hipMemcpy(c->d_vars.p, vd.data(), vd.size() * sizeof(VariantDesc), hipMemcpyHostToDevice));
     if ((rc = prepare_signs(c))) return rc;
     c->dirty = false;
+    c->prefix_key.clear();
     drop_graph(c);
     return SOFT_OK;
 }
@@ -688,8 +694,13 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
         if (rc) return rc;
         rp.gtile = c->d_gtile.p;
     }
-    // shared-prefix slots, filled by the build launch before the sampler
+    // Shared-prefix slots, filled by the build launch before the sampler.  The
+    // states depend on the loaded tables and on what this key holds, so they
+    // stay for the runs that follow: one wave walks a whole list for them
+    // (85 to 265 us, with the sign pass most of a launch of 10^5 shots).  Runs
+    // of a context are in stream order, or ordered by the caller.
     const bool pfx = use_prefix(c);
+    std::vector<uint64_t> pkey;
     rp.prefix = nullptr;
     rp.prefix_stride = 0;
     if (pfx) {
@@ -697,7 +708,12 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
         if (rc) return rc;
         rp.prefix = c->d_prefix.p;
         rp.prefix_stride = prefix_stride(c);
+        const double tau = tau_of(c);
+        uint64_t tb;
+        std::memcpy(&tb, &tau, sizeof(tb));
+        pkey = {(uint64_t)(uintptr_t)c->d_prefix.p, (uint64_t)c->bits, tb, rp.support_cap};
     }
+    const bool build = pfx && pkey != c->prefix_key;
     const uint64_t bgrid = std::min<uint64_t>(grid, (2ull * rp.n_vars + s.wpb - 1) / s.wpb);
     const bool sgn = use_signs(c, rp);
     rp.grab = group_size(c, s, grid, n_shots, sgn);
@@ -741,6 +757,7 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     if (gs.launched) HIPCHK(c, hipEventSynchronize(gs.done));  // its previous launch may still read its arguments
     gs.args = rp;
     gs.bargs = build_params(rp);
+    if (!build) gs.bargs.n_shots = 0;  // the node finds nothing to do
     gs.sargs = sp;
     void *args[7] = {(void *)&gs.args.ev, (void *)&gs.args.nz, (void *)&gs.args.tm1, (void *)&gs.args.det,
                      (void *)&gs.args.words, (void *)&gs.args.bm, (void *)&gs.args};
@@ -801,8 +818,14 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
         gs.key = key;
         ++c->graph_instantiations;
     }
+    // another stream than the last launch's: after it, for the states it built
+    if (c->graph_done && stream != c->graph_stream) HIPCHK(c, hipStreamWaitEvent(stream, c->graph_done, 0));
+    if (build) c->prefix_key.clear();
     HIPCHK(c, hipGraphLaunch(gs.exec, stream));
+    if (build) c->prefix_key = pkey;
     HIPCHK(c, hipEventRecord(gs.done, stream));
+    c->graph_done = gs.done;
+    c->graph_stream = stream;
     gs.launched = true;
     ++c->graph_launches;
     return SOFT_OK;

@@ -126,3 +126,36 @@ def test_null_outputs_and_noalloc():
         f(4, n, status=st)
         torch.cuda.synchronize()
         assert (st.cpu().numpy().view(np.uint32) == ref["status"]).all()
+
+
+def test_states_kept_between_runs():
+    # the checkpoint states of a context stay for the runs that follow, on
+    # this stream or another; a new precision, pruning threshold, support cap
+    # or circuit builds them again
+    import torch
+    w = workloads.config("cultivation_42q", seed=1)
+    N = 20_000
+
+    def fresh(bits, tau, cap, text=w.text):
+        ctx = make_ctx(text, w.noise, seed=8, bits=bits, tau=tau, cap=cap, keep=(0, 16))
+        out = run_gpu(ctx, 0, N)
+        return out, [ctx.read_coeffs(s) for s in range(16)], ctx.counters()["support_hist"]
+
+    ctx = make_ctx(w.text, w.noise, seed=8, bits=64, keep=(0, 16))
+    other = workloads.config("cultivation_15q", seed=1).text
+    side = torch.cuda.Stream()
+    for bits, tau, cap, text in ((64, -1.0, 0, w.text), (64, -1.0, 0, w.text), (32, -1.0, 0, w.text), (32, 1e-3, 0, w.text),
+                                 (64, -1.0, 512, w.text), (64, -1.0, 0, w.text), (64, -1.0, 0, other), (64, -1.0, 0, w.text)):
+        if text is not w.text or bits == 64:
+            ctx.load_circuit(text)
+        ctx.set_precision(bits)
+        ctx.set_prune(tau)
+        ctx.set_caps(cap)
+        ref, kept, hist = fresh(bits, tau, cap, text)
+        for stream in (None, side, None):
+            with torch.cuda.stream(stream or torch.cuda.current_stream()):
+                got = run_gpu(ctx, 0, N)
+            for k in ("status", "abort_op", "obs", "outcomes"):
+                assert (got[k] == ref[k]).all(), (bits, tau, cap, k)
+            assert [ctx.read_coeffs(s) for s in range(16)] == kept
+            assert ctx.counters()["support_hist"] == hist
