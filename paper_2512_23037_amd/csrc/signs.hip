@@ -106,6 +106,7 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
     bool stop = false;   // no slot below `limit` is undecided: to be settled
     uint64_t i = 0;
     uint32_t s_lo = 0, s_hi = 0;
+    PhiloxShot stream0 = {0, 0, 0};  // a word per slot: the shot's noise words
     uint32_t x[W];
     uint32_t pos = 0;    // next word (GAPS) or noise slot (of the lane's group)
     uint32_t drawn = 0;  // GAPS: slots decided
@@ -362,6 +363,7 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
                             act = true;
                             s_lo = (uint32_t)(A->shot0 + i);
                             s_hi = (uint32_t)((A->shot0 + i) >> 32);
+                            if (!GAPS) stream0.start(s_lo, s_hi, key0);
 #pragma unroll
                             for (int w = 0; w < W; ++w) x[w] = 0u;
                             add_to(x, A->vecs + (size_t)D->ref_vec * Q);
@@ -393,9 +395,12 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
 
         // ---- one step of every shot in flight: a Philox block a lane ----
         const bool run = act && !stop;
-        uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0, m = 0;
+        uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
+        uint4 th;
+        bool any = false;  // one of the lane's slots is hit
         if (run) {
-            philox10<true>((pos >> 2) + sub, s_lo, s_hi, GAPS ? 2u : 0u, key0, key1, w0, w1, w2, w3);
+            if (GAPS) philox10<true>(pos >> 2, s_lo, s_hi, 2u, key0, key1, w0, w1, w2, w3);
+            else stream0.block((pos >> 2) + sub, 0u, key0, key1, w0, w1, w2, w3);
             if (GAPS) {
                 // Two candidates a block (gap word, acceptance word).  The gap
                 // is the table's #{j : w < tb[j]}; its estimate from the
@@ -447,13 +452,14 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
             } else {
                 // Signatures only reach forward, so hits past `limit` may be
                 // taken too: they change nothing at or before test `row`.
-                const uint4 th = *reinterpret_cast<const uint4 *>(draws + pos + 4u * sub);
-                m = (w0 <= th.x ? 1u : 0u) | (w1 <= th.y ? 2u : 0u) | (w2 <= th.z ? 4u : 0u) | (w3 <= th.w ? 8u : 0u);
+                th = *reinterpret_cast<const uint4 *>(draws + pos + 4u * sub);
+                any = (w0 <= th.x) | (w1 <= th.y) | (w2 <= th.z) | (w3 <= th.w);
             }
         }
         if (!GAPS) {
-            if (__ballot(m != 0u) != 0ull) {
+            if (__ballot(any) != 0ull) {
                 uint32_t d[W], dck = 0xFFFFFFFFu;  // what this lane's hits change
+                uint32_t m = any ? (w0 <= th.x ? 1u : 0u) | (w1 <= th.y ? 2u : 0u) | (w2 <= th.z ? 4u : 0u) | (w3 <= th.w ? 8u : 0u) : 0u;
 #pragma unroll
                 for (int w = 0; w < W; ++w) d[w] = 0u;
                 while (m) {
