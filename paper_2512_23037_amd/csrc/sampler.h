@@ -89,7 +89,7 @@ hipError_t launch_signs(const SignParams &p, uint32_t size, bool gaps, dim3 grid
 
 // Work cursors, after the counter rows: the eight of a queue (take_item), each
 // in a cache line of its own, for the sampler, the sign pass and the prefix
-// build.
+// build (a launch of its own, at most one item a wave but in soft_run_noalloc).
 constexpr uint32_t kQueueCursors = 8, kCursorStride = 16, kQueueWords = kQueueCursors * kCursorStride;
 constexpr uint32_t kSampleCursor = 0, kSignCursor = kQueueWords, kBuildCursor = 2 * kQueueWords;
 constexpr uint32_t kCursorWords = 3 * kQueueWords;

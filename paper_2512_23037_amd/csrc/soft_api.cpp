@@ -144,12 +144,10 @@ struct soft_ctx {
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;
         hipGraphNode_t sampler = nullptr;
-        hipGraphNode_t build = nullptr;  // the prefix build (between reset and sampler), if any
-        hipEvent_t done = nullptr;   // recorded after the slot's last launch
+            hipEvent_t done = nullptr;   // recorded after the slot's last launch
         bool launched = false;
         std::vector<unsigned char> key;  // kernel, grid, block, LDS, counters
         RunParams args;                  // argument storage of the sampler node
-        RunParams bargs;                 // and of the prefix build node
         hipGraphNode_t signs = nullptr;  // the sign pass (before the sampler), if any
         SignParams sargs;
         unsigned long long *r_counters = nullptr, *r_next = nullptr;  // reset node arguments
@@ -266,7 +264,6 @@ void drop_slot(soft_ctx *c, soft_ctx::GraphSlot &g) {
     g.exec = nullptr;
     g.graph = nullptr;
     g.sampler = nullptr;
-    g.build = nullptr;
     g.signs = nullptr;
     g.launched = false;
     g.key.clear();
@@ -620,6 +617,10 @@ uint64_t grid_blocks(const soft_ctx *c, const Shape &s, uint64_t n_shots) {
     return std::min<uint64_t>((uint64_t)c->num_cus * s.bpc, std::max<uint64_t>(blocks_needed, 1));
 }
 
+// Blocks of the prefix build: one item a wave, so that it needs no cursors and
+// may run before they are reset.
+uint32_t build_blocks(const Shape &s, const RunParams &rp) { return (2u * rp.n_vars + s.wpb - 1u) / s.wpb; }
+
 // LDS layout of a wave's slot (tile unless in device memory, record words
 // past kRecSgpr).
 void set_wave_layout(const soft_ctx *c, const Shape &s, RunParams &rp) {
@@ -689,8 +690,8 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     const uint64_t grid = grid_blocks(c, s, n_shots);
     const dim3 g((uint32_t)grid), b(64u * s.wpb);
     set_wave_layout(c, s, rp);
-    if (s.gt != TM_LDS) {  // one slab per wave of the grid
-        int rc = ensure(c, c->d_gtile, (size_t)grid * s.wpb * slab_bytes(c, s));
+    if (s.gt != TM_LDS) {  // one slab per wave of the grid (the build's or the sampler's)
+        int rc = ensure(c, c->d_gtile, std::max<size_t>(grid, build_blocks(s, rp)) * s.wpb * slab_bytes(c, s));
         if (rc) return rc;
         rp.gtile = c->d_gtile.p;
     }
@@ -714,7 +715,6 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
         pkey = {(uint64_t)(uintptr_t)c->d_prefix.p, (uint64_t)c->bits, tb, rp.support_cap};
     }
     const bool build = pfx && pkey != c->prefix_key;
-    const uint64_t bgrid = std::min<uint64_t>(grid, (2ull * rp.n_vars + s.wpb - 1) / s.wpb);
     const bool sgn = use_signs(c, rp);
     rp.grab = group_size(c, s, grid, n_shots, sgn);
     SignParams sp;
@@ -729,9 +729,9 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     const uint32_t ns = rp.words != nullptr ? NS_EXPLICIT : (rp.noise_mode == 1u ? NS_GAPS : NS_SLOTS);
     const void *kfn = sampler_kernel(c->bits == 64, ns, s.gt, sampler_lean(rp));
     // what the nodes' launch configuration and the reset node depend on
-    const uint64_t kv[11] = {(uint64_t)(uintptr_t)kfn, grid, (uint64_t)b.x, (uint64_t)lds,
+    const uint64_t kv[9] = {(uint64_t)(uintptr_t)kfn, grid, (uint64_t)b.x, (uint64_t)lds,
                             (uint64_t)(uintptr_t)rp.counters, (uint64_t)rp.n_vars, (uint64_t)(uintptr_t)rp.next,
-                            (uint64_t)pfx, pfx ? bgrid : 0ull, (uint64_t)(uintptr_t)sfn, (uint64_t)sgrid};
+                            (uint64_t)(uintptr_t)sfn, (uint64_t)sgrid};
     std::vector<unsigned char> key((const unsigned char *)kv, (const unsigned char *)kv + sizeof(kv));
     // The slot to use: one with this key whose last launch is done; else an
     // empty one (instantiated below); else one with this key (after waiting
@@ -756,15 +756,11 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     soft_ctx::GraphSlot &gs = *slot;
     if (gs.launched) HIPCHK(c, hipEventSynchronize(gs.done));  // its previous launch may still read its arguments
     gs.args = rp;
-    gs.bargs = build_params(rp);
-    if (!build) gs.bargs.n_shots = 0;  // the node finds nothing to do
     gs.sargs = sp;
     void *args[7] = {(void *)&gs.args.ev, (void *)&gs.args.nz, (void *)&gs.args.tm1, (void *)&gs.args.det,
                      (void *)&gs.args.words, (void *)&gs.args.bm, (void *)&gs.args};
-    void *bargs[7] = {(void *)&gs.bargs.ev, (void *)&gs.bargs.nz, (void *)&gs.bargs.tm1, (void *)&gs.bargs.det,
-                      (void *)&gs.bargs.words, (void *)&gs.bargs.bm, (void *)&gs.bargs};
     void *sargs[1] = {(void *)&gs.sargs};
-    hipKernelNodeParams kp, kb, ks;
+    hipKernelNodeParams kp, ks;
     std::memset(&kp, 0, sizeof(kp));
     std::memset(&ks, 0, sizeof(ks));
     ks.func = const_cast<void *>(sfn);
@@ -776,12 +772,7 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     kp.blockDim = b;
     kp.sharedMemBytes = (unsigned int)lds;
     kp.kernelParams = args;
-    kb = kp;
-    kb.func = const_cast<void *>(prefix_kernel(c->bits == 64, s.gt));
-    kb.gridDim = dim3((uint32_t)bgrid);
-    kb.kernelParams = bargs;
     if (gs.exec && gs.key == key) {
-        if (pfx) HIPCHK(c, hipGraphExecKernelNodeSetParams(gs.exec, gs.build, &kb));
         if (sgn) HIPCHK(c, hipGraphExecKernelNodeSetParams(gs.exec, gs.signs, &ks));
         HIPCHK(c, hipGraphExecKernelNodeSetParams(gs.exec, gs.sampler, &kp));
     } else {
@@ -800,10 +791,6 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
         hipError_t e = hipGraphCreate(&gs.graph, 0);
         if (e == hipSuccess) e = hipGraphAddKernelNode(&rnode, gs.graph, nullptr, 0, &rk);
         hipGraphNode_t before = rnode;
-        if (e == hipSuccess && pfx) {
-            e = hipGraphAddKernelNode(&gs.build, gs.graph, &rnode, 1, &kb);
-            before = gs.build;
-        }
         if (e == hipSuccess && sgn) {
             e = hipGraphAddKernelNode(&gs.signs, gs.graph, &before, 1, &ks);
             before = gs.signs;
@@ -820,7 +807,10 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     }
     // another stream than the last launch's: after it, for the states it built
     if (c->graph_done && stream != c->graph_stream) HIPCHK(c, hipStreamWaitEvent(stream, c->graph_done, 0));
-    if (build) c->prefix_key.clear();
+    if (build) {
+        c->prefix_key.clear();
+        HIPCHK(c, launch_prefix_build(build_params(rp), c->bits == 64, dim3(build_blocks(s, rp)), b, lds, stream));
+    }
     HIPCHK(c, hipGraphLaunch(gs.exec, stream));
     if (build) c->prefix_key = pkey;
     HIPCHK(c, hipEventRecord(gs.done, stream));
