@@ -69,11 +69,49 @@ __device__ __forceinline__ uint64_t lane64(uint64_t x, uint32_t l) {
 }
 __device__ __forceinline__ double unid(double x) { return __longlong_as_double((long long)uni64((uint64_t)__double_as_longlong(x))); }
 
+// x from the lane that differs in the lane bits of the step: 32 and 16 by the
+// half- and row-swapping instructions (of x with itself: one result holds the
+// lower halves twice, the other the upper), 8 and 4 by rotating the row of 16
+// (by 8 it is the lane ^ 8, and once the values repeat every 8 lanes, by 4 the
+// lane ^ 4), 2 and 1 within quads.
+template <int STEP> __device__ __forceinline__ uint32_t dpp_word(uint32_t x) {
+    constexpr int ctrl = STEP == 8 ? 0x128 : STEP == 4 ? 0x124 : STEP == 2 ? 0x4E : 0xB1;  // row_ror:8, row_ror:4, quad_perm
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, ctrl, 0xF, 0xF, true);
+}
+template <int STEP> __device__ __forceinline__ double sum_step(double x) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+    if (STEP >= 16) {
+        uint32_t l0, l1, h0, h1;
+        if (STEP == 32) {
+            auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+            auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+            l0 = l[0]; l1 = l[1]; h0 = h[0]; h1 = h[1];
+        } else {
+            auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+            auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+            l0 = l[0]; l1 = l[1]; h0 = h[0]; h1 = h[1];
+        }
+        return __longlong_as_double((long long)(((uint64_t)h0 << 32) | l0)) +
+               __longlong_as_double((long long)(((uint64_t)h1 << 32) | l1));
+    }
+    lo = dpp_word<STEP>(lo);
+    hi = dpp_word<STEP>(hi);
+    return x + __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
 // Butterfly sum over the 64 lanes; every lane ends with the same bits because
-// each step adds the same two partial sums in either order.
+// each step adds the same two partial sums in either order.  The steps move
+// data between lanes in registers: through the LDS crossbar each took two
+// permutes and their latency, six times in a row, and a measurement sums up to
+// three times.
 __device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
+    x = sum_step<32>(x);
+    x = sum_step<16>(x);
+    x = sum_step<8>(x);
+    x = sum_step<4>(x);
+    x = sum_step<2>(x);
+    x = sum_step<1>(x);
     return unid(x);
 }
 
@@ -1702,31 +1740,66 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
                     const uint32_t S = (uint32_t)__ballot(sgl != 0u);
                     const uint32_t e0 = uni(di->E[1]), e1 = uni(di->E[2]), e2 = uni(di->E[4]);
                     auto coset_el = [&](uint32_t w) { return ((w & 1u) ? e0 : 0u) ^ ((w & 2u) ? e1 : 0u) ^ ((w & 4u) ? e2 : 0u); };
+                    // the terms' fields, term g in lane g, read once: loads
+                    // of them in the pass made it wait term by term
+                    const uint32_t ugv = di->ug[lane & 7u], gmv = di->gm[lane & 7u];
+                    const R wrv = sizeof(R) == 4 ? (R)di->fre[lane & 7u] : (R)di->dre[lane & 7u];
+                    const R wiv = sizeof(R) == 4 ? (R)di->fim[lane & 7u] : (R)di->dim[lane & 7u];
+                    auto of_term = [&](uint32_t x, uint32_t g) { return uni((uint32_t)__builtin_amdgcn_readlane((int)x, (int)g)); };
+                    auto weight = [&](R x, uint32_t g) -> R {
+                        if (sizeof(R) == 4) return (R)__uint_as_float(of_term(__float_as_uint((float)x), g));
+                        return (R)__longlong_as_double((long long)lane64((uint64_t)__double_as_longlong((double)x), g));
+                    };
+                    // y + w x, as every term adds
+                    auto mac = [](C y, R wr, R wi, C x) {
+                        y.x = fma(wr, x.x, fma(-wi, x.y, y.x));
+                        y.y = fma(wr, x.y, fma(wi, x.x, y.y));
+                        return y;
+                    };
                     // the gate is unitary: the carried norm sets the pruning level
                     const R thr = (R)(tau2 * nrm2 * itscale2);
                     const uint32_t kin = 1u << k, um = (1u << r) - 1u;
                     uint32_t cnt = 0;
+                    if (ng == 2u && r == 1u) {
+                        // one qubit (the conditional S and T of gate
+                        // teleportation, RZ): pairs (j0, j1 = j0 ^ e0), each
+                        // read once; I is term 0, Z term 1
+                        const R w0r = weight(wrv, 0u), w0i = weight(wiv, 0u), w1r = weight(wrv, 1u), w1i = weight(wiv, 1u);
+                        const uint32_t g1 = of_term(gmv, 1u), s1 = (S >> 1) & 1u, h = lead & 31u, gp = par32(g1 & e0);
+                        const C z = mk<C>(0.0, 0.0);
+                        lane_pass(1u << (knew - 1u), lane, [&](uint32_t p) {
+                            const uint32_t j0 = ins0(p, h), j1 = j0 ^ e0;
+                            C x0 = v[j0 < kin ? j0 : 0u], x1 = v[j1 < kin ? j1 : 0u];
+                            if (j0 >= kin) x0 = z;
+                            if (j1 >= kin) x1 = z;
+                            const bool n0 = (s1 ^ par32(g1 & j0)) != 0u, n1 = n0 != (gp != 0u);  // Z's signs from j0, from j1
+                            bool k0, k1;
+                            const C o0 = t_keep<R, C>(mac(mac(z, w0r, w0i, x0), n1 ? -w1r : w1r, n1 ? -w1i : w1i, x1), thr, k0);
+                            const C o1 = t_keep<R, C>(mac(mac(z, w0r, w0i, x1), n0 ? -w1r : w1r, n0 ? -w1i : w1i, x0), thr, k1);
+                            cnt += (uint32_t)(__popcll(__ballot(k0)) + __popcll(__ballot(k1)));
+                            v[j0] = o0;
+                            v[j1] = o1;
+                        });
+                    } else {
                     lane_pass(1u << knew, lane, [&](uint32_t L) {
                         const uint32_t u = L & um;
                         uint32_t j0 = L >> r;  // zeros at the lead bits, ascending
                         for (uint32_t i = 0; i < r; ++i) j0 = ins0(j0, (lead >> (5u * i)) & 31u);
                         C y = mk<C>(0.0, 0.0);
                         for (uint32_t g = 0; g < ng; ++g) {
-                            const uint32_t jin = j0 ^ coset_el(u ^ uni(di->ug[g]));
+                            const uint32_t jin = j0 ^ coset_el(u ^ of_term(ugv, g));
                             C xv = v[jin < kin ? jin : 0u];
                             if (jin >= kin) xv = mk<C>(0.0, 0.0);
-                            const R wr = sizeof(R) == 4 ? (R)unif(di->fre[g]) : (R)unid(di->dre[g]);
-                            const R wi = sizeof(R) == 4 ? (R)unif(di->fim[g]) : (R)unid(di->dim[g]);
-                            const bool neg = (((S >> g) ^ par32(uni(di->gm[g]) & jin)) & 1u) != 0u;
-                            const R cr = neg ? -wr : wr, ci = neg ? -wi : wi;
-                            y.x = fma(cr, xv.x, fma(-ci, xv.y, y.x));
-                            y.y = fma(cr, xv.y, fma(ci, xv.x, y.y));
+                            const R wr = weight(wrv, g), wi = weight(wiv, g);
+                            const bool neg = (((S >> g) ^ par32(of_term(gmv, g) & jin)) & 1u) != 0u;
+                            y = mac(y, neg ? -wr : wr, neg ? -wi : wi, xv);
                         }
                         bool keep;
                         const C o = t_keep<R, C>(y, thr, keep);
                         cnt += (uint32_t)__popcll(__ballot(keep));
                         v[j0 ^ coset_el(u)] = o;
                     });
+                    }
                     k = knew;
                     cnt = uni(cnt);
                     maxsup = max(maxsup, cnt);
