@@ -537,8 +537,6 @@ __device__ __forceinline__ uint32_t t_double(const Tile<C, TM> &v, uint32_t lane
 }
 
 
-__device__ __forceinline__ float unif(float x) { return __uint_as_float(uni(__float_as_uint(x))); }
-
 // Fields of the current event (held one dword per lane in `evc`).
 #define EV32(f) ((uint32_t)__builtin_amdgcn_readlane((int)evc, (int)(offsetof(Event, f) / 4u)))
 #define EV64(f)                                                                                  \
@@ -555,11 +553,23 @@ __device__ __forceinline__ float unif(float x) { return __uint_as_float(uni(__fl
 // LEAN: a launch with no kept states, no trace, no support cap and no shot
 // list (and never the prefix build); those paths compile out, which frees
 // scalar registers in the event loop.
+// The launch's parameters, read again where they are used: kept in scalar
+// registers over a shot they spilled to lanes, which every use then reads back
+// with vector instructions.
+typedef const __attribute__((address_space(4))) RunParams ConstRun;
+__device__ __forceinline__ ConstRun &args() {
+    // the kernels' seventh argument, after six pointers
+    typedef const __attribute__((address_space(4))) unsigned char ConstByte;
+    ConstByte *p = (ConstByte *)__builtin_amdgcn_kernarg_segment_ptr() + 6u * sizeof(void *);
+    asm volatile("" : "+s"(p));
+    return *(ConstRun *)p;
+}
+
 template <typename R, uint32_t NS, uint32_t TM, bool LEAN = false>
 __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz,
                                              const uint32_t *__restrict__ tm1, const uint32_t *__restrict__ det,
                                              const uint32_t *__restrict__ words, const BatchMember *__restrict__ bm,
-                                             const RunParams &P) {
+                                             const RunParams &) {
     typedef typename Cx<R>::T C;
     constexpr bool EXPL = NS == NS_EXPLICIT, GAPS = NS == NS_GAPS;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -567,7 +577,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
     const uint32_t wave = threadIdx.x >> 6;
     // The coefficient tile lives in LDS; or (TM_MEM) in a per-wave slab of
     // device memory for spans whose tile does not fit in LDS; or (TM_SPLIT)
-    // its low P.lds_entries entries in LDS and the rest in a per-wave slab.
+    // its low args().lds_entries entries in LDS and the rest in a per-wave slab.
     // The record words past kRecSgpr are always in LDS.
     Tile<C, TM> v;
     v.hi = nullptr;
@@ -575,18 +585,18 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
     uint32_t *rec;
     const size_t gwave = (size_t)blockIdx.x * (blockDim.x >> 6) + wave;
     if (TM == TM_MEM) {
-        v.lo = reinterpret_cast<C *>(P.gtile) + gwave * P.tile_entries;
-        rec = reinterpret_cast<uint32_t *>(smem + (size_t)wave * P.wave_bytes);
+        v.lo = reinterpret_cast<C *>(args().gtile) + gwave * args().tile_entries;
+        rec = reinterpret_cast<uint32_t *>(smem + (size_t)wave * args().wave_bytes);
     } else {
-        v.lo = reinterpret_cast<C *>(smem + (size_t)wave * P.wave_bytes);
-        rec = reinterpret_cast<uint32_t *>(smem + (size_t)wave * P.wave_bytes + P.rec_off);
+        v.lo = reinterpret_cast<C *>(smem + (size_t)wave * args().wave_bytes);
+        rec = reinterpret_cast<uint32_t *>(smem + (size_t)wave * args().wave_bytes + args().rec_off);
         if (TM == TM_SPLIT) {
-            v.lim = P.lds_entries;
+            v.lim = args().lds_entries;
             // hi + j (j >= lim) is entry j's place in the slab: the slab's
             // address less lim entries, formed as an integer
-            const uintptr_t slab = reinterpret_cast<uintptr_t>(P.gtile) +
-                                   gwave * (size_t)(P.tile_entries - P.lds_entries) * sizeof(C);
-            v.hi = reinterpret_cast<C *>(slab - (uintptr_t)P.lds_entries * sizeof(C));
+            const uintptr_t slab = reinterpret_cast<uintptr_t>(args().gtile) +
+                                   gwave * (size_t)(args().tile_entries - args().lds_entries) * sizeof(C);
+            v.hi = reinterpret_cast<C *>(slab - (uintptr_t)args().lds_entries * sizeof(C));
         }
     }
     // Lanes read entries that other lanes wrote in the previous pass: with a
@@ -595,21 +605,21 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
     auto tile_sync = [&]() {
         if (TM != TM_LDS) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     };
-    const uint32_t key0 = (uint32_t)P.seed, key1 = (uint32_t)(P.seed >> 32);
-    const double tau2 = P.tau2;
+    const uint32_t key0 = (uint32_t)args().seed, key1 = (uint32_t)(args().seed >> 32);
+    const double tau2 = args().tau2;
 
     // The supports of the shots that the sign pass decided: those the
     // checkpoint before their first hit holds (C_CK0 counts them by
     // checkpoint), as for a shot that starts there and defers what follows.
-    if (LEAN && P.signs && gwave == 0) {
-        for (uint32_t x = 0; x < P.n_vars; ++x) {
+    if (LEAN && args().signs && gwave == 0) {
+        for (uint32_t x = 0; x < args().n_vars; ++x) {
             if (lane > kMaxCheckpoints) continue;
-            unsigned long long *row = P.counters + (size_t)x * C_COUNT;
+            unsigned long long *row = args().counters + (size_t)x * C_COUNT;
             const unsigned long long c = row[C_CK0 + lane];
             uint32_t sup = 1u;
-            if (lane && P.prefix && c) {
+            if (lane && args().prefix && c) {
                 const CkptState *cs = reinterpret_cast<const CkptState *>(
-                    P.prefix + (size_t)(P.vars[x].ck_off + lane - 1u) * P.prefix_stride);
+                    args().prefix + (size_t)(args().vars[x].ck_off + lane - 1u) * args().prefix_stride);
                 if (cs->valid == 1u) sup = max(1u, cs->maxsup);
             }
             if (c) atomicAdd(row + C_HIST0 + min(15u, 31u - (uint32_t)__clz(sup)), c);
@@ -626,12 +636,12 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
     bool var_ok = false;
     uint64_t var_lo = 0, var_end = 0;
     auto flush_counters = [&]() {
-        if ((!LEAN && P.prefix_build)) {  // the build samples no shots
+        if ((!LEAN && args().prefix_build)) {  // the build samples no shots
             myc = 0;
             maxdev = 0.0;
             return;
         }
-        unsigned long long *row = P.counters + (size_t)var * C_COUNT;
+        unsigned long long *row = args().counters + (size_t)var * C_COUNT;
         if (lane < (uint32_t)C_COUNT && lane != (uint32_t)C_NORMDEV_BITS && myc) atomicAdd(row + lane, (unsigned long long)myc);
         if (lane == (uint32_t)C_NORMDEV_BITS) atomicMax(row + lane, (unsigned long long)__double_as_longlong(maxdev));
         myc = 0;
@@ -650,50 +660,50 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
     // then status, abort op and observables; null when the caller did not ask.
     uint32_t *out_plane = nullptr;
     if (lane < kRecSgpr) {
-        if (P.outcomes && lane < P.rec_words) out_plane = P.outcomes + (uint64_t)lane * P.n_shots;
+        if (args().outcomes && lane < args().rec_words) out_plane = args().outcomes + (uint64_t)lane * args().n_shots;
     } else if (lane == kRecSgpr) {
-        out_plane = P.status;
+        out_plane = args().status;
     } else if (lane == kRecSgpr + 1u) {
-        out_plane = P.abort_op;
+        out_plane = args().abort_op;
     } else if (lane == kRecSgpr + 2u) {
-        out_plane = P.obs;
+        out_plane = args().obs;
     }
     while (true) {
         if (todo == 0ull) {
             if (group_rest == 0u) {
                 uint64_t item;
-                if (!take_item(P.next, (P.n_shots + P.grab - 1u) / P.grab, uni((uint32_t)gwave),
+                if (!take_item(args().next, (args().n_shots + args().grab - 1u) / args().grab, uni((uint32_t)gwave),
                                gridDim.x * (blockDim.x >> 6), lane, started, item))
                     break;
-                group_base = item * P.grab;
-                group_rest = (uint32_t)min((uint64_t)P.grab, P.n_shots - group_base);
+                group_base = item * args().grab;
+                group_rest = (uint32_t)min((uint64_t)args().grab, args().n_shots - group_base);
             } else {
                 group_base += 64u;
             }
             const uint32_t len = min(group_rest, 64u);
             group_rest -= len;
             // after the sign pass: the shots it left
-            todo = __ballot(lane < len && !(LEAN && P.signs && P.status[group_base + lane] != kStatusPending));
+            todo = __ballot(lane < len && !(LEAN && args().signs && args().status[group_base + lane] != kStatusPending));
             continue;
         }
         const uint64_t i = group_base + (uint32_t)__builtin_ctzll(todo);
         todo &= todo - 1ull;
         // a vector load of a uniform address: say that the result is uniform
         // (item i of the prefix build runs the first shot of variant i / 2)
-        const uint64_t shot = uni64((!LEAN && P.prefix_build) ? ((i >> 1) ? P.vars[(i >> 1) - 1u].shot_end : 0ull)
-                                    : (!LEAN && P.shot_list) ? P.shot_list[i] : P.shot0 + i);
+        const uint64_t shot = uni64((!LEAN && args().prefix_build) ? ((i >> 1) ? args().vars[(i >> 1) - 1u].shot_end : 0ull)
+                                    : (!LEAN && args().shot_list) ? args().shot_list[i] : args().shot0 + i);
         const uint32_t s_lo = (uint32_t)shot, s_hi = (uint32_t)(shot >> 32);
         if (!var_ok || shot >= var_end || shot < var_lo) {
             if (var_ok) flush_counters();
             // shots past the last range (possible only in a shot list) run as the last variant
             var = 0;
-            while (var + 1u < P.n_vars && P.vars[var].shot_end <= shot) ++var;
+            while (var + 1u < args().n_vars && args().vars[var].shot_end <= shot) ++var;
             var = uni(var);
-            var_lo = uni64(var ? P.vars[var - 1u].shot_end : 0ull);
-            var_end = uni64(P.vars[var].shot_end);
+            var_lo = uni64(var ? args().vars[var - 1u].shot_end : 0ull);
+            var_end = uni64(args().vars[var].shot_end);
             var_ok = true;
         }
-        const uint32_t *wrow = EXPL ? words + i * P.word_stride : nullptr;
+        const uint32_t *wrow = EXPL ? words + i * args().word_stride : nullptr;
 
         // ---- per-shot state (set at the start of each attempt below) ----
         // record words 0..3 live in scalar registers, the rest in LDS
@@ -766,10 +776,10 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         uint32_t m_base = 0xFFFFFF00u, mw0 = 0, mw1 = 0, mw2 = 0, mw3 = 0;
 
         // steps of this shot to trace (0 unless it is the traced shot)
-        const uint32_t trace_lim = LEAN ? 0u : uni(P.trace_n != 0u && shot == P.trace_shot ? P.trace_n : 0u);
+        const uint32_t trace_lim = LEAN ? 0u : uni(args().trace_n != 0u && shot == args().trace_shot ? args().trace_n : 0u);
         const bool tracing = trace_lim != 0u;
         // noise tables of this variant (read where used: the draws are rare)
-        const VariantDesc *vdp = P.vars + var;
+        const VariantDesc *vdp = args().vars + var;
         const uint32_t n_slots = uni(vdp->n_noise);
 
         // Draw the next 256 noise slots: one Philox block of 4 words per lane.
@@ -813,7 +823,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
             const uint32_t aw = uni((uint32_t)__builtin_amdgcn_readlane((int)(hi ? w3 : w1), (int)L));
             gd += 2u;
             const uint32_t lim = vdp->n_noise - nz_drawn;
-            const uint32_t *tb = P.gaps + vdp->gap_off;
+            const uint32_t *tb = args().gaps + vdp->gap_off;
             // G = #{j < lim : w < tb[j]} (tb is non-increasing).  q^G is
             // about w / 2^32, so G is within a slot or two of
             // x = log2(w / 2^32) / log2(q): with kGapEstimate, lanes 0..3
@@ -908,8 +918,8 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         // so the restarted shot is the one the full list gives.
         // (with a support cap the full list runs: the cap is defined by the
         // supports of the circuit's own gate order)
-        bool full = tracing || !P.speculate || (LEAN ? 0xFFFFFFFFu : P.support_cap) != 0xFFFFFFFFu || vdp->ev_off_full == vdp->ev_off;
-        if ((!LEAN && P.prefix_build)) full = (i & 1u) != 0u || vdp->ev_off_full == vdp->ev_off;
+        bool full = tracing || !args().speculate || (LEAN ? 0xFFFFFFFFu : args().support_cap) != 0xFFFFFFFFu || vdp->ev_off_full == vdp->ev_off;
+        if ((!LEAN && args().prefix_build)) full = (i & 1u) != 0u || vdp->ev_off_full == vdp->ev_off;
         bool pfx_done = false;      // the build wrote every checkpoint of this item's list
         uint32_t ck_next_done = 0;  // checkpoints written
         // the checkpoint whose tile the shot still has to load (null: the
@@ -918,7 +928,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         // Deferred T runs (EVF_DEFER): skipped while defer_ok; `deferred` once
         // one was skipped, and `redo` when an event needed its tile (the
         // attempt then runs again with defer_ok off).
-        bool defer_ok = P.defer != 0u && !tracing && !(!LEAN && P.prefix_build) && (LEAN ? 0xFFFFFFFFu : P.support_cap) == 0xFFFFFFFFu;
+        bool defer_ok = args().defer != 0u && !tracing && !(!LEAN && args().prefix_build) && (LEAN ? 0xFFFFFFFFu : args().support_cap) == 0xFFFFFFFFu;
         // Butterfly pairs run as one pass where an FP32 pass reads and
         // writes device memory (tiles there, or split tiles larger than
         // their LDS part): each entry crosses to the slab once instead of
@@ -929,7 +939,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         // Not when a trace wants the state after each event or a support cap
         // is checked after each T.
         constexpr bool kPairs = TM != TM_LDS && sizeof(R) == 4;
-        const bool pair_ok = kPairs && !tracing && (LEAN ? 0xFFFFFFFFu : P.support_cap) == 0xFFFFFFFFu;
+        const bool pair_ok = kPairs && !tracing && (LEAN ? 0xFFFFFFFFu : args().support_cap) == 0xFFFFFFFFu;
         auto pair_now = [&](uint32_t fl) { return (fl & EVF_PAIR) && pair_ok && (1u << k) > v.lim; };
         bool deferred = false, redo = false;
         // A deferred run applied late: the signs the run saw and the state
@@ -942,7 +952,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         auto put = [&](uint32_t l, uint32_t x) { stash = lane == l ? x : stash; };
         auto get = [&](uint32_t l) { return uni((uint32_t)__builtin_amdgcn_readlane((int)stash, (int)l)); };
         auto get64 = [&](uint32_t l) { return ((uint64_t)get(l + 1u) << 32) | (uint64_t)get(l); };
-        const uint32_t tile_off = kCkptRecOff + ((P.rec_words * 4u + 15u) & ~15u);
+        const uint32_t tile_off = kCkptRecOff + ((args().rec_words * 4u + 15u) & ~15u);
         auto materialize = [&]() {
             const C *pt = reinterpret_cast<const C *>(lazy_slot + tile_off);
             lane_pass(1u << k, lane, [&](uint32_t j) { v[j] = pt[j]; });
@@ -951,7 +961,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         };
         for (;;) {
         const uint32_t *evl = reinterpret_cast<const uint32_t *>(ev + (full ? vdp->ev_off_full : vdp->ev_off));
-        for (uint32_t w = kRecSgpr + lane; w < P.rec_words; w += 64) rec[w] = 0u;
+        for (uint32_t w = kRecSgpr + lane; w < args().rec_words; w += 64) rec[w] = 0u;
         rrv = 0u;
         if (lane == 0) v[0] = mk<C>(1.0, 0.0);
         tile_sync();
@@ -977,13 +987,13 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         // the build launch wrote for this launch.
         const uint32_t ck_o = uni(full ? vdp->ck_off_full : vdp->ck_off);
         const uint32_t ck_c = uni(full ? vdp->ck_cnt_full : vdp->ck_cnt);
-        auto ck_slot = [&](uint32_t t) { return P.prefix + (size_t)t * P.prefix_stride; };
+        auto ck_slot = [&](uint32_t t) { return args().prefix + (size_t)t * args().prefix_stride; };
         // The build: no noise (every slot counts as drawn, none hit); the
         // list's events run up to its last checkpoint, and the state at each
         // checkpoint goes to its slot (the full list's item only, when the
         // variant has one list).
         uint32_t ck_next = 0;
-        if ((!LEAN && P.prefix_build)) {
+        if ((!LEAN && args().prefix_build)) {
             nz_drawn = n_slots;
             if (ck_c == 0u || (!(i & 1u) && vdp->ev_off_full == vdp->ev_off)) {
                 pfx_done = true;  // nothing to write (or the odd item writes these slots)
@@ -996,8 +1006,8 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
             const double nn = tile_norm(v, k, lane);
             lane_pass(1u << k, lane, [&](uint32_t j) { pt[j] = v[j]; });
             uint32_t *pr = reinterpret_cast<uint32_t *>(slot + kCkptRecOff);
-            if (lane < kRecSgpr && lane < P.rec_words) pr[lane] = rrv;
-            for (uint32_t w = kRecSgpr + lane; w < P.rec_words; w += 64u) pr[w] = rec[w];
+            if (lane < kRecSgpr && lane < args().rec_words) pr[lane] = rrv;
+            for (uint32_t w = kRecSgpr + lane; w < args().rec_words; w += 64u) pr[w] = rec[w];
             if (lane == 0) {
                 CkptState *cs = reinterpret_cast<CkptState *>(slot);
                 cs->rD = rD;
@@ -1023,11 +1033,11 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         lazy_slot = nullptr;
         deferred = false;
         replaying = false;
-        if (P.prefix != nullptr && !(!LEAN && P.prefix_build) && !tracing && ck_c != 0u) {
+        if (args().prefix != nullptr && !(!LEAN && args().prefix_build) && !tracing && ck_c != 0u) {
             // checkpoint c's noise count and validity in lane c (one load each)
             uint32_t cev = 0u, cnz = 0xFFFFFFFFu, cok = 0u;
             if (lane < ck_c) {
-                const Checkpoint cp = P.ckpts[ck_o + lane];
+                const Checkpoint cp = args().ckpts[ck_o + lane];
                 cev = cp.ev;
                 cnz = cp.nz;
                 cok = reinterpret_cast<const CkptState *>(ck_slot(ck_o + lane))->valid;
@@ -1057,8 +1067,8 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
                 maxsup = h32(offsetof(CkptState, maxsup));
                 obs = h32(offsetof(CkptState, obs));
                 const uint32_t *pr = reinterpret_cast<const uint32_t *>(slot + kCkptRecOff);
-                if (lane < kRecSgpr && lane < P.rec_words) rrv = pr[lane];
-                for (uint32_t w = kRecSgpr + lane; w < P.rec_words; w += 64u) rec[w] = pr[w];
+                if (lane < kRecSgpr && lane < args().rec_words) rrv = pr[lane];
+                for (uint32_t w = kRecSgpr + lane; w < args().rec_words; w += 64u) rec[w] = pr[w];
                 lazy_slot = slot;
                 e0 = uni((uint32_t)__builtin_amdgcn_readlane((int)cev, (int)best));
                 myc += lane == (uint32_t)C_PREFIX ? 1u : 0u;
@@ -1071,7 +1081,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         uint32_t evx = evl[(uint64_t)(e0 + 1u) * 64u + lane];
         uint32_t e = e0;  // after the loop: the last event run
         // trace steps, or (build) the events up to the last checkpoint
-        const uint32_t dump_lim = ((!LEAN && P.prefix_build) && ck_c) ? uni(P.ckpts[ck_o + ck_c - 1u].ev) + 1u : trace_lim;
+        const uint32_t dump_lim = ((!LEAN && args().prefix_build) && ck_c) ? uni(args().ckpts[ck_o + ck_c - 1u].ev) + 1u : trace_lim;
         for (;; ++e) {
             if (replaying && e == get(10)) {
                 // the deferred run is applied: back to the event that needed
@@ -1086,8 +1096,8 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
             }
             uint32_t evy = evl[(uint64_t)(e + 2u) * 64u + lane];
             if (e - 1u < dump_lim) {  // state after event e-1 (e = 0 wraps past any limit)
-                if ((!LEAN && P.prefix_build)) {
-                    if (e == uni(P.ckpts[ck_o + ck_next].ev)) {
+                if ((!LEAN && args().prefix_build)) {
+                    if (e == uni(args().ckpts[ck_o + ck_next].ev)) {
                         write_ckpt(ck_o + ck_next);
                         ck_next_done = ++ck_next;
                         if (ck_next == ck_c) {
@@ -1096,9 +1106,9 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
                         }
                     }
                 } else {
-                    dump_state(P.trace_meta + (uint64_t)(e - 1u) * KM_COUNT,
-                               P.trace_v + (uint64_t)(e - 1u) * P.tile_entries * 2u, v, lane, P.tile_entries, status,
-                               abort_src, e - 1u, 1u, rD, rS, a, k, nrm2, P.phase_tab, phase8, var, full ? 1u : 0u,
+                    dump_state(args().trace_meta + (uint64_t)(e - 1u) * KM_COUNT,
+                               args().trace_v + (uint64_t)(e - 1u) * args().tile_entries * 2u, v, lane, args().tile_entries, status,
+                               abort_src, e - 1u, 1u, rD, rS, a, k, nrm2, args().phase_tab, phase8, var, full ? 1u : 0u,
                                1.0 / itscale2);
                 }
             }
@@ -1252,7 +1262,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
                 phase8 = (phase8 + EV32(boff)) & 15u;
                 cmax = uni(cmax);
                 maxsup = max(maxsup, cmax);
-                if (cmax > (LEAN ? 0xFFFFFFFFu : P.support_cap)) {  // only the full list enforces a cap
+                if (cmax > (LEAN ? 0xFFFFFFFFu : args().support_cap)) {  // only the full list enforces a cap
                     restart = true;
                     break;
                 }
@@ -1310,7 +1320,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
                     const uint32_t cnt = uni((uint32_t)__popcll(kb));
                     maxsup = max(maxsup, cnt);
                     // lanes n/2 .. n-1 hold the entries with the dropped bit set
-                    if (cnt > (LEAN ? 0xFFFFFFFFu : P.support_cap) || (kb >> (n >> 1)) != 0ull) {
+                    if (cnt > (LEAN ? 0xFFFFFFFFu : args().support_cap) || (kb >> (n >> 1)) != 0ull) {
                         fail = true;
                         fi = i;
                         break;
@@ -1410,7 +1420,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
                 phase8 = (phase8 + ((flags & EVF_TDG) ? 15u : 1u)) & 15u;
                 cnt = uni(cnt);
                 maxsup = max(maxsup, cnt);
-                if (cnt > (LEAN ? 0xFFFFFFFFu : P.support_cap)) {
+                if (cnt > (LEAN ? 0xFFFFFFFFu : args().support_cap)) {
                     // the speculative list visits other intermediate states:
                     // the full list decides where (and whether) the cap is hit
                     if (!full) {
@@ -1724,7 +1734,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
                 // from the coset's entries (0 past the old span).  A coset sits on
                 // the lanes of one iteration, whose reads all come before its
                 // writes, so the update is in place.
-                const DiagInfo *di = P.diag + EV32(boff);
+                const DiagInfo *di = args().diag + EV32(boff);
                 const uint32_t ng = uni(di->ng), r = uni(di->r), knew = uni(di->knew), lead = uni(di->lead);
                 if ((flags & EVF_COND) && !cond_check(flags)) {
                     // a classically controlled gate that does not fire: the
@@ -1803,7 +1813,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
                     k = knew;
                     cnt = uni(cnt);
                     maxsup = max(maxsup, cnt);
-                    if (cnt > (LEAN ? 0xFFFFFFFFu : P.support_cap)) {
+                    if (cnt > (LEAN ? 0xFFFFFFFFu : args().support_cap)) {
                         if (!full) {  // the full list decides where the cap is hit
                             restart = true;
                             break;
@@ -1857,11 +1867,11 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         }
         // a kept shot whose last deferred run was never applied: its final
         // state needs it, so the attempt runs again without deferring
-        if (!LEAN && !restart && deferred && P.keep_n && shot >= P.keep_lo && shot - P.keep_lo < P.keep_n) {
+        if (!LEAN && !restart && deferred && args().keep_n && shot >= args().keep_lo && shot - args().keep_lo < args().keep_n) {
             restart = true;
             redo = true;
         }
-        if (!restart || (!LEAN && P.prefix_build)) break;
+        if (!restart || (!LEAN && args().prefix_build)) break;
         if (redo) {  // the same list again, every T run applied
             redo = false;
             defer_ok = false;
@@ -1871,12 +1881,12 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
             myc += lane == (uint32_t)C_RESTARTS ? 1u : 0u;
         }
         }
-        if ((!LEAN && P.prefix_build)) {
+        if ((!LEAN && args().prefix_build)) {
             // a list that ended (or stopped) before a checkpoint leaves its slot invalid
             if (!pfx_done && lane == 0) {
                 const uint32_t o = full ? vdp->ck_off_full : vdp->ck_off, cnt = full ? vdp->ck_cnt_full : vdp->ck_cnt;
                 for (uint32_t t = ck_next_done; t < cnt; ++t)
-                    reinterpret_cast<CkptState *>(P.prefix + (size_t)(o + t) * P.prefix_stride)->valid = 0u;
+                    reinterpret_cast<CkptState *>(args().prefix + (size_t)(o + t) * args().prefix_stride)->valid = 0u;
             }
             continue;
         }
@@ -1884,7 +1894,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         // ---- shot end: norm check, outputs, kept states, counters ----
         // (a shot that ended on a checkpoint's tile without loading it: the
         // sum stored with it, computed the same way)
-        const bool kept = !LEAN && P.keep_n && shot >= P.keep_lo && shot - P.keep_lo < P.keep_n;
+        const bool kept = !LEAN && args().keep_n && shot >= args().keep_lo && shot - args().keep_lo < args().keep_n;
         if (lazy_slot != nullptr && kept) materialize();
         const double nn = lazy_slot != nullptr ? unid(reinterpret_cast<const CkptState *>(lazy_slot)->tnorm)
                                                : tile_norm(v, k, lane);
@@ -1896,16 +1906,16 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
                                : lane == kRecSgpr + 1u ? abort_src : obs;
             if (out_plane) out_plane[i] = val;
         }
-        if (P.outcomes)
-            for (uint32_t w = kRecSgpr + lane; w < P.rec_words; w += 64u) P.outcomes[(uint64_t)w * P.n_shots + i] = rec[w];
+        if (args().outcomes)
+            for (uint32_t w = kRecSgpr + lane; w < args().rec_words; w += 64u) args().outcomes[(uint64_t)w * args().n_shots + i] = rec[w];
         if (kept) {
-            const uint64_t kk = shot - P.keep_lo;
-            dump_state(P.keep_meta + kk * KM_COUNT, P.keep_v + kk * (uint64_t)P.tile_entries * 2u, v, lane,
-                       P.tile_entries, status, abort_src, term, after, rD, rS, a, k, nrm2, P.phase_tab, phase8, var, full ? 1u : 0u, 1.0 / itscale2);
+            const uint64_t kk = shot - args().keep_lo;
+            dump_state(args().keep_meta + kk * KM_COUNT, args().keep_v + kk * (uint64_t)args().tile_entries * 2u, v, lane,
+                       args().tile_entries, status, abort_src, term, after, rD, rS, a, k, nrm2, args().phase_tab, phase8, var, full ? 1u : 0u, 1.0 / itscale2);
         }
         if (term < trace_lim)
-            dump_state(P.trace_meta + (uint64_t)term * KM_COUNT, P.trace_v + (uint64_t)term * P.tile_entries * 2u, v,
-                       lane, P.tile_entries, status, abort_src, term, after, rD, rS, a, k, nrm2, P.phase_tab, phase8, var, full ? 1u : 0u, 1.0 / itscale2);
+            dump_state(args().trace_meta + (uint64_t)term * KM_COUNT, args().trace_v + (uint64_t)term * args().tile_entries * 2u, v,
+                       lane, args().tile_entries, status, abort_src, term, after, rD, rS, a, k, nrm2, args().phase_tab, phase8, var, full ? 1u : 0u, 1.0 / itscale2);
         const uint32_t bucket = min(15u, 31u - (uint32_t)__clz(maxsup));
         myc += (lane == C_SHOTS) + (lane == C_PASSED + status) +
                (lane == C_LOGICAL && status == ST_PASSED && obs != 0u) + (lane == C_HIST0 + bucket);
