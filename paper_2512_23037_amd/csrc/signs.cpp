@@ -313,34 +313,43 @@ void build_signs(const Program &P, SignProgram &out) {
 
     // ---- how many shots a check ends: hits whose signature has a check, and
     // coins (independent ones halve the shots that go on) ----
-    Vec checks(W);
+    Vec checks(W), pairs(W);
     bool any = false;
-    for (uint32_t i = 0; i < nt; ++i)
+    for (uint32_t i = 0; i < nt; ++i) {
         if (out.tests[i].kind == SGT_CHECK) {
             flip(checks, i);
             any = any || ((out.ref[i >> 5] >> (i & 31u)) & 1u);
+        } else if (tests[i].pair >= 0) {
+            flip(pairs, i);
         }
+    }
     double lam = 0.0;
     for (uint32_t s = 0; s < P.n_noise; ++s) {
         const uint32_t kind = out.slots[s].kind;
         if (kind == NZ_NONE) continue;
         const uint32_t *g = &out.vecs[(size_t)s * kSignVecs * W];
-        auto flips = [&](uint32_t a, uint32_t b) {  // Paulis 1..3 (0: none) on the two qubits
-            for (uint32_t i = 0; i < tw; ++i)
-                if (((a ? g[(a - 1u) * W + i] : 0u) ^ (b ? g[(2u + b) * W + i] : 0u)) & checks[i]) return 1u;
-            return 0u;
+        uint32_t bad = 0, broken = 0, all = 1;
+        auto count = [&](uint32_t a, uint32_t b) {  // Paulis 1..3 (0: none) on the two qubits
+            uint32_t c = 0, p = 0;
+            for (uint32_t i = 0; i < tw; ++i) {
+                const uint32_t v = (a ? g[(a - 1u) * W + i] : 0u) ^ (b ? g[(2u + b) * W + i] : 0u);
+                c |= v & checks[i];
+                p |= v & pairs[i];
+            }
+            bad += c ? 1u : 0u;
+            broken += p ? 1u : 0u;
         };
-        uint32_t bad = 0, all = 1;
         if (kind == NZ_DEP1) {
             all = 3;
-            for (uint32_t a = 1; a < 4u; ++a) bad += flips(a, 0u);
+            for (uint32_t a = 1; a < 4u; ++a) count(a, 0u);
         } else if (kind == NZ_DEP2) {
             all = 15;
-            for (uint32_t i = 1; i < 16u; ++i) bad += flips(i >> 2, i & 3u);
+            for (uint32_t i = 1; i < 16u; ++i) count(i >> 2, i & 3u);
         } else {
-            bad = flips(kind == NZ_ZERR ? 3u : 1u, 0u);
+            count(kind == NZ_ZERR ? 3u : 1u, 0u);
         }
         lam -= std::log1p(-std::min(P.noise_p[s] * bad / all, 1.0 - 1e-12));
+        out.breaks += P.noise_p[s] * broken / all;
     }
     std::vector<Vec> ech;
     for (Vec v : out.coin) {

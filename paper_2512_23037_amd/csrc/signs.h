@@ -30,6 +30,7 @@ struct SignProgram {
     std::vector<SignMeas> meas;
     bool complete = false;                    // the signs decide the whole list
     double ends = 0.0;                        // about the fraction of shots that a check ends by signs
+    double breaks = 0.0;                      // about the T pairs that noise breaks per shot
 };
 
 // Build the sign program of the list P.  `on` stays false when the list has

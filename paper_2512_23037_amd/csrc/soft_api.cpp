@@ -117,6 +117,7 @@ struct soft_ctx {
     SignParams sign_tables = {};              // their places in it
     uint32_t sign_size = 0;                   // their vector size (kSignTestWords)
     uint32_t sign_on = 0;                     // some variant's shots are worth it: bit 0 gaps, bit 1 slots
+    bool sign_few = false;                    // it leaves few shots to the sampler
     unsigned long long *d_counters = nullptr;  // kMaxVariants rows of C_COUNT, then the work cursor
     const unsigned long long *last_counters = nullptr;  // counters of the last run
     double *d_phase = nullptr;                 // cos/sin of k pi/8, k = 0..15
@@ -305,6 +306,10 @@ int compile_variant(soft_ctx *c, Variant &V) {
 // twice.  Drawing by gaps costs little of a shot, a word per slot much of it.
 constexpr double kSignEndsGaps = 0.02, kSignEndsSlots = 0.25;
 
+// Up to one broken T pair a shot, hardly any shot breaks dependent ones or
+// more than four at a time: a complete list leaves some in 10^5 to the sampler.
+constexpr double kSignFewBreaks = 1.0;
+
 // The sign pass's tables: every variant's sign program in the smallest common
 // vector size.
 int prepare_signs(soft_ctx *c) {
@@ -312,6 +317,7 @@ int prepare_signs(soft_ctx *c) {
     std::vector<SignProgram> sp(nv);
     c->sign_on = 0;
     c->sign_size = 0;
+    c->sign_few = true;
     auto fits = [](const SignProgram &S, uint32_t k) {
         return S.need.tests <= kSignTestWords[k] && S.need.out() <= kSignOutWords[k];
     };
@@ -322,6 +328,7 @@ int prepare_signs(soft_ctx *c) {
         build_signs(V.has_fast ? V.fast : V.prog, sp[v]);
         SignProgram &S = sp[v];
         S.on = S.on && fits(S, 3u) && (S.complete || S.ends >= kSignEndsGaps);
+        if (!S.on || !S.complete || S.breaks > kSignFewBreaks) c->sign_few = false;
         if (!S.on) continue;
         while (!fits(S, c->sign_size)) ++c->sign_size;
         c->sign_on |= 1u | ((S.complete || S.ends >= kSignEndsSlots) ? 2u : 0u);
@@ -522,10 +529,23 @@ uint32_t noise_source(const soft_ctx *c) {
     return c->words_dev != nullptr ? NS_EXPLICIT : (c->noise_mode == 1 ? NS_GAPS : NS_SLOTS);
 }
 
+// Whether a launch runs the sign pass: its results stand on T pairs that
+// cancel exactly and on checkpoints and deferred runs being allowed to skip
+// their work, so every option that asks for that work keeps it (and a pruning
+// threshold above rounding changes the states it would skip); kept states,
+// traces, caps, shot lists (`list`) and explicit words need the sampler's own
+// walk.
+constexpr double kSignMaxTau = 1e-6;
+bool use_signs(const soft_ctx *c, bool list) {
+    const uint32_t bit = c->noise_mode == 1 ? 1u : 2u;
+    return (c->sign_on & bit) && !list && !c->keep_n && !c->trace_n && !c->words_dev && !c->support_cap &&
+           c->speculate && c->shared_prefix && c->defer_t && tau_of(c) <= kSignMaxTau;
+}
+
 // The placement asked for (soft_set_tile_memory), or (auto) LDS when one
 // wave's tile fits in a block's LDS, else device memory.  A split needs a
 // span of at least 2^8 entries; below that the tile is small and goes to LDS.
-Shape placement(const soft_ctx *c) {
+Shape placement(const soft_ctx *c, bool list) {
     Shape s;
     if (c->tile_mode == 2) {
         s.gt = TM_MEM;
@@ -536,10 +556,15 @@ Shape placement(const soft_ctx *c) {
         // LDS up to 8 KiB a wave (20 waves a CU, the register-bound
         // occupancy), a split above that while the tile would fit a block's
         // LDS (its LDS part holds twice the waves or more), device memory for
-        // tiles no block holds
+        // tiles no block holds.  When the sign pass leaves few shots, waves in
+        // flight do not count but each one's way through its list does: whole
+        // tiles in LDS up to a block's (27 variants in FP64 343 -> 304 us, a
+        // first call of the span-12 scan 1065 -> 850).
         Shape l;
         if (wave_bytes(c, l) > (uint32_t)c->max_lds_block) {
             s.gt = TM_MEM;
+        } else if (c->sign_few && use_signs(c, list)) {
+            s.gt = TM_LDS;
         } else if (tile_bytes(c) > 8192u && split_possible(c)) {
             s.gt = TM_SPLIT;
             s.lds_log2 = split_log2_default(c);
@@ -551,8 +576,8 @@ Shape placement(const soft_ctx *c) {
 // Resident waves per CU when the tile is not the limit (4 waves per SIMD).
 constexpr uint32_t kMemTileWavesPerCu = 16u;
 
-Shape default_shape(const soft_ctx *c) {
-    Shape s = placement(c);
+Shape default_shape(const soft_ctx *c, bool list) {
+    Shape s = placement(c, list);
     const uint32_t wb = wave_bytes(c, s);
     const uint32_t cap = s.gt == TM_MEM ? kMemTileWavesPerCu : kMaxWavesPerCu;
     const uint32_t waves_cu = std::max<uint32_t>(1u, std::min<uint32_t>(cap, kLdsPerCu / wb));
@@ -575,15 +600,15 @@ TuneKey tune_key(const soft_ctx *c) {
                    c->tile_mode | (int)(c->split_log2 << 8), c->noise_mode);
 }
 
-Shape current_shape(const soft_ctx *c) {
-    Shape s = default_shape(c);
+Shape current_shape(const soft_ctx *c, bool list = false) {
+    Shape s = default_shape(c, list);
     {
         std::lock_guard<std::mutex> lock(g_tune_mu);
         auto it = g_tuned.find(tune_key(c));
         if (it != g_tuned.end()) s = it->second;
     }
     if (c->tile_mode) {  // an explicit placement overrides a tuned one
-        const Shape p = placement(c);
+        const Shape p = placement(c, list);
         if (p.gt != s.gt || (p.gt == TM_SPLIT && c->split_log2)) {
             s.gt = p.gt;
             s.lds_log2 = p.lds_log2;
@@ -629,18 +654,6 @@ void set_wave_layout(const soft_ctx *c, const Shape &s, RunParams &rp) {
     rp.gtile = nullptr;
     rp.tile_mode = s.gt;
     rp.lds_entries = s.gt == TM_SPLIT ? (1u << s.lds_log2) : 0u;
-}
-
-// Whether a launch runs the sign pass: its results stand on T pairs that
-// cancel exactly and on checkpoints and deferred runs being allowed to skip
-// their work, so every option that asks for that work keeps it (and a pruning
-// threshold above rounding changes the states it would skip); kept states,
-// traces, caps, shot lists and explicit words need the sampler's own walk.
-constexpr double kSignMaxTau = 1e-6;
-bool use_signs(const soft_ctx *c, const RunParams &rp) {
-    const uint32_t bit = rp.noise_mode == 1u ? 1u : 2u;
-    return (c->sign_on & bit) && sampler_lean(rp) && c->speculate && c->shared_prefix && c->defer_t &&
-           tau_of(c) <= kSignMaxTau;
 }
 
 // The sign pass's arguments and grid (waves), after rp's outputs, counters and
@@ -715,7 +728,7 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
         pkey = {(uint64_t)(uintptr_t)c->d_prefix.p, (uint64_t)c->bits, tb, rp.support_cap};
     }
     const bool build = pfx && pkey != c->prefix_key;
-    const bool sgn = use_signs(c, rp);
+    const bool sgn = use_signs(c, rp.shot_list != nullptr);
     rp.grab = group_size(c, s, grid, n_shots, sgn);
     SignParams sp;
     uint32_t sgrid = 0;
@@ -1332,7 +1345,7 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
         HIPCHK(c, launch_prefix_build(build_params(rp), c->bits == 64,
                                  dim3((uint32_t)std::min<uint64_t>(grid, (2ull * rp.n_vars + s.wpb - 1) / s.wpb)),
                                  dim3(64u * s.wpb), (size_t)s.wpb * wave_bytes(c, s), stream));
-    const bool sgn = use_signs(c, rp);
+    const bool sgn = use_signs(c, rp.shot_list != nullptr);
     rp.grab = group_size(c, s, grid, n_shots, sgn);
     if (sgn) {
         rp.signs = 1;
@@ -1398,7 +1411,7 @@ int soft_run_list(soft_ctx *c, const uint64_t *shots_dev, uint64_t n_shots, uint
     if (rc) return rc;
     if (c->words_dev) return fail(c, SOFT_EUNSUPPORTED, "explicit words are for soft_run");
     if (n_shots == 0) return SOFT_OK;
-    Shape s = current_shape(c);
+    Shape s = current_shape(c, true);
     if ((rc = check_shape(c, s))) return rc;
     return run_impl(c, 0, n_shots, outcomes, status, abort_op, obs, (hipStream_t)hip_stream, s, shots_dev);
 }
@@ -1577,14 +1590,14 @@ int soft_autotune(soft_ctx *c, uint64_t sample_shots, void *hip_stream) {
     // placement.  Each is run once untimed and twice timed; the faster timing
     // counts, so one noisy launch cannot pick a worse shape than the default.
     std::vector<Shape> cands;
-    cands.push_back(default_shape(c));
+    cands.push_back(default_shape(c, true));
     const uint32_t wpbs[3] = {1, 2, 4};
     const uint32_t grabs[2] = {16, 64};
     // placements: the one asked for; in auto mode LDS (when it fits), device
     // memory, and splits whose LDS part is 1/2, 1/4 or 1/8 of the tile
     std::vector<Shape> places;
     if (c->tile_mode != 0) {
-        places.push_back(placement(c));
+        places.push_back(placement(c, true));
         if (places[0].gt == TM_SPLIT && !c->split_log2)  // other LDS parts of the split
             for (uint32_t d = 1; d <= 3; ++d) {
                 Shape p = places[0];
