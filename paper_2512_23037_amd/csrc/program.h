@@ -372,7 +372,10 @@ enum Status : uint32_t { ST_PASSED = 0, ST_DISCARDED = 1, ST_OVERFLOW = 2, ST_NU
 // What the sign pass writes for a shot that the sampler kernel has to run.
 constexpr uint32_t kStatusPending = 0xFFFFFFFFu;
 
-// Device counters, all 64-bit: one row of C_COUNT per variant.
+// Device counters, all 64-bit: rows of C_COUNT, `shards` (a power of two) per
+// variant.  A wave adds to the row of its number: every wave of a launch adds
+// once, additions to one address follow each other every 16 ns, and 2500 waves
+// on one row took 40 us of an 8-qubit launch of 10^4 shots.
 enum Counter {
     C_SHOTS = 0, C_PASSED, C_DISCARDED, C_OVERFLOW, C_NUMERIC, C_LOGICAL,
     C_ENTRIES_T, C_ENTRIES_M, C_NOISE, C_EVENTS, C_NORMDEV_BITS,
@@ -383,6 +386,8 @@ enum Counter {
     C_CK0 = C_HIST0 + 16,    // shots the sign pass decided, by checkpoints before their first noise hit
     C_COUNT = C_CK0 + kMaxCheckpoints + 1
 };
+
+constexpr uint32_t kCounterRows = 160, kMaxShards = 16;
 
 // Per kept shot (and per traced step): meta words, and separately the dense
 // coefficient tile as double pairs.  KM_VALID holds kStateValid once written.

@@ -27,7 +27,7 @@ struct RunParams {
     uint32_t *status;         // [n_shots]
     uint32_t *abort_op;       // [n_shots] or null
     uint32_t *obs;            // [n_shots] or null
-    unsigned long long *counters;  // [variants][C_COUNT]
+    unsigned long long *counters;  // [variants][shards][C_COUNT]
     unsigned long long *next;      // work-stealing cursors
     unsigned long long *keep_meta; // [keep_n][KM_COUNT] or null
     double *keep_v;                // [keep_n][tile_entries][2] or null
@@ -42,7 +42,8 @@ struct RunParams {
     uint64_t seed, shot0, n_shots, keep_lo;
     uint64_t word_stride;
     uint32_t keep_n, n_vars, rec_words, support_cap;
-    uint32_t trace_n, pad_;
+    uint32_t trace_n;
+    uint32_t shards;          // counter rows per variant (a power of two)
     uint32_t wave_bytes, tile_bytes, tile_entries, grab;
     uint32_t rec_off;         // byte offset of the record in a wave's LDS slot (LDS tiles; 0 when the
                               // record fits in scalar registers and never touches LDS)
@@ -76,6 +77,7 @@ struct SignParams {
     uint64_t seed, shot0, n_shots;
     uint32_t n_vars, rec_words, chunk;
     uint32_t prefix;          // 1: count the shots a checkpoint precedes
+    uint32_t shards, pad;
 };
 
 // The sign pass's vector sizes: a launch uses the smallest that holds its
@@ -95,6 +97,7 @@ constexpr uint32_t kSampleCursor = 0, kSignCursor = kQueueWords, kBuildCursor = 
 constexpr uint32_t kCursorWords = 3 * kQueueWords;
 
 // Zero `n` counters and the work cursors: a kernel, so it can live in a graph.
+constexpr uint32_t kResetBlock = 1024;
 hipError_t launch_reset(unsigned long long *counters, uint32_t n, unsigned long long *next, hipStream_t stream);
 
 // The persistent sampler: grid x block threads, `lds` bytes of dynamic LDS.
@@ -103,7 +106,7 @@ hipError_t launch_sampler(const RunParams &p, bool fp64, dim3 grid, dim3 block, 
 // Host handles of the kernels, for graphs built from explicit kernel nodes:
 // the sampler instantiation for a precision, noise source and tile mode
 // (arguments: ev, nz, tm1, det, words, bm, then the RunParams by value), and
-// the counter reset (arguments: counters, n, next; one block of 256 threads).
+// the counter reset (arguments: counters, n, next; one block of kResetBlock threads).
 const void *sampler_kernel(bool fp64, uint32_t noise_source, uint32_t tile_mode, bool lean);
 // Whether a launch with these parameters runs the lean kernel (no kept
 // states, no trace, no support cap, no shot list, no explicit words; see

@@ -611,15 +611,16 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
     // The supports of the shots that the sign pass decided: those the
     // checkpoint before their first hit holds (C_CK0 counts them by
     // checkpoint), as for a shot that starts there and defers what follows.
-    if (LEAN && args().signs && gwave == 0) {
-        for (uint32_t x = 0; x < args().n_vars; ++x) {
+    if (LEAN && args().signs) {
+        const uint32_t shards = args().shards, rows = args().n_vars * shards;
+        for (uint32_t x = uni((uint32_t)gwave); x < rows; x += gridDim.x * (blockDim.x >> 6)) {
             if (lane > kMaxCheckpoints) continue;
             unsigned long long *row = args().counters + (size_t)x * C_COUNT;
             const unsigned long long c = row[C_CK0 + lane];
             uint32_t sup = 1u;
             if (lane && args().prefix && c) {
                 const CkptState *cs = reinterpret_cast<const CkptState *>(
-                    args().prefix + (size_t)(args().vars[x].ck_off + lane - 1u) * args().prefix_stride);
+                    args().prefix + (size_t)(args().vars[x / shards].ck_off + lane - 1u) * args().prefix_stride);
                 if (cs->valid == 1u) sup = max(1u, cs->maxsup);
             }
             if (c) atomicAdd(row + C_HIST0 + min(15u, 31u - (uint32_t)__clz(sup)), c);
@@ -641,7 +642,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
             maxdev = 0.0;
             return;
         }
-        unsigned long long *row = args().counters + (size_t)var * C_COUNT;
+        unsigned long long *row = args().counters + ((size_t)var * args().shards + (uni((uint32_t)gwave) & (args().shards - 1u))) * C_COUNT;
         if (lane < (uint32_t)C_COUNT && lane != (uint32_t)C_NORMDEV_BITS && myc) atomicAdd(row + lane, (unsigned long long)myc);
         if (lane == (uint32_t)C_NORMDEV_BITS) atomicMax(row + lane, (unsigned long long)__double_as_longlong(maxdev));
         myc = 0;
@@ -2015,7 +2016,7 @@ bool sampler_lean(const RunParams &p) {
 }
 
 hipError_t launch_reset(unsigned long long *counters, uint32_t n, unsigned long long *next, hipStream_t stream) {
-    hipLaunchKernelGGL(k_reset, dim3(1), dim3(256), 0, stream, counters, n, next);
+    hipLaunchKernelGGL(k_reset, dim3(1), dim3(kResetBlock), 0, stream, counters, n, next);
     return hipGetLastError();
 }
 

@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
     uint64_t words = 0;  // of this lane
     auto desc = [&]() { return (ConstDesc *)args()->desc + var; };
     auto flush = [&]() {
-        unsigned long long *row = args()->counters + (size_t)var * C_COUNT;
+        unsigned long long *row = args()->counters + ((size_t)var * args()->shards + (blockIdx.x & (args()->shards - 1u))) * C_COUNT;
         for (int o = 32; o >= 1; o >>= 1) words += __shfl_xor((unsigned long long)words, o, 64);
         const uint64_t v = lane == C_SHOTS ? n_pass + n_disc : lane == C_PASSED ? n_pass : lane == C_DISCARDED ? n_disc
                          : lane == C_LOGICAL ? n_logical : lane == C_NOISE ? words : lane == C_PREFIX ? n_prefix

@@ -45,7 +45,8 @@ struct Variant {
 };
 
 // counter rows, then the work cursors (on a cache line's start)
-constexpr size_t kCursorOff = ((size_t)kMaxVariants * C_COUNT + kCursorStride - 1) / kCursorStride * kCursorStride;
+static_assert(kMaxVariants <= kCounterRows, "a row per variant");
+constexpr size_t kCursorOff = ((size_t)kCounterRows * C_COUNT + kCursorStride - 1) / kCursorStride * kCursorStride;
 constexpr size_t kCounterWords = kCursorOff + kCursorWords;
 static_assert(kCounterWords * sizeof(unsigned long long) <= kScratchCounterBytes, "scratch counter area");
 
@@ -118,8 +119,9 @@ struct soft_ctx {
     uint32_t sign_size = 0;                   // their vector size (kSignTestWords)
     uint32_t sign_on = 0;                     // some variant's shots are worth it: bit 0 gaps, bit 1 slots
     bool sign_few = false;                    // it leaves few shots to the sampler
-    unsigned long long *d_counters = nullptr;  // kMaxVariants rows of C_COUNT, then the work cursor
+    unsigned long long *d_counters = nullptr;  // kCounterRows rows of C_COUNT, then the work cursors
     const unsigned long long *last_counters = nullptr;  // counters of the last run
+    uint32_t last_shards = 1;                           // and their rows per variant
     double *d_phase = nullptr;                 // cos/sin of k pi/8, k = 0..15
     unsigned char *scratch = nullptr;          // this device's static scratch (soft_run_noalloc)
 
@@ -668,6 +670,7 @@ uint32_t sign_params(const soft_ctx *c, const RunParams &rp, SignParams &sp) {
     sp.abort_op = rp.abort_op;
     sp.obs = rp.obs;
     sp.counters = rp.counters;
+    sp.shards = rp.shards;
     sp.next = rp.next + kSignCursor;
     sp.seed = rp.seed;
     sp.shot0 = rp.shot0;
@@ -791,14 +794,14 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     } else {
         drop_slot(c, gs);
         gs.r_counters = rp.counters;
-        gs.r_n = rp.n_vars * (uint32_t)C_COUNT;
+        gs.r_n = rp.n_vars * rp.shards * (uint32_t)C_COUNT;
         gs.r_next = rp.next;
         void *rargs[3] = {(void *)&gs.r_counters, (void *)&gs.r_n, (void *)&gs.r_next};
         hipKernelNodeParams rk;
         std::memset(&rk, 0, sizeof(rk));
         rk.func = const_cast<void *>(reset_kernel());
         rk.gridDim = dim3(1);
-        rk.blockDim = dim3(256);
+        rk.blockDim = dim3(kResetBlock);
         rk.kernelParams = rargs;
         hipGraphNode_t rnode = nullptr;
         hipError_t e = hipGraphCreate(&gs.graph, 0);
@@ -834,6 +837,13 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     return SOFT_OK;
 }
 
+// Counter rows per variant.
+uint32_t shards(const soft_ctx *c) {
+    uint32_t s = kMaxShards;
+    while (s * c->vars.size() > kCounterRows) s /= 2u;
+    return s;
+}
+
 int make_params(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes, uint32_t *status, uint32_t *abort_op,
                 uint32_t *obs, RunParams &rp) {
     std::memset(&rp, 0, sizeof(rp));
@@ -859,6 +869,7 @@ int make_params(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcome
     rp.obs = obs;
     rp.counters = c->d_counters;
     rp.next = c->d_counters + kCursorOff;
+    rp.shards = shards(c);
     rp.seed = c->seed;
     rp.shot0 = shot0;
     rp.n_shots = n_shots;
@@ -911,6 +922,7 @@ int run_impl(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes, 
     if ((rc = launch(c, rp, s, n_shots, stream))) return rc;
     c->ran = true;
     c->last_counters = c->d_counters;
+    c->last_shards = rp.shards;
     c->last_stream = stream;
     c->last_shot0 = shot0;
     c->last_n = n_shots;
@@ -1340,7 +1352,7 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
         rp.gtile = c->scratch + kScratchCounterBytes + kScratchPrefixBytes;
     }
     const hipStream_t stream = (hipStream_t)hip_stream;
-    HIPCHK(c, launch_reset(rp.counters, rp.n_vars * (uint32_t)C_COUNT, rp.next, stream));
+    HIPCHK(c, launch_reset(rp.counters, rp.n_vars * rp.shards * (uint32_t)C_COUNT, rp.next, stream));
     if (pfx)
         HIPCHK(c, launch_prefix_build(build_params(rp), c->bits == 64,
                                  dim3((uint32_t)std::min<uint64_t>(grid, (2ull * rp.n_vars + s.wpb - 1) / s.wpb)),
@@ -1357,6 +1369,7 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
                              (size_t)s.wpb * wave_bytes(c, s), stream));
     c->ran = true;
     c->last_counters = rp.counters;
+    c->last_shards = rp.shards;
     c->last_stream = stream;
     c->last_shot0 = shot0;
     c->last_n = n_shots;
@@ -1370,12 +1383,14 @@ int read_rows(soft_ctx *c, uint32_t v0, uint32_t v1, soft_counters *out) {
     if (!c->ran) return fail(c, SOFT_ESTATE, "no run yet");
     HIPCHK(c, hipSetDevice(c->device));
     HIPCHK(c, hipStreamSynchronize(c->last_stream));
-    std::vector<unsigned long long> h((size_t)(v1 - v0) * C_COUNT);
-    HIPCHK(c, hipMemcpy(h.data(), c->last_counters + (size_t)v0 * C_COUNT, h.size() * sizeof(unsigned long long),
+    // (the variants are the last run's: a load ends that run's counters)
+    const uint32_t k = c->last_shards;
+    std::vector<unsigned long long> h((size_t)(v1 - v0) * k * C_COUNT);
+    HIPCHK(c, hipMemcpy(h.data(), c->last_counters + (size_t)v0 * k * C_COUNT, h.size() * sizeof(unsigned long long),
                         hipMemcpyDeviceToHost));
     std::memset(out, 0, sizeof(*out));
     double dev = 0.0;
-    for (uint32_t v = 0; v < v1 - v0; ++v) {
+    for (uint32_t v = 0; v < (v1 - v0) * k; ++v) {
         const unsigned long long *r = h.data() + (size_t)v * C_COUNT;
         out->shots += r[C_SHOTS];
         out->passed += r[C_PASSED];
