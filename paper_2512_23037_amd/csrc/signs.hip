@@ -25,10 +25,18 @@ namespace {
 
 __device__ __forceinline__ uint32_t first32(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 
-// floor(mul w / (d1 + 1)) for mul = 3 or 15 and w <= d1
+// v of the lane N further on in its row of 16 lanes (all lanes active)
+template <int N> __device__ __forceinline__ uint32_t ror16(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + N, 0xF, 0xF, true);
+}
+
+// floor(mul w / (d1 + 1)) for mul = 3 or 15 and w <= d1: a hit's Pauli code.
+// The quotient in single precision is off by less than 2^-17; 2^-10 below it,
+// its floor is the result or one less, which an exact product tells.
 __device__ __forceinline__ uint32_t part(uint32_t mul, uint32_t w, uint32_t d1) {
-    if (d1 == 0xFFFFFFFFu) return __umulhi(mul, w);
-    return quot16((uint64_t)mul * w, (uint64_t)d1 + 1ull);
+    const float f = (float)w * (float)mul * __builtin_amdgcn_rcpf((float)d1 + 1.0f);
+    const uint32_t q = (uint32_t)fmaxf(f - 0.0009765625f, 0.0f) + 1u;
+    return (uint64_t)q * d1 + q <= (uint64_t)mul * w ? q : q - 1u;
 }
 
 // Lanes that run one shot together.  With gap sampling a shot draws a few
@@ -46,6 +54,10 @@ constexpr uint32_t kLeft = 0xFFFFFFFFu;
 // Idle lanes take new shots once this many wait: a start costs about as much
 // as a step of one-lane shots, whether one lane or all take it.
 constexpr uint32_t kRefill = 32;
+
+// One-lane shots stopped at a broken pair wait until this many do: settling
+// takes longer than a step, however few lanes take part.
+constexpr uint32_t kSettle = 12;
 
 // The launch's arguments, read again where they are used: everything outside
 // the step is rare, and kept in scalar registers across it its pointers
@@ -66,6 +78,7 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
     static_assert(W % 4 == 0, "vectors are read four words at a time");
     __shared__ uint32_t hist[kMaxCheckpoints + 1];
     __shared__ uint32_t stops[32 * TW + 1];  // SignTest::stop of the variant's rows
+    __shared__ uint64_t pair_rows[TW / 2 + 1];  // and which of them are SGT_PAIR
     const uint32_t lane = threadIdx.x, sub = lane % GL;
     const uint32_t key0 = (uint32_t)P0.seed, key1 = (uint32_t)(P0.seed >> 32);
     if (lane <= kMaxCheckpoints) hist[lane] = 0u;
@@ -142,29 +155,58 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
         limit = stops[t];
         if (gens != 0u && t >= mtest) limit = mstop;
     };
-    // the signature of a hit at slot s, its Pauli from the word w <= d1, into v
-    auto hit = [&](uint32_t (&v)[W], uint32_t s, uint32_t kind, uint32_t w, uint32_t d1) {
-        uint32_t a = 1u, b = 0u;
-        if (kind == NZ_DEP1) {
-            a = part(3u, w, d1) + 1u;
-        } else if (kind == NZ_DEP2) {
-            const uint32_t code = part(15u, w, d1) + 1u;
-            a = code >> 2;
-            b = code & 3u;
-        } else if (kind == NZ_ZERR) {
-            a = 3u;
-        }
+    // The vectors whose sum is the signature of a hit at slot s, its Pauli from
+    // the word w <= d1 (NZ_NONE: the zero vector twice).
+    auto codes = [&](uint32_t s, uint32_t kind, uint32_t w, uint32_t d1, uint32_t &u, uint32_t &v) {
+        const uint32_t code = part(kind == NZ_DEP2 ? 15u : 3u, w, d1) + 1u;
+        const uint32_t a = kind == NZ_DEP2 ? code >> 2 : kind == NZ_DEP1 ? code : kind == NZ_ZERR ? 3u : kind == NZ_NONE ? 0u : 1u;
+        const uint32_t b = kind == NZ_DEP2 ? code & 3u : 0u;
         const uint32_t v0 = kSignVecs * s - 1u;
-        const int32_t va = (int32_t)(a ? v0 + a : zero_vec), vb = (int32_t)(b ? v0 + 3u + b : zero_vec);
-        const uint4 *pa = vecs + (int64_t)va * Q, *pb = vecs + (int64_t)vb * Q;
+        u = a ? v0 + a : zero_vec;
+        v = b ? v0 + 3u + b : zero_vec;
+    };
+    auto sum_of = [&](uint32_t (&d)[W], uint32_t u, uint32_t v) {
+        const uint4 *pa = vecs + (int64_t)(int32_t)u * Q, *pb = vecs + (int64_t)(int32_t)v * Q;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const uint4 ua = pa[q], ub = pb[q];
-            v[4 * q] ^= ua.x ^ ub.x;
-            v[4 * q + 1] ^= ua.y ^ ub.y;
-            v[4 * q + 2] ^= ua.z ^ ub.z;
-            v[4 * q + 3] ^= ua.w ^ ub.w;
+            d[4 * q] = ua.x ^ ub.x;
+            d[4 * q + 1] = ua.y ^ ub.y;
+            d[4 * q + 2] = ua.z ^ ub.z;
+            d[4 * q + 3] = ua.w ^ ub.w;
         }
+    };
+    // GAPS: the gaps of two words: a gap is its table's #{j < lim : w < tb[j]}
+    // (or more, past lim).  An estimate from the word's logarithm puts four
+    // entries around it, which decide it unless they do not bracket it (then a
+    // binary search).
+    auto gaps_of = [&](uint32_t wa, uint32_t wb, uint32_t lim, uint32_t &ga, uint32_t &gb) {
+        const uint32_t ws[2] = {wa, wb};
+        uint32_t b[2], t[2][4], g[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const float est = fminf(fmaxf((__log2f((float)ws[k] + 0.5f) - 32.0f) * l2q, 0.0f), (float)lim);
+            b[k] = max((uint32_t)est, 2u) - 2u;
+            __builtin_memcpy(t[k], draws + b[k], 16);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            uint32_t n = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) n += ws[k] < t[k][j] ? 1u : 0u;
+            g[k] = b[k] + n;
+            if ((n == 4u && b[k] + 4u < lim) || (n == 0u && b[k] != 0u)) {
+                uint32_t lo = 0, hi = lim;  // ws[k] < draws[j] for j < lo, not for j >= hi (or past the slots)
+                while (lo < hi) {
+                    const uint32_t h = (lo + hi) >> 1;
+                    if (ws[k] < draws[h]) lo = h + 1u;
+                    else hi = h;
+                }
+                g[k] = lo;
+            }
+        }
+        ga = g[0];
+        gb = g[1];
     };
 
     // the index shift of a set of pending pairs
@@ -270,17 +312,20 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
 
     for (;;) {
         // ---- stopped shots are settled and end, idle lanes take new ones ----
-        const uint64_t busy = __ballot(act && !stop), stopped = __ballot(stop);
-        const uint32_t waiting = 64u - (uint32_t)__builtin_popcountll(dry ? busy | ~stopped : busy);
+        const uint64_t busy = __ballot(act && !stop);
+        const uint32_t waiting = 64u - (uint32_t)__builtin_popcountll(dry ? busy | __ballot(!stop) : busy);
         if (waiting >= kRefill || busy == 0ull) {
-            bool fin = false;
-            if (stop) {
+            const bool open = stop && (!GAPS || (gens != 0u && row >= mtest) || ((pair_rows[row >> 6] >> (row & 63u)) & 1u));
+            const bool do_settle = !GAPS || (uint32_t)__builtin_popcountll(__ballot(open)) >= kSettle || busy == 0ull;
+            bool fin = stop && !open;
+            if (open && do_settle) {
                 bool on = settle();
                 while (on && (GAPS ? next_s : pos) >= limit) on = settle();
                 fin = !on;
                 stop = false;
                 held = on;
             }
+            if (fin) stop = false;
             bool pass = false, disc = false, logical = false;
             if (fin) {
                 ConstParams *A = args();
@@ -346,7 +391,13 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
                     vecs = A->vecs + (size_t)D->vec_off * Q;
                     zero_vec = 0u - D->vec_off;
                     if (D->on)
-                        for (uint32_t t = lane; t <= n_tests; t += 64u) stops[t] = A->tests[D->test_off + t].stop;
+                        for (uint32_t t0 = 0; t0 <= n_tests; t0 += 64u) {
+                            const uint32_t t = min(t0 + lane, n_tests);
+                            const SignTest T = A->tests[D->test_off + t];
+                            stops[t] = T.stop;
+                            const uint64_t m = __ballot(T.kind == SGT_PAIR);
+                            if (lane == 0u) pair_rows[t0 >> 6] = m;
+                        }
                     __syncthreads();  // (one wave: its LDS writes are done)
                     ready = true;
                 }
@@ -402,51 +453,50 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
             if (GAPS) philox10<true>(pos >> 2, s_lo, s_hi, 2u, key0, key1, w0, w1, w2, w3);
             else stream0.block((pos >> 2) + sub, 0u, key0, key1, w0, w1, w2, w3);
             if (GAPS) {
-                // Two candidates a block (gap word, acceptance word).  The gap
-                // is the table's #{j : w < tb[j]}; its estimate from the
-                // word's logarithm puts four entries around it, which decide
-                // it unless they do not bracket it (then a binary search).  A
-                // candidate that a settled shot held back goes first.
-#pragma unroll 1
-                for (uint32_t half = 0; half < 2u; ++half) {
-                    uint32_t s = next_s, aw = next_w;
-                    if (stop) continue;
-                    if (!held) {
-                        if ((pos & 2u) != 2u * half) continue;
-                        const uint32_t w = half ? w2 : w0;
-                        aw = half ? w3 : w1;
-                        pos += 2u;
-                        const uint32_t lim = n_noise - drawn;
-                        const float est = fminf(fmaxf((__log2f((float)w + 0.5f) - 32.0f) * l2q, 0.0f), (float)lim);
-                        const uint32_t b = max((uint32_t)est, 2u) - 2u;
-                        uint32_t t[4];
-                        __builtin_memcpy(t, draws + b, 16);
-                        const uint32_t n = (w < t[0] ? 1u : 0u) + (w < t[1] ? 1u : 0u) + (w < t[2] ? 1u : 0u) + (w < t[3] ? 1u : 0u);
-                        uint32_t G = b + n;
-                        if (n == 4u || (n == 0u && b != 0u)) {
-                            uint32_t lo = 0, hi = lim;  // w < draws[j] for j < lo, not for j >= hi (or past the slots)
-                            while (lo < hi) {
-                                const uint32_t h = (lo + hi) >> 1;
-                                if (w < draws[h]) lo = h + 1u;
-                                else hi = h;
-                            }
-                            G = lo;
-                        }
-                        s = drawn + min(G, lim);
-                    }
-                    if (s >= limit) {
-                        stop = true;
-                        next_s = s;
-                        next_w = aw;
-                        continue;
-                    }
+                // Two candidates a block (gap word, acceptance word); one that a
+                // settled shot held back goes first.  Both are looked up before
+                // the first is taken: the step waits for three reads in a row
+                // (gap, slot, signatures), not six.
+                const uint32_t lim = n_noise - drawn;
+                uint32_t g1, g2;
+                gaps_of(w0, w2, lim, g1, g2);
+                const uint32_t s1 = held ? next_s : drawn + min(g1, lim), a1 = held ? next_w : w1;
+                const bool two = !held || (pos & 2u);
+                if (!held) pos += 2u;
+                if (s1 >= limit) {
+                    stop = true;
+                    next_s = s1;
+                    next_w = a1;
+                } else {
                     held = false;
-                    drawn = s + 1u;
-                    const SignSlot sl = slots[s];
-                    if (aw <= sl.acc1 && sl.kind != NZ_NONE) {
-                        hit(x, s, sl.kind, aw, sl.acc1);
-                        ck = min(ck, sl.ckpt);
-                        find_first();
+                    const uint32_t s2 = min(s1 + 1u + g2, n_noise), t2 = min(s2, n_noise - 1u);
+                    const SignSlot sl1 = slots[s1], sl2 = slots[t2];
+                    const bool hit1 = a1 <= sl1.acc1 && sl1.kind != NZ_NONE;
+                    const bool hit2 = two && w3 <= sl2.acc1 && sl2.kind != NZ_NONE;
+                    uint32_t u1, v1, u2, v2;
+                    codes(s1, hit1 ? sl1.kind : (uint32_t)NZ_NONE, a1, sl1.acc1, u1, v1);
+                    codes(t2, hit2 ? sl2.kind : (uint32_t)NZ_NONE, w3, sl2.acc1, u2, v2);
+                    uint32_t d1[W], d2[W];
+                    sum_of(d1, u1, v1);
+                    sum_of(d2, u2, v2);
+#pragma unroll
+                    for (int w = 0; w < W; ++w) x[w] ^= d1[w];
+                    if (hit1) ck = min(ck, sl1.ckpt);
+                    drawn = s1 + 1u;
+                    find_first();
+                    if (two) {
+                        pos += 2u;
+                        if (s2 >= limit) {
+                            stop = true;
+                            next_s = s2;
+                            next_w = w3;
+                        } else {
+#pragma unroll
+                            for (int w = 0; w < W; ++w) x[w] ^= d2[w];
+                            if (hit2) ck = min(ck, sl2.ckpt);
+                            drawn = s2 + 1u;
+                            find_first();
+                        }
                     }
                 }
             } else {
@@ -469,16 +519,26 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
                     const SignSlot sl = slots[s];
                     const uint32_t w = j == 0u ? w0 : j == 1u ? w1 : j == 2u ? w2 : w3;
                     if (sl.kind != NZ_NONE) {
-                        hit(d, s, sl.kind, w, sl.thr1);
+                        uint32_t h[W], u, v;
+                        codes(s, sl.kind, w, sl.thr1, u, v);
+                        sum_of(h, u, v);
+#pragma unroll
+                        for (int k = 0; k < W; ++k) d[k] ^= h[k];
                         if (s < limit) dck = min(dck, sl.ckpt);
                     }
                 }
+                // the group's 16 lanes are a DPP row: rotations by 8, 4, 2, 1
 #pragma unroll
-                for (uint32_t o = GL / 2u; o >= 1u; o >>= 1) {
-#pragma unroll
-                    for (int w = 0; w < W; ++w) d[w] ^= (uint32_t)__shfl_xor((int)d[w], (int)o, 64);
-                    dck = min(dck, (uint32_t)__shfl_xor((int)dck, (int)o, 64));
+                for (int w = 0; w < W; ++w) {
+                    d[w] ^= ror16<8>(d[w]);
+                    d[w] ^= ror16<4>(d[w]);
+                    d[w] ^= ror16<2>(d[w]);
+                    d[w] ^= ror16<1>(d[w]);
                 }
+                dck = min(dck, ror16<8>(dck));
+                dck = min(dck, ror16<4>(dck));
+                dck = min(dck, ror16<2>(dck));
+                dck = min(dck, ror16<1>(dck));
 #pragma unroll
                 for (int w = 0; w < W; ++w) x[w] ^= d[w];
                 ck = min(ck, dck);

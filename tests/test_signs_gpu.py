@@ -79,6 +79,19 @@ def test_vector_sizes(n_rounds, mode):
 
 
 @pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("p", [1e-6, 0.02, 0.3, 0.75])
+def test_rare_and_dense_hits(p, mode):
+    # gaps past the last slot and of no slot at all, several hits in a step of
+    # one shot, and kinds whose rates differ (candidates that are not accepted)
+    def build():
+        ctx = make_ctx(rounds(40), {k: p / (1 + i % 3) for i, k in enumerate(NOISE)}, seed=23)
+        ctx.set_noise_mode(mode)
+        return ctx
+
+    both(build, 9, 5000)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
 def test_variants_meet_inside_a_chunk(mode):
     # a circuit without checks before its first random read of coefficients
     # (left to the sampler) between two that the signs decide
