@@ -25,11 +25,6 @@ namespace {
 
 __device__ __forceinline__ uint32_t first32(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 
-// v of the lane N further on in its row of 16 lanes (all lanes active)
-template <int N> __device__ __forceinline__ uint32_t ror16(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + N, 0xF, 0xF, true);
-}
-
 // floor(mul w / (d1 + 1)) for mul = 3 or 15 and w <= d1: a hit's Pauli code.
 // The quotient in single precision is off by less than 2^-17; 2^-10 below it,
 // its floor is the result or one less, which an exact product tells.
@@ -52,8 +47,13 @@ constexpr int kSignWaves(int tests) { return tests <= 4 ? 5 : tests <= 8 ? 4 : 3
 constexpr uint32_t kLeft = 0xFFFFFFFFu;
 
 // Idle lanes take new shots once this many wait: a start costs about as much
-// as a step of one-lane shots, whether one lane or all take it.
-constexpr uint32_t kRefill = 32;
+// as a step of one-lane shots, whether one lane or all take it.  With a word
+// per slot a step costs less than a start and a shot of n slots takes n / 64 of
+// them: long shots fill one group at a time (2800 slots: 937 us, 958 by twos),
+// short ones three (524 slots: 559 us, 581 by twos, 678 by ones).
+template <bool GAPS> __device__ __forceinline__ uint32_t refill_at(uint32_t n_noise) {
+    return GAPS ? 32u : n_noise >= 1024u ? 16u : 48u;
+}
 
 // One-lane shots stopped at a broken pair wait until this many do: settling
 // takes longer than a step, however few lanes take part.
@@ -87,6 +87,7 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
     // shots' counts.
     uint32_t var = 0xFFFFFFFFu, n_noise = 0, n_tests = 0;
     float l2q = 0.0f;
+    uint32_t refill = 1;
     const uint32_t *draws = nullptr;   // its gap table, or its thresholds
     const SignSlot *slots = nullptr;
     const uint4 *vecs = nullptr;       // its first slot's signatures
@@ -314,7 +315,7 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
         // ---- stopped shots are settled and end, idle lanes take new ones ----
         const uint64_t busy = __ballot(act && !stop);
         const uint32_t waiting = 64u - (uint32_t)__builtin_popcountll(dry ? busy | __ballot(!stop) : busy);
-        if (waiting >= kRefill || busy == 0ull) {
+        if (waiting >= refill || busy == 0ull) {
             const bool open = stop && (!GAPS || (gens != 0u && row >= mtest) || ((pair_rows[row >> 6] >> (row & 63u)) & 1u));
             const bool do_settle = !GAPS || (uint32_t)__builtin_popcountll(__ballot(open)) >= kSettle || busy == 0ull;
             bool fin = stop && !open;
@@ -385,6 +386,7 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
                     ConstDesc *D = desc();
                     n_noise = V[var].n_noise;
                     n_tests = D->n_tests;
+                    refill = refill_at<GAPS>(n_noise);
                     l2q = V[var].gap_l2q;
                     draws = GAPS ? A->gaps + V[var].gap_off : A->tm1 + V[var].tm1_off;
                     slots = A->slots + D->slot_off;
@@ -508,40 +510,27 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
         }
         if (!GAPS) {
             if (__ballot(any) != 0ull) {
-                uint32_t d[W], dck = 0xFFFFFFFFu;  // what this lane's hits change
+                // All lanes of a group take the group's hits, one after the
+                // other (there is rarely a second): x needs no reduction.
                 uint32_t m = any ? (w0 <= th.x ? 1u : 0u) | (w1 <= th.y ? 2u : 0u) | (w2 <= th.z ? 4u : 0u) | (w3 <= th.w ? 8u : 0u) : 0u;
-#pragma unroll
-                for (int w = 0; w < W; ++w) d[w] = 0u;
-                while (m) {
-                    const uint32_t j = (uint32_t)__builtin_ctz(m), s = pos + 4u * sub + j;
-                    m &= m - 1u;
-                    if (s >= n_noise) break;
-                    const SignSlot sl = slots[s];
-                    const uint32_t w = j == 0u ? w0 : j == 1u ? w1 : j == 2u ? w2 : w3;
-                    if (sl.kind != NZ_NONE) {
-                        uint32_t h[W], u, v;
+                for (;;) {
+                    const uint64_t hits = __ballot(m != 0u);
+                    if (hits == 0ull) break;
+                    const uint32_t group = (uint32_t)(hits >> (lane - sub)) & ((1u << GL) - 1u);
+                    const uint32_t src = lane - sub + (uint32_t)__builtin_ctz(group | 0x10000u) % GL;
+                    const uint32_t j = (uint32_t)__builtin_ctz(m | 8u);
+                    const uint32_t s = (uint32_t)__shfl((int)(pos + 4u * sub + j), (int)src, 64);
+                    const uint32_t w = (uint32_t)__shfl((int)(j == 0u ? w0 : j == 1u ? w1 : j == 2u ? w2 : w3), (int)src, 64);
+                    if (lane == src) m &= m - 1u;
+                    if (group != 0u && s < n_noise) {
+                        const SignSlot sl = slots[s];
+                        uint32_t u, v;
                         codes(s, sl.kind, w, sl.thr1, u, v);
-                        sum_of(h, u, v);
-#pragma unroll
-                        for (int k = 0; k < W; ++k) d[k] ^= h[k];
-                        if (s < limit) dck = min(dck, sl.ckpt);
+                        add_to(x, vecs + (int64_t)(int32_t)u * Q);
+                        add_to(x, vecs + (int64_t)(int32_t)v * Q);
+                        if (sl.kind != NZ_NONE && s < limit) ck = min(ck, sl.ckpt);
                     }
                 }
-                // the group's 16 lanes are a DPP row: rotations by 8, 4, 2, 1
-#pragma unroll
-                for (int w = 0; w < W; ++w) {
-                    d[w] ^= ror16<8>(d[w]);
-                    d[w] ^= ror16<4>(d[w]);
-                    d[w] ^= ror16<2>(d[w]);
-                    d[w] ^= ror16<1>(d[w]);
-                }
-                dck = min(dck, ror16<8>(dck));
-                dck = min(dck, ror16<4>(dck));
-                dck = min(dck, ror16<2>(dck));
-                dck = min(dck, ror16<1>(dck));
-#pragma unroll
-                for (int w = 0; w < W; ++w) x[w] ^= d[w];
-                ck = min(ck, dck);
                 if (run) find_first();
             }
             if (run) {
