@@ -1924,14 +1924,19 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
     if (var_ok) flush_counters();
 }
 
-// An FP32 tile of a 2^10 span takes 8 KiB of LDS, so LDS holds 5 waves per
-// SIMD; the register budget is set to match.  What no longer fits in
-// registers is what lives across a whole shot (group outputs, shot
-// constants), never the event loop's working set.  FP64 asks for 5 waves per
-// SIMD as well (96 VGPRs, more spilled): left to itself the compiler takes
-// 154 VGPRs and 3 waves.  On the 42-qubit workload 4 waves (128 VGPRs) were
-// 15% faster than 3, and once the lean kernels had freed registers 5 waves
-// were 2.4% faster than 4 (141.3 against 137.9 M shots/s).
+// Waves per SIMD that the registers are set to.  An FP32 tile of a 2^10 span
+// takes 8 KiB of LDS, so LDS holds 5; what no longer fits in 96 VGPRs is what
+// lives across a whole shot (group outputs, shot constants), never the event
+// loop's working set.  FP64 spills 58 of them at 5 waves and a wave's events
+// wait for them one after the other: 4 waves (128 VGPRs) take 67 us instead of
+// 74 on 10^4 8-qubit shots, 64 instead of 68 on 65537 of 42 qubits, and with
+// split tiles and a word per slot 7.8 ms instead of 8.3 (42 qubits, whole
+// lists).  They lose 2 to 3% with tiles in memory and with split tiles and
+// gaps, which stay at 5.  The full kernels (traces, kept states, lists) have
+// more to spill either way and measure the same.
+template <uint32_t NS, uint32_t TM, bool LEAN>
+constexpr int kWaves64 = LEAN && (TM == TM_LDS || (TM == TM_SPLIT && NS == NS_SLOTS)) ? 4 : 5;
+
 template <uint32_t NS, uint32_t TM, bool LEAN>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8)))
 k_sample_f32(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz, const uint32_t *__restrict__ tm1,
@@ -1941,7 +1946,7 @@ k_sample_f32(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz, cons
 }
 
 template <uint32_t NS, uint32_t TM, bool LEAN>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves64<NS, TM, LEAN>, 8)))
 k_sample_f64(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz, const uint32_t *__restrict__ tm1,
              const uint32_t *__restrict__ det, const uint32_t *__restrict__ words, const BatchMember *__restrict__ bm,
              RunParams P) {
