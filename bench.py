@@ -37,8 +37,6 @@ LONG_SHOTS_P = 5e-4     # noise rate of the leg whose discard rate is near the p
 
 # Peaks (MI355X: 256 CUs x 4 SIMDs x 16 lanes at 2.4 GHz):
 INT_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12   # 32-bit vector lane-ops/s, 39.3 T
-FP32_PEAK_TFLOPS = 157.3                       # published vector FP32 (packed FMA)
-FP32_NONPACKED_TFLOPS = 78.6                   # one FMA per lane per cycle (the kernels are compiled without packed FP32)
 
 # Algorithmic work per unit (the measurement plan's units):
 INT_PER_ENTRY = 8        # per coefficient entry an event touches: alpha^beta, parity(gamma & alpha), partner compare
@@ -187,12 +185,20 @@ def int_ops(w):
 
 
 def roofline(work, shared, nsample, shots, ms, c, traffic_path=PROFILE_TRAFFIC, issue_path=PROFILE_ISSUE):
-    """Algorithmic int and FP work of one launch over its measured time.  The
-    work is the oracle's per-shot work on a sample less the part each shot
-    spends on the noiseless trajectory that all shots share (computed once
-    per launch, a negligible term left out, so the count is a lower bound)."""
+    """The work that one launch cannot do without over its measured time.
+
+    achieved/frac: the noise words that the oracle draws for the shots, up to
+    the check that ends each (a quarter of a Philox block a word).  On these
+    circuits the records follow from the noise's signs unless it breaks a T
+    pair, so a sampler need not touch a coefficient for most shots.
+
+    formalism: the oracle's per-shot work on coefficients and words, less the
+    part each shot spends on the noiseless trajectory that all shots share.
+    It says how much of the method's work the launch stands for; its rate is
+    no fraction of a peak, since most of that work is not executed."""
     ps = {k: (v - shared[k]) / nsample for k, v in work.items()}
-    int_per_shot = int_ops(ps)
+    method_ops = int_ops(ps)
+    int_per_shot = INT_PER_UNIFORM * work["noise_words"] / nsample
     fp_per_shot = (FP_T_BRANCH * ps["t_entries"] + FP_T_PHASE * ps["t_phase_flips"] + FP_M_IN * ps["m_entries"] +
                    FP_M_OUT * ps["m_out_entries"] + FP_M_PAIR * ps["m_pairs"])
     sec = ms / 1e3
@@ -204,10 +210,9 @@ def roofline(work, shared, nsample, shots, ms, c, traffic_path=PROFILE_TRAFFIC, 
            "units": {"int_per_entry": INT_PER_ENTRY, "int_per_uniform": INT_PER_UNIFORM, "fp_t_branch": FP_T_BRANCH,
                      "fp_t_phase": FP_T_PHASE, "fp_m_in": FP_M_IN, "fp_m_out": FP_M_OUT, "fp_m_pair": FP_M_PAIR},
            "work_per_shot": ps,
-           "ops_per_shot_from_start": int_ops({k: v / nsample for k, v in work.items()}),
-           "fp": {"flops_per_shot": fp_per_shot, "achieved": fp_rate, "unit": "TFLOP/s",
-                  "peak": FP32_PEAK_TFLOPS, "frac": fp_rate / FP32_PEAK_TFLOPS,
-                  "peak_nonpacked": FP32_NONPACKED_TFLOPS, "frac_nonpacked": fp_rate / FP32_NONPACKED_TFLOPS}}
+           "formalism": {"ops_per_shot": method_ops, "rate": method_ops * shots / sec / 1e12, "unit": "Tops/s",
+                         "ops_per_shot_from_start": int_ops({k: v / nsample for k, v in work.items()}),
+                         "flops_per_shot": fp_per_shot, "flop_rate": fp_rate, "flop_unit": "TFLOP/s"}}
     t = profile_of(traffic_path, shots)
     out["traffic_source"] = None
     if t is not None:
@@ -222,8 +227,7 @@ def roofline(work, shared, nsample, shots, ms, c, traffic_path=PROFILE_TRAFFIC, 
         out["measured"]["source"] = ("rocprofv3 --pmc SQ_INSTS_VALU, SQ_INSTS_SALU: profiles/" +
                                      os.path.basename(issue_path).replace("_issue.json", "_sq_counters.md"))
     # The same unit costs over the work the kernel executed (its own
-    # counters): dense-tile T entries instead of the oracle's sparse support,
-    # no class sums for measurements whose outcome the compiled span fixes.
+    # counters: the shots the sign pass left, and the words both drew).
     ex_int = INT_PER_ENTRY * (c["entries_t"] + c["entries_m"]) + INT_PER_UNIFORM * c["noise_slots"]
     out["executed"] = {"ops_per_launch": ex_int, "achieved": ex_int / sec / 1e12,
                        "frac": ex_int / sec / 1e12 / INT_PEAK_TOPS,

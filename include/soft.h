@@ -10,8 +10,8 @@
  * the Pauli-on-basis identity Eq. 4, Theorem 1 part 3), Pauli measurements
  * collapse and renormalise (Theorem 1 part 2), and Pauli noise is drawn per
  * shot (Sec. II-C, pure-state simulation model; uniform depolarizing noise of
- * Sec. III).  All shots of a run execute on one GPU in one persistent,
- * work-stealing kernel.
+ * Sec. III).  All shots of a run execute on one GPU in persistent
+ * kernels whose waves take shots from a queue.
  *
  * General conventions
  *  - Every call returns 0 on success or a negative SOFT_E* code; the message
@@ -201,7 +201,7 @@ int soft_set_prune(soft_ctx *ctx, double tau);
 /* Fixed capacities and launch shape (Sec. IV-B: per-shot capacity with an
  * overflow flag).  support_cap: a shot whose support |v| exceeds it after a T
  * ends as OVERFLOW (0 = no cap).  waves_per_block (1..4), blocks_per_cu
- * (1..32), grab (1..64, consecutive shots a wave takes per steal; their
+ * (1..32), grab (1..64, consecutive shots a wave takes at a time; their
  * outputs are written together): launch shape, 0 = the autotuned or default
  * value (for grab its upper end: launches of few shots a wave take fewer at a
  * time).  One wave runs one shot at a time, so shots in flight per block =
@@ -299,7 +299,8 @@ int soft_set_deferred_t(soft_ctx *ctx, int on);
 
 /* Where the per-wave coefficient tile lives (the GPU memory layout of
  * Sec. IV-B, re-planned for LDS and HBM): 0 = automatic (LDS when one
- * wave's tile takes at most 8 KiB; a split as mode 3 picks it when the tile
+ * wave's tile takes at most 8 KiB, or when it fits in a block's LDS and the
+ * sign pass decides nearly every shot; a split as mode 3 picks it when the tile
  * is larger but fits in a block's LDS; else device memory; soft_autotune also
  * tries device memory and other splits), 1 = LDS, 2 = device memory (HBM; one slab
  * of 2^k_max entries per resident wave, allocated by the library on first
@@ -355,8 +356,8 @@ int soft_run(soft_ctx *ctx, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments, outputs and results as soft_run; the caller owns the outputs.
  * This call allocates nothing: no hipMalloc / hipFree, no graph is built.
- * It launches the counter reset and the sampler directly on hip_stream (so
- * a caller may capture them) and takes its counters, work cursors,
+ * It launches the counter reset, the checkpoint build, the sign pass and the
+ * sampler directly on hip_stream (so a caller may capture them) and takes its counters, work cursors,
  * checkpoint slots (soft_set_shared_prefix; at most 4 MiB, else shots run
  * from the start with the same results) and any device-memory tiles from a static
  * scratch array of 36 MiB + 64 KiB per GPU, which the library holds on each
@@ -448,11 +449,12 @@ int soft_variant_info(soft_ctx *ctx, uint32_t variant, uint64_t info[8]);
  * words), tile placement (0 LDS, 1 device memory, 2 split). */
 int soft_launch_shape(soft_ctx *ctx, uint32_t out[5]);
 
-/* Graph reuse of this context (the persistent launch is a hipGraph of two
- * kernel nodes, Sec. IV-B's batched launches): out[0] = graph
+/* Graph reuse of this context (a launch is a hipGraph of the counter reset,
+ * the sign pass where it runs and the sampler, Sec. IV-B's batched launches;
+ * checkpoint states are built before it): out[0] = graph
  * instantiations so far, out[1] = graph launches so far.  A run whose
  * precision, noise source, tile placement and launch shape match an existing
- * instantiation only updates the sampler node's arguments (shot range,
+ * instantiation only updates the nodes' arguments (shot range,
  * outputs, ...), so a scan of equal batches instantiates at most twice (two
  * instantiations are used in turn, so that one can be updated while the
  * other runs). */

@@ -28,7 +28,7 @@ struct RunParams {
     uint32_t *abort_op;       // [n_shots] or null
     uint32_t *obs;            // [n_shots] or null
     unsigned long long *counters;  // [variants][shards][C_COUNT]
-    unsigned long long *next;      // work-stealing cursors
+    unsigned long long *next;      // work cursors
     unsigned long long *keep_meta; // [keep_n][KM_COUNT] or null
     double *keep_v;                // [keep_n][tile_entries][2] or null
     unsigned long long *trace_meta;  // [trace_n][KM_COUNT] or null
@@ -77,7 +77,8 @@ struct SignParams {
     uint64_t seed, shot0, n_shots;
     uint32_t n_vars, rec_words, chunk;
     uint32_t prefix;          // 1: count the shots a checkpoint precedes
-    uint32_t shards, pad;
+    uint32_t shards;          // counter rows per variant
+    uint32_t pad;
 };
 
 // The sign pass's vector sizes: a launch uses the smallest that holds its

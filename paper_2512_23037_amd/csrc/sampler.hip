@@ -1,8 +1,13 @@
-// sampler.hip -- persistent, work-stealing shot sampler for gfx950 (CDNA4).
+// sampler.hip -- persistent shot sampler for gfx950 (CDNA4).
 //
-// One wavefront (64 lanes) runs one shot at a time and then steals the next
-// shot index from a global counter, so early postselection aborts and uneven
-// coefficient supports balance themselves.  Per shot a wave holds:
+// One wavefront (64 lanes) runs one shot at a time, from groups of consecutive
+// shots that it starts with or takes from the launch's queue (device.h), so
+// early postselection aborts and uneven coefficient supports balance
+// themselves.  After a sign pass (signs.hip) it runs the shots that pass left.
+// What bounds it: with every shot to run, VALU issue (10^4 instructions a shot
+// for 52 events of injected T gates, 76% busy); with few left, the length of
+// single shots, each event 2000 to 5000 cycles of dependent instructions.
+// Per shot a wave holds:
 //   * the 2n tableau signs as two 64-bit words (rD, rS) and the offset a of
 //     the coefficient support -- wave-uniform scalars;
 //   * the coefficients as a dense LDS tile of 2^k complex numbers (k = span
@@ -662,8 +667,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
         maxdev = 0.0;
     };
 
-    // Work stealing by groups of `grab` consecutive shots, at most 64 of them
-    // at a time.  A wave writes its shots' output words one shot after the
+    // Groups of `grab` consecutive shots, at most 64 of them at a time.  A wave writes its shots' output words one shot after the
     // other, so L2 gathers each output plane's words of a group into whole
     // lines.
     uint64_t group_base = 0;

@@ -6,14 +6,15 @@
 // move the first set test.  What the coefficients decide (SGT_HAND) is left to
 // the sampler kernel, which runs after this one on the pending shots.
 //
-// With gap sampling a shot is a few Philox blocks, table reads and XORs: 10^7
-// shots of the 42-qubit circuit at p = 1e-3 take 0.85 ms (12 G shots/s), bound
-// by the latency of the table reads and by lanes that wait for the longest of
-// their neighbours' shots, and for the few that settle a broken pair (0.45 ms
-// without those).  With a word per slot it is bound by the Philox multiplies:
-// 5 10^5 shots at p = 5e-4 (1.4 G words) take 1.3 ms.  The launches take 2.9 and
-// 1.5 ms; 48.3 and 3.2 with the sampler kernel alone, 12.2 and 2.2 with the
-// broken pairs (5% of the shots) left to it.
+// With gap sampling a shot is a few Philox blocks, table reads and XORs.  What
+// bounds it is VALU issue with about half the lanes at work (a wave fills its
+// lanes when half of them have ended: 50 of 64 busy in a step, fewer in the
+// shots' ends and starts) and the reads' latency between: a step waits for its
+// gaps, its slots and their signatures.  A launch of 10^7 shots of the 42-qubit
+// circuit at p = 1e-3 takes 0.50 ms, 20 G shots/s (48.4 ms with the sampler
+// kernel alone).  With a word per slot it is bound by the Philox blocks, 222
+// cycles each of about 350 a step takes: 5 10^5 shots at p = 5e-4 (1.4 G words)
+// take 0.93 ms (3.2 with the sampler kernel alone).
 #include <hip/hip_runtime.h>
 
 #include "device.h"

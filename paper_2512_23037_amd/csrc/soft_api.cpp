@@ -1,10 +1,10 @@
 // soft_api.cpp -- the C ABI declared in include/soft.h.
 //
 // Host side of the sampler: owns the compiled circuit and its device copy,
-// chooses the launch shape (fixed, default or autotuned), captures the
-// reset + sampler launch pair into a hipGraph, and decodes kept final states
-// for the readout calls.  No simulation arithmetic runs here; every shot is
-// computed by the kernels in sampler.hip.
+// chooses the launch shape (fixed, default or autotuned), runs the reset, the
+// sign pass and the sampler as one hipGraph, and decodes kept final states for
+// the readout calls.  No simulation arithmetic runs here; every shot is
+// computed by the kernels in signs.hip and sampler.hip.
 #include "soft.h"
 
 #include <hip/hip_runtime.h>
@@ -137,10 +137,11 @@ struct soft_ctx {
     DevBuf<double> d_trace_v;
     uint32_t trace_tile = 0;
 
-    // The reset + sampler pair as a graph of two kernel nodes, instantiated
-    // twice (two slots used in turn).  A run whose kernel and launch shape
-    // match the slot's only updates the sampler node's arguments (shot range,
-    // outputs, ...), so one instantiation serves a whole scan; a slot is
+    // The reset, the sign pass (where it runs) and the sampler as a graph of
+    // two or three kernel nodes, instantiated twice (two slots used in turn).
+    // A run whose kernels and launch shape match the slot's only updates the
+    // nodes' arguments (shot range, outputs, ...), so one instantiation serves
+    // a whole scan; a slot is
     // updated only after its previous launch has finished (its event), since
     // an update may rewrite arguments a running launch still reads.
     struct GraphSlot {
@@ -634,9 +635,6 @@ int check_shape(soft_ctx *c, const Shape &s) {
     return SOFT_OK;
 }
 
-// Launch reset + sampler on `stream` through an instantiated graph: a slot
-// whose kernel and launch shape match gets the new arguments, else a slot is
-// built (reset node -> sampler node) and instantiated.
 // Blocks of a launch: the resident blocks of the shape, at most one per
 // `wpb` shots.
 uint64_t grid_blocks(const soft_ctx *c, const Shape &s, uint64_t n_shots) {
@@ -706,6 +704,9 @@ uint32_t group_size(const soft_ctx *c, const Shape &s, uint64_t grid, uint64_t n
     return (uint32_t)(each < 4u ? each : std::min<uint64_t>(s.grab, each / 4u));
 }
 
+// Launch on `stream` through an instantiated graph: a slot whose kernels and
+// launch shape match gets the new arguments, else a slot is built (reset ->
+// sign pass -> sampler) and instantiated.
 int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStream_t stream) {
     const uint32_t wb = wave_bytes(c, s);
     const size_t lds = (size_t)s.wpb * wb;
