@@ -449,15 +449,11 @@ int soft_variant_info(soft_ctx *ctx, uint32_t variant, uint64_t info[8]);
  * words), tile placement (0 LDS, 1 device memory, 2 split). */
 int soft_launch_shape(soft_ctx *ctx, uint32_t out[5]);
 
-/* Graph reuse of this context (a launch is a hipGraph of the counter reset,
- * the sign pass where it runs and the sampler, Sec. IV-B's batched launches;
- * checkpoint states are built before it): out[0] = graph
- * instantiations so far, out[1] = graph launches so far.  A run whose
- * precision, noise source, tile placement and launch shape match an existing
- * instantiation only updates the nodes' arguments (shot range,
- * outputs, ...), so a scan of equal batches instantiates at most twice (two
- * instantiations are used in turn, so that one can be updated while the
- * other runs). */
+/* Launches of this context (Sec. IV-B's batched launches): out[0] = graphs
+ * instantiated, always 0 (a run's kernels -- checkpoint build where needed,
+ * counter reset, sign pass where it runs, sampler -- go to the stream one
+ * after the other), out[1] = runs launched so far (soft_run, soft_run_list,
+ * soft_autotune's). */
 int soft_graph_info(soft_ctx *ctx, uint64_t out[2]);
 
 #ifdef __cplusplus

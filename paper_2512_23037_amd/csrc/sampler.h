@@ -97,23 +97,20 @@ constexpr uint32_t kQueueCursors = 8, kCursorStride = 16, kQueueWords = kQueueCu
 constexpr uint32_t kSampleCursor = 0, kSignCursor = kQueueWords, kBuildCursor = 2 * kQueueWords;
 constexpr uint32_t kCursorWords = 3 * kQueueWords;
 
-// Zero `n` counters and the work cursors: a kernel, so it can live in a graph.
+// Zero `n` counters and the work cursors: a kernel, so it can be captured.
 constexpr uint32_t kResetBlock = 1024;
 hipError_t launch_reset(unsigned long long *counters, uint32_t n, unsigned long long *next, hipStream_t stream);
 
 // The persistent sampler: grid x block threads, `lds` bytes of dynamic LDS.
 hipError_t launch_sampler(const RunParams &p, bool fp64, dim3 grid, dim3 block, size_t lds, hipStream_t stream);
 
-// Host handles of the kernels, for graphs built from explicit kernel nodes:
-// the sampler instantiation for a precision, noise source and tile mode
-// (arguments: ev, nz, tm1, det, words, bm, then the RunParams by value), and
-// the counter reset (arguments: counters, n, next; one block of kResetBlock threads).
+// Host handle of the sampler instantiation for a precision, noise source and
+// tile mode (arguments: ev, nz, tm1, det, words, bm, then the RunParams by value).
 const void *sampler_kernel(bool fp64, uint32_t noise_source, uint32_t tile_mode, bool lean);
 // Whether a launch with these parameters runs the lean kernel (no kept
 // states, no trace, no support cap, no shot list, no explicit words; see
 // sampler.hip).
 bool sampler_lean(const RunParams &p);
-const void *reset_kernel();
 // The shared-prefix build kernel for a precision and tile mode (arguments as
 // the sampler's, with RunParams::prefix_build set), and a direct launch of it.
 const void *prefix_kernel(bool fp64, uint32_t tile_mode);

@@ -2053,8 +2053,6 @@ const void *sampler_kernel(bool fp64, uint32_t ns, uint32_t tm, bool lean) {
     return ks[kernel_index(fp64, ns, tm > TM_SPLIT ? TM_LDS : tm, lean)];
 }
 
-const void *reset_kernel() { return (const void *)k_reset; }
-
 const void *prefix_kernel(bool fp64, uint32_t tm) {
     const void *ks[6] = {(const void *)k_prefix_f32<TM_LDS>, (const void *)k_prefix_f32<TM_MEM>,
                          (const void *)k_prefix_f32<TM_SPLIT>, (const void *)k_prefix_f64<TM_LDS>,

@@ -324,7 +324,7 @@ class Context:
         return {k: int(v) for k, v in zip(keys, a)}
 
     def graph_info(self) -> dict:
-        """Graph instantiations and launches of this context so far."""
+        """Runs launched by this context so far (and graphs instantiated: 0)."""
         import numpy as np
         a = np.zeros(2, dtype=np.uint64)
         self._check(self._lib.soft_graph_info(self._h, _ptr(a)))

@@ -6,7 +6,7 @@ rates with intervals, discard rates, and throughput sweeps.
   within a given factor (1000 in the paper's Sec. IV figures) of the
   maximum-likelihood hypothesis.
 * ``run_batches``: run shots [shot0, shot0 + total) of a loaded context in
-  launches of ``batch`` shots (each launch is the library's captured graph),
+  launches of ``batch`` shots (each launch is the library's reset, sign pass and sampler),
   summing the device counters of every variant.
 * ``noise_scan``: one circuit at several noise rates, as the variants of one
   mixture, so every batch is a single persistent launch; reports per rate the
@@ -156,7 +156,7 @@ def batch_sweep(ctx, sizes, reps: int = 3) -> list[dict]:
     status = torch.empty(max(sizes), dtype=torch.int32, device="cuda")
     stream = torch.cuda.current_stream()
     for n in sizes:
-        ctx.run(0, n, status=status, stream=stream)  # warm-up and graph capture
+        ctx.run(0, n, status=status, stream=stream)  # warm-up
         best = math.inf
         for r in range(reps):
             e0 = torch.cuda.Event(enable_timing=True)
@@ -191,7 +191,7 @@ def p_sweep(text: str, ps, shots: int, bits: int = 32, seed: int = 0, noise_mode
         ctx.set_rng(seed)
         ctx.set_precision(bits)
         ctx.set_noise_mode(noise_mode)
-        ctx.run(0, shots, status=status, stream=stream)  # warm-up and graph capture
+        ctx.run(0, shots, status=status, stream=stream)  # warm-up
         best = math.inf
         for r in range(reps):
             e0 = torch.cuda.Event(enable_timing=True)

@@ -172,3 +172,39 @@ def test_states_kept_between_runs():
                 assert (got[k] == ref[k]).all(), (bits, tau, cap, k)
             assert [ctx.read_coeffs(s) for s in range(16)] == kept
             assert ctx.counters()["support_hist"] == hist
+
+
+def test_captured_runs():
+    # soft_run recorded by a stream capture: the replays build their own
+    # checkpoint states, whatever other runs of the context left, and those
+    # runs build theirs again
+    import torch
+    w = workloads.config("cultivation_15q", seed=1)
+    ctx = make_ctx(w.text, NOISE, seed=5)
+    ctx.set_noise_mode(1)
+    n = 3001
+    ref = run_gpu(ctx, 0, n)
+    outs = soft.sample(ctx, 0, n)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        ctx.run(0, n, *outs, stream=torch.cuda.current_stream().cuda_stream)
+    for rep in range(3):
+        for o in outs:
+            o.zero_()
+        if rep:  # other states in the slots
+            ctx.set_precision(32)
+            other = run_gpu(ctx, 0, n)
+            ctx.set_precision(64)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        nw = ref["outcomes"].shape[0]
+        assert (outs[1].cpu().numpy().view(np.uint32) == ref["status"]).all()
+        assert (outs[0].cpu().numpy().view(np.uint32)[:nw] == ref["outcomes"]).all()
+        again = run_gpu(ctx, 0, n)
+        assert (again["status"] == ref["status"]).all() and (again["outcomes"] == ref["outcomes"]).all()
+        if rep:
+            ctx.set_precision(32)
+            assert (run_gpu(ctx, 0, n)["status"] == other["status"]).all()
+            ctx.set_precision(64)
