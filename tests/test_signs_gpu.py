@@ -66,6 +66,21 @@ def test_sizes(n, shot0, mode):
         assert ca["events"] < 0.5 * cb["events"]
 
 
+@pytest.mark.parametrize("n", [2_000_001, 5_300_007])
+def test_few_left_over(n):
+    # groups of several reads of 256 statuses, the last one short, with and
+    # without shots left in them
+    w = workloads.config("cultivation_15q", seed=1)
+
+    def build():
+        ctx = make_ctx(w.text, {k: 2e-3 for k in NOISE}, seed=7)
+        ctx.set_noise_mode(1)
+        return ctx
+
+    a, ca, cb = both(build, 11, n)
+    assert 0 < ca["events"] < 0.01 * cb["events"]
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("n_rounds", [1, 8, 16, 60, 200, 300])
 def test_vector_sizes(n_rounds, mode):
