@@ -91,15 +91,8 @@ __device__ __forceinline__ uint32_t quot16(uint64_t x, uint64_t d) {
     return m;
 }
 
-// A launch's items [0, n) dealt out to its waves.  Wave w starts with item w,
-// without a cursor, so a launch of at most one item a wave has no atomics;
-// the rest come from eight cursors, wave w's being w mod 8 (of one-wave blocks,
-// consecutive ones go to the eight XCDs in turn).  Atomics on one address
-// follow each other every 16 ns: with one cursor for all, 25 000 items of four
-// shots took 0.43 ms where the work in them took 0.14, and the 5120 waves of a
-// small launch of the sampler spent 80 us finding that nothing was left.
-// The next item of the wave (all lanes active); false when there is none.
-// `started` is its state, false at first.
+// The next of a launch's items [0, n) for this wave (queue.h; all lanes
+// active); false when there is none.  `started` is its state, false at first.
 __device__ __forceinline__ bool take_item(unsigned long long *cursors, uint64_t n, uint32_t wave, uint32_t waves,
                                           uint32_t lane, bool &started, uint64_t &item) {
     if (!started) {
@@ -108,13 +101,12 @@ __device__ __forceinline__ bool take_item(unsigned long long *cursors, uint64_t 
         return item < n;
     }
     if (n <= waves) return false;
-    const uint32_t id = wave % kQueueCursors;
+    const uint32_t id = queue_cursor(wave, waves);
     unsigned long long c = 0;
     if (lane == 0) c = atomicAdd(cursors + id * kCursorStride, 1ull);
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)c);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(c >> 32));
-    const uint32_t first = (waves - id + kQueueCursors - 1u) / kQueueCursors;  // items of this cursor that waves start with
-    item = (first + (((uint64_t)hi << 32) | lo)) * kQueueCursors + id;
+    item = queue_item(id, ((uint64_t)hi << 32) | lo, waves);
     return item < n;
 }
 

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "program.h"
+#include "queue.h"
 
 namespace soft {
 
@@ -90,10 +91,9 @@ constexpr uint32_t kSignWavesPerCu[4] = {24, 24, 20, 12};  // by their registers
 const void *signs_kernel(uint32_t size, bool gaps);
 hipError_t launch_signs(const SignParams &p, uint32_t size, bool gaps, dim3 grid, hipStream_t stream);
 
-// Work cursors, after the counter rows: the eight of a queue (take_item), each
+// Work cursors, after the counter rows: the eight of a queue (queue.h), each
 // in a cache line of its own, for the sampler, the sign pass and the prefix
 // build (a launch of its own, at most one item a wave but in soft_run_noalloc).
-constexpr uint32_t kQueueCursors = 8, kCursorStride = 16, kQueueWords = kQueueCursors * kCursorStride;
 constexpr uint32_t kSampleCursor = 0, kSignCursor = kQueueWords, kBuildCursor = 2 * kQueueWords;
 constexpr uint32_t kCursorWords = 3 * kQueueWords;
 
