@@ -352,6 +352,8 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
                         for (int w = 0; w < RO - 1; ++w)
                             if ((uint32_t)w < A->rec_words) A->outcomes[(uint64_t)w * A->n_shots + i] = x[TW + w] & mk[w];
+                        // (a variant that this pass leaves to the sampler may have more words)
+                        for (uint32_t w = RO - 1; w < A->rec_words; ++w) A->outcomes[(uint64_t)w * A->n_shots + i] = 0u;
                     }
                     words += GAPS ? pos : min(pos, n_noise);
                     atomicAdd(&hist[ck], 1u);

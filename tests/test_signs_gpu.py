@@ -223,3 +223,26 @@ def test_captured_runs():
             ctx.set_precision(32)
             assert (run_gpu(ctx, 0, n)["status"] == other["status"]).all()
             ctx.set_precision(64)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_record_planes_of_a_longer_variant(mode):
+    # a shot that the signs decide has a zero in every record word past its
+    # circuit's own, also those that only a variant left to the sampler has
+    long = "QUBITS 2\nH 0\nT 0\nMPP X0\n" + "R 1\nX 1\nM 1\n" * 200
+    ctx = soft.Context(0)
+    ctx.load_mixture([rounds(4), long], [NOISE] * 2, [300, 500])
+    ctx.set_rng(3)
+    ctx.set_noise_mode(mode)
+    got = []
+    for on in (True, False):
+        ctx.set_shared_prefix(on)
+        import torch
+        outs = [torch.full((ctx.info()["record_words"], 500), -7, dtype=torch.int32, device="cuda")] + \
+            [torch.full((500,), -7, dtype=torch.int32, device="cuda") for _ in range(3)]
+        ctx.run(0, 500, *outs)
+        torch.cuda.synchronize()
+        got.append([o.cpu().numpy() for o in outs] + [ctx.counters()["events"]])
+    assert got[0][0].shape[0] > 4 and got[0][4] < got[1][4]
+    for a, b in zip(got[0][:4], got[1][:4]):
+        assert (a == b).all()
