@@ -101,7 +101,8 @@ typedef struct {
 int soft_create(soft_ctx **out, int hip_device);
 
 /* Free everything the context owns (the device memory of Sec. IV-B it
- * allocated); waits for its last run first.  NULL is allowed. */
+ * allocated); waits for its last run first.  Graphs that recorded its runs
+ * must not be replayed afterwards.  NULL is allowed. */
 void soft_destroy(soft_ctx *ctx);
 
 /* Message of the last failed call on ctx ("" if none); valid until the next
@@ -347,6 +348,14 @@ int soft_set_keep(soft_ctx *ctx, uint64_t shot_lo, uint32_t count);
  *   abort_op_dev: uint32 [n_shots] op index that ended the shot
  *                 (0xffffffff if it passed), or NULL;
  *   obs_dev:      uint32 [n_shots], bit j = observable j, or NULL.
+ * A stream capture may record the call, with the circuit, settings and
+ * outputs of that moment (a capture mode that forbids allocation needs a run
+ * of the same settings and size before it).  A replay builds its own
+ * checkpoint states.  Every buffer of the library that a recording reads is
+ * kept, unchanged by later loads, until soft_destroy; recordings are not
+ * replayed after that.  Replays and other runs of the context share its
+ * counters and tiles, so the caller orders them; soft_read_counters reads
+ * what the last of them left, in the layout of the context's last run call.
  * EINVAL if the shots reach past the last variant's range of a mixture. */
 int soft_run(soft_ctx *ctx, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes_dev,
              uint32_t *status_dev, uint32_t *abort_op_dev, uint32_t *obs_dev,
@@ -366,7 +375,7 @@ int soft_run(soft_ctx *ctx, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes
  * (soft_set_tile_memory) get at most 32 MiB of slabs, so such a launch may
  * run fewer waves; ECAPACITY when one block's slabs exceed 32 MiB.
  * The circuit's device tables are uploaded (allocated) by the soft_load_*
- * calls, never here.
+ * calls, never here; those that a recording reads are kept until soft_destroy.
  *   ESTATE: no circuit loaded;
  *   EUNSUPPORTED: kept states or a trace are on (they use library buffers).
  * Every call on a GPU, from any context, shares that GPU's scratch and leaves

@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "compile.h"
+#include "devbuf.h"
 #include "sampler.h"
 #include "signs.h"
 
@@ -63,9 +64,9 @@ typedef std::tuple<std::string, int, uint64_t, int, double, uint32_t, int, int> 
 std::mutex g_tune_mu;
 std::map<TuneKey, Shape> g_tuned;
 
-template <typename T> struct DevBuf {
-    T *p = nullptr;
-    size_t n = 0;  // elements allocated
+struct HipMem {
+    static int alloc(void **p, size_t bytes) { return (int)hipMalloc(p, bytes); }
+    static int free(void *p) { return (int)hipFree(p); }
 };
 
 }  // namespace
@@ -101,6 +102,7 @@ struct soft_ctx {
     Shape user;                               // explicit launch shape parts
     std::string arch;                         // gcnArchName of the device (autotune cache key)
 
+    Buffers<HipMem> mem;
     DevBuf<Event> d_ev;
     DevBuf<NoiseLoc> d_nz;
     DevBuf<uint32_t> d_tm1, d_det, d_gap;
@@ -109,6 +111,7 @@ struct soft_ctx {
     DevBuf<VariantDesc> d_vars;
     DevBuf<unsigned char> d_gtile;            // device-memory tiles
     DevBuf<unsigned char> d_prefix;           // checkpoint state slots (one per table entry)
+    DevBuf<unsigned char> d_prefix_rec;       // those that recorded launches build in every replay
     DevBuf<Checkpoint> d_ckpt;                // checkpoint table
     uint32_t n_ckpt = 0;                      // its entries
     // What the states in d_prefix were built for (none: empty); a run that
@@ -140,9 +143,11 @@ struct soft_ctx {
     uint64_t launches = 0;
     hipEvent_t done = nullptr;           // after the last launch, and its stream
     hipStream_t done_stream = nullptr;
-    // Whether checkpoint states stay for later runs: not once a launch was
-    // recorded by a stream capture, whose replays write them at any time.
-    bool keep_states = true;
+
+    template <typename F> void each_buffer(F f) {
+        f(d_ev), f(d_nz), f(d_tm1), f(d_det), f(d_gap), f(d_bm), f(d_diag), f(d_vars), f(d_gtile), f(d_prefix), f(d_prefix_rec);
+        f(d_ckpt), f(d_signs), f(d_keep_meta), f(d_keep_v), f(d_trace_meta), f(d_trace_v);
+    }
 
     bool ran = false;
     hipStream_t last_stream = nullptr;
@@ -163,21 +168,24 @@ int fail(soft_ctx *c, int code, const std::string &msg) {
         if (e_ != hipSuccess) return fail((ctx), SOFT_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-template <typename T> int ensure(soft_ctx *c, DevBuf<T> &b, size_t n) {
-    if (n == 0) n = 1;
-    if (b.n >= n) return SOFT_OK;
-    if (b.p) HIPCHK(c, hipFree(b.p));
-    b.p = nullptr;
-    b.n = 0;
-    HIPCHK(c, hipMalloc((void **)&b.p, n * sizeof(T)));
-    b.n = n;
-    return SOFT_OK;
+int alloc_rc(soft_ctx *c, int e) {
+    return e ? fail(c, SOFT_EDEVICE, std::string("device memory: ") + hipGetErrorString((hipError_t)e)) : SOFT_OK;
+}
+template <typename T> int ensure(soft_ctx *c, DevBuf<T> &b, size_t n) { return alloc_rc(c, c->mem.ensure(b, n)); }
+template <typename T> int renew(soft_ctx *c, DevBuf<T> &b, size_t n) { return alloc_rc(c, c->mem.renew(b, n)); }
+
+// Whether a stream capture records the launches on `stream`.
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();  // (the launches report it)
+    return st != hipStreamCaptureStatusNone;
 }
 
-template <typename T> void release(DevBuf<T> &b) {
-    if (b.p) (void)hipFree(b.p);
-    b.p = nullptr;
-    b.n = 0;
+// A recording holds the context's buffers from here on (but for the states
+// that stay between runs: a recorded launch has its own).
+void mark_recorded(soft_ctx *c) {
+    c->each_buffer([](auto &b) { b.recorded = b.p != nullptr; });
+    c->d_prefix.recorded = false;
 }
 
 double tau_of(const soft_ctx *c) { return c->tau >= 0.0 ? c->tau : (c->bits == 32 ? 1e-6 : 1e-12); }
@@ -378,7 +386,7 @@ int prepare_signs(soft_ctx *c) {
                           put(test.data(), test.size() * sizeof(SignTest)), put(mask.data(), mask.size() * sizeof(uint32_t)),
                           put(coin.data(), coin.size() * sizeof(uint2)), put(desc.data(), nv * sizeof(SignDesc)),
                           put(pair.data(), pair.size() * sizeof(SignPair)), put(meas.data(), meas.size() * sizeof(SignMeas))};
-    int rc = ensure(c, c->d_signs, all.size());
+    int rc = renew(c, c->d_signs, all.size());
     if (rc) return rc;
     HIPCHK(c, hipMemcpy(c->d_signs.p, all.data(), all.size(), hipMemcpyHostToDevice));
     SignParams &T = c->sign_tables;
@@ -465,12 +473,12 @@ int prepare(soft_ctx *c) {
     c->any_prefix = !ck.empty();
     c->n_ckpt = (uint32_t)ck.size();
     int rc;
-    if ((rc = ensure(c, c->d_ev, ev.size())) || (rc = ensure(c, c->d_nz, std::max<size_t>(nz.size(), 1))) ||
-        (rc = ensure(c, c->d_tm1, tm1.size())) || (rc = ensure(c, c->d_det, std::max<size_t>(det.size(), 2))) ||
-        (rc = ensure(c, c->d_bm, std::max<size_t>(bm.size(), 1))) || (rc = ensure(c, c->d_vars, vd.size())) ||
-        (rc = ensure(c, c->d_diag, std::max<size_t>(dg.size(), 1))) ||
-        (rc = ensure(c, c->d_gap, std::max<size_t>(gap.size(), 1))) ||
-        (rc = ensure(c, c->d_ckpt, std::max<size_t>(ck.size(), 1))))
+    if ((rc = renew(c, c->d_ev, ev.size())) || (rc = renew(c, c->d_nz, std::max<size_t>(nz.size(), 1))) ||
+        (rc = renew(c, c->d_tm1, tm1.size())) || (rc = renew(c, c->d_det, std::max<size_t>(det.size(), 2))) ||
+        (rc = renew(c, c->d_bm, std::max<size_t>(bm.size(), 1))) || (rc = renew(c, c->d_vars, vd.size())) ||
+        (rc = renew(c, c->d_diag, std::max<size_t>(dg.size(), 1))) ||
+        (rc = renew(c, c->d_gap, std::max<size_t>(gap.size(), 1))) ||
+        (rc = renew(c, c->d_ckpt, std::max<size_t>(ck.size(), 1))))
         return rc;
     if (!ck.empty()) HIPCHK(c, hipMemcpy(c->d_ckpt.p, ck.data(), ck.size() * sizeof(Checkpoint), hipMemcpyHostToDevice));
     if (!gap.empty()) HIPCHK(c, hipMemcpy(c->d_gap.p, gap.data(), gap.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
@@ -691,6 +699,7 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     const uint64_t grid = grid_blocks(c, s, n_shots);
     const dim3 g((uint32_t)grid), b(64u * s.wpb);
     set_wave_layout(c, s, rp);
+    const bool captured = capturing(stream);
     if (s.gt != TM_LDS) {  // one slab per wave of the grid (the build's or the sampler's)
         int rc = ensure(c, c->d_gtile, std::max<size_t>(grid, build_blocks(s, rp)) * s.wpb * slab_bytes(c, s));
         if (rc) return rc;
@@ -700,32 +709,38 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     // states depend on the loaded tables and on what this key holds, so they
     // stay for the runs that follow: one wave walks a whole list for them
     // (85 to 265 us, with the sign pass most of a launch of 10^5 shots).  Runs
-    // of a context are in stream order, or ordered by the caller.
+    // of a context are in stream order, or ordered by the caller.  A recorded
+    // launch has slots of its own and builds its states in every replay.
     const bool pfx = use_prefix(c);
+    bool build = false;
     std::vector<uint64_t> pkey;
     rp.prefix = nullptr;
     rp.prefix_stride = 0;
     if (pfx) {
-        int rc = ensure(c, c->d_prefix, (size_t)c->n_ckpt * prefix_stride(c));
-        if (rc) return rc;
-        rp.prefix = c->d_prefix.p;
+        const size_t bytes = (size_t)c->n_ckpt * prefix_stride(c);
+        if (captured && c->d_prefix_rec.n < bytes && c->d_prefix.n >= bytes) {
+            // (a capture may forbid allocation: it takes the slots that are there)
+            if (int rc = alloc_rc(c, c->mem.drop(c->d_prefix_rec))) return rc;
+            std::swap(c->d_prefix, c->d_prefix_rec);
+            c->prefix_key.clear();
+        }
+        DevBuf<unsigned char> &slots = captured ? c->d_prefix_rec : c->d_prefix;
+        if (int rc = ensure(c, slots, bytes)) return rc;
+        rp.prefix = slots.p;
         rp.prefix_stride = prefix_stride(c);
         const double tau = tau_of(c);
         uint64_t tb;
         std::memcpy(&tb, &tau, sizeof(tb));
-        pkey = {(uint64_t)(uintptr_t)c->d_prefix.p, (uint64_t)c->bits, tb, rp.support_cap};
+        pkey = {(uint64_t)(uintptr_t)slots.p, (uint64_t)c->bits, tb, rp.support_cap};
+        build = captured || pkey != c->prefix_key;
     }
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();  // (the launches report it)
-    const bool captured = capture != hipStreamCaptureStatusNone;
-    if (captured) c->keep_states = false;
-    const bool build = pfx && (!c->keep_states || pkey != c->prefix_key);
+    if (captured) mark_recorded(c);
     const bool sgn = use_signs(c, rp.shot_list != nullptr);
     rp.grab = group_size(c, s, grid, n_shots, sgn);
     // another stream than the last launch's: after it, for the states it built
     if (!captured && c->done && stream != c->done_stream) HIPCHK(c, hipStreamWaitEvent(stream, c->done, 0));
     if (build) {
-        c->prefix_key.clear();
+        if (!captured) c->prefix_key.clear();
         HIPCHK(c, launch_prefix_build(build_params(rp), c->bits == 64, dim3(build_blocks(s, rp)), b, lds, stream));
     }
     HIPCHK(c, launch_reset(rp.counters, rp.n_vars * rp.shards * (uint32_t)C_COUNT, rp.next, stream));
@@ -738,7 +753,7 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     HIPCHK(c, launch_sampler(rp, c->bits == 64, g, b, lds, stream));
     ++c->launches;
     if (captured) return SOFT_OK;
-    if (build && c->keep_states) c->prefix_key = pkey;
+    if (build) c->prefix_key = pkey;
     if (!c->done) HIPCHK(c, hipEventCreateWithFlags(&c->done, hipEventDisableTiming));
     HIPCHK(c, hipEventRecord(c->done, stream));
     c->done_stream = stream;
@@ -992,22 +1007,8 @@ void soft_destroy(soft_ctx *c) {
     (void)hipSetDevice(c->device);
     if (c->ran && c->last_stream) (void)hipStreamSynchronize(c->last_stream);
     wait_done(c);
-    release(c->d_ev);
-    release(c->d_nz);
-    release(c->d_tm1);
-    release(c->d_gap);
-    release(c->d_det);
-    release(c->d_bm);
-    release(c->d_diag);
-    release(c->d_vars);
-    release(c->d_gtile);
-    release(c->d_prefix);
-    release(c->d_ckpt);
-    release(c->d_signs);
-    release(c->d_keep_meta);
-    release(c->d_keep_v);
-    release(c->d_trace_meta);
-    release(c->d_trace_v);
+    c->each_buffer([c](auto &b) { c->mem.release(b); });
+    c->mem.release_aside();
     if (c->d_counters) (void)hipFree(c->d_counters);
     if (c->d_phase) (void)hipFree(c->d_phase);
     if (c->done) (void)hipEventDestroy(c->done);
@@ -1259,6 +1260,7 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
         rp.gtile = c->scratch + kScratchCounterBytes + kScratchPrefixBytes;
     }
     const hipStream_t stream = (hipStream_t)hip_stream;
+    if (capturing(stream)) mark_recorded(c);
     HIPCHK(c, launch_reset(rp.counters, rp.n_vars * rp.shards * (uint32_t)C_COUNT, rp.next, stream));
     if (pfx)
         HIPCHK(c, launch_prefix_build(build_params(rp), c->bits == 64,
