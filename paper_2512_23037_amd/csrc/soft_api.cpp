@@ -153,6 +153,8 @@ struct soft_ctx {
     hipStream_t last_stream = nullptr;
     uint64_t last_shot0 = 0, last_n = 0;
     bool last_list = false;  // the last run sampled a shot list
+    hipStream_t noalloc_stream = nullptr;  // of the last soft_run_noalloc that no capture recorded,
+    bool noalloc_pending = false;          // not waited for since
 };
 
 namespace {
@@ -250,9 +252,12 @@ uint32_t split_log2_default(const soft_ctx *c) {
     return L;
 }
 
-// Wait for the last launch (each waits for the one before it).
-void wait_done(const soft_ctx *c) {
+// Wait for the last launch (each waits for the one before it); a
+// soft_run_noalloc records no event, its stream is waited for.
+void wait_done(soft_ctx *c) {
     if (c->done) (void)hipEventSynchronize(c->done);
+    if (c->noalloc_pending) (void)hipStreamSynchronize(c->noalloc_stream);
+    c->noalloc_pending = false;
 }
 
 int compile_into(soft_ctx *c, const std::string &text, const NoiseModel &nm, Program &out, bool speculate = false) {
@@ -473,6 +478,7 @@ int prepare(soft_ctx *c) {
     c->any_prefix = !ck.empty();
     c->n_ckpt = (uint32_t)ck.size();
     int rc;
+    wait_done(c);  // its launches read the tables
     if ((rc = renew(c, c->d_ev, ev.size())) || (rc = renew(c, c->d_nz, std::max<size_t>(nz.size(), 1))) ||
         (rc = renew(c, c->d_tm1, tm1.size())) || (rc = renew(c, c->d_det, std::max<size_t>(det.size(), 2))) ||
         (rc = renew(c, c->d_bm, std::max<size_t>(bm.size(), 1))) || (rc = renew(c, c->d_vars, vd.size())) ||
@@ -492,7 +498,6 @@ int prepare(soft_ctx *c) {
     if ((rc = prepare_signs(c))) return rc;
     c->dirty = false;
     c->prefix_key.clear();
-    wait_done(c);
     return SOFT_OK;
 }
 
@@ -1260,7 +1265,12 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
         rp.gtile = c->scratch + kScratchCounterBytes + kScratchPrefixBytes;
     }
     const hipStream_t stream = (hipStream_t)hip_stream;
-    if (capturing(stream)) mark_recorded(c);
+    if (capturing(stream)) {
+        mark_recorded(c);
+    } else {
+        c->noalloc_stream = stream;
+        c->noalloc_pending = true;
+    }
     HIPCHK(c, launch_reset(rp.counters, rp.n_vars * rp.shards * (uint32_t)C_COUNT, rp.next, stream));
     if (pfx)
         HIPCHK(c, launch_prefix_build(build_params(rp), c->bits == 64,
