@@ -101,6 +101,10 @@ constexpr uint32_t kCursorWords = 3 * kQueueWords;
 constexpr uint32_t kResetBlock = 1024;
 hipError_t launch_reset(unsigned long long *counters, uint32_t n, unsigned long long *next, hipStream_t stream);
 
+// Zero `n` words: a kernel, since a recorded memset has given wrong results on
+// replays after the first.
+hipError_t launch_clear(unsigned long long *p, uint64_t n, hipStream_t stream);
+
 // The persistent sampler: grid x block threads, `lds` bytes of dynamic LDS.
 hipError_t launch_sampler(const RunParams &p, bool fp64, dim3 grid, dim3 block, size_t lds, hipStream_t stream);
 

@@ -2007,6 +2007,10 @@ __global__ void k_reset(unsigned long long *counters, uint32_t n, unsigned long 
     for (uint32_t t = threadIdx.x; t < kCursorWords; t += blockDim.x) next[t] = 0ull;
 }
 
+__global__ void k_clear(unsigned long long *p, uint64_t n) {
+    for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (uint64_t)gridDim.x * blockDim.x) p[t] = 0ull;
+}
+
 template <typename R, uint32_t NS, uint32_t TM, bool LEAN> const void *kernel_ptr() {
     if (sizeof(R) == 4) return (const void *)k_sample_f32<NS, TM, LEAN>;
     return (const void *)k_sample_f64<NS, TM, LEAN>;
@@ -2052,6 +2056,12 @@ bool sampler_lean(const RunParams &p) {
 
 hipError_t launch_reset(unsigned long long *counters, uint32_t n, unsigned long long *next, hipStream_t stream) {
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(kResetBlock), 0, stream, counters, n, next);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear(unsigned long long *p, uint64_t n, hipStream_t stream) {
+    const uint32_t blocks = (uint32_t)(n < 262144u ? (n + 255u) / 256u : 1024u);
+    hipLaunchKernelGGL(k_clear, dim3(blocks ? blocks : 1u), dim3(256), 0, stream, p, n);
     return hipGetLastError();
 }
 

@@ -846,7 +846,7 @@ int run_impl(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes, 
     rp.grab = s.grab;
     rp.shot_list = shot_list;
     if (c->trace_n)  // mark every trace step unwritten
-        HIPCHK(c, hipMemsetAsync(c->d_trace_meta.p, 0, (size_t)c->trace_n * KM_COUNT * sizeof(unsigned long long), stream));
+        HIPCHK(c, launch_clear(c->d_trace_meta.p, (uint64_t)c->trace_n * KM_COUNT, stream));
     if ((rc = launch(c, rp, s, n_shots, stream))) return rc;
     c->ran = true;
     c->last_counters = c->d_counters;

@@ -102,3 +102,32 @@ def test_states_stay_for_eager_runs_after_a_capture():
         for k in want:
             assert (got[k] == want[k]).all()
         assert ctx.counters()["support_hist"] == hist
+
+
+def test_traced_replays():
+    # a recorded run marks the trace's steps unwritten in every replay: between
+    # them another, longer shot is traced into the same buffer
+    w = workloads.config("cultivation_15q", seed=1)
+    ctx = make_ctx(w.text, NOISE, seed=5)
+    n, steps = 200, 48
+    ops = run_gpu(ctx, 0, n)["abort_op"]
+    short, long = int(np.argmin(ops)), int(np.argmax(ops))
+
+    def trace():
+        got = [ctx.read_trace(s) for s in range(steps)]
+        return [g is not None for g in got], str(got)
+
+    ctx.set_trace(long, steps)
+    run_gpu(ctx, 0, n)
+    most = sum(trace()[0])
+    ctx.set_trace(short, steps)
+    run_gpu(ctx, 0, n)
+    want = trace()
+    assert 0 < sum(want[0]) < most
+    rec = Recording(ctx, 0, n)
+    for _ in range(3):
+        ctx.set_trace(long, steps)
+        run_gpu(ctx, 0, n)
+        assert sum(trace()[0]) == most
+        rec.check()
+        assert trace() == want
