@@ -403,12 +403,13 @@ int soft_run_list(soft_ctx *ctx, const uint64_t *shots_dev, uint64_t n_shots, ui
 
 /* Aggregates of the last run (the statistics the host reads back, Sec. IV-B;
  * discard rate and logical errors as in Sec. V); synchronizes that run's
- * stream.  ESTATE before any run. */
+ * stream.  Loads since then leave them as they are.  ESTATE before any run. */
 int soft_read_counters(soft_ctx *ctx, soft_counters *out);
 
 /* Aggregates of the last run over the shots of one variant of a mixture
  * (variant 0 of a single circuit is the whole run), as soft_read_counters
- * (Sec. IV-B, Sec. V).  Synchronizes.  EINVAL: no such variant. */
+ * (Sec. IV-B, Sec. V).  Synchronizes.  All zero for a variant loaded after
+ * that run, past the ones it had.  EINVAL: no such variant. */
 int soft_read_variant_counters(soft_ctx *ctx, uint32_t variant, soft_counters *out);
 
 /* Final coefficients v_alpha of Definition 1 / Eq. 3 of a kept shot of the

@@ -124,7 +124,7 @@ struct soft_ctx {
     bool sign_few = false;                    // it leaves few shots to the sampler
     unsigned long long *d_counters = nullptr;  // kCounterRows rows of C_COUNT, then the work cursors
     const unsigned long long *last_counters = nullptr;  // counters of the last run
-    uint32_t last_shards = 1;                           // and their rows per variant
+    uint32_t last_shards = 1, last_vars = 0;            // their rows per variant, and its variants
     double *d_phase = nullptr;                 // cos/sin of k pi/8, k = 0..15
     unsigned char *scratch = nullptr;          // this device's static scratch (soft_run_noalloc)
 
@@ -851,6 +851,7 @@ int run_impl(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes, 
     c->ran = true;
     c->last_counters = c->d_counters;
     c->last_shards = rp.shards;
+    c->last_vars = rp.n_vars;
     c->last_stream = stream;
     c->last_shot0 = shot0;
     c->last_n = n_shots;
@@ -1289,6 +1290,7 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
     c->ran = true;
     c->last_counters = rp.counters;
     c->last_shards = rp.shards;
+    c->last_vars = rp.n_vars;
     c->last_stream = stream;
     c->last_shot0 = shot0;
     c->last_n = n_shots;
@@ -1297,16 +1299,20 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
 }
 
 namespace {
-// Sum of the counter rows [v0, v1) (maximum for the norm deviation).
+// Sum of the last run's counters over its variants [v0, v1) (maximum for the
+// norm deviation).  A load since then changes neither that run's variants nor
+// where its rows lie; variants that it did not have counted nothing.
 int read_rows(soft_ctx *c, uint32_t v0, uint32_t v1, soft_counters *out) {
     if (!c->ran) return fail(c, SOFT_ESTATE, "no run yet");
     HIPCHK(c, hipSetDevice(c->device));
     HIPCHK(c, hipStreamSynchronize(c->last_stream));
-    // (the variants are the last run's: a load ends that run's counters)
     const uint32_t k = c->last_shards;
+    v1 = std::min(v1, c->last_vars);
+    v0 = std::min(v0, v1);
     std::vector<unsigned long long> h((size_t)(v1 - v0) * k * C_COUNT);
-    HIPCHK(c, hipMemcpy(h.data(), c->last_counters + (size_t)v0 * k * C_COUNT, h.size() * sizeof(unsigned long long),
-                        hipMemcpyDeviceToHost));
+    if (!h.empty())
+        HIPCHK(c, hipMemcpy(h.data(), c->last_counters + (size_t)v0 * k * C_COUNT, h.size() * sizeof(unsigned long long),
+                            hipMemcpyDeviceToHost));
     std::memset(out, 0, sizeof(*out));
     double dev = 0.0;
     for (uint32_t v = 0; v < (v1 - v0) * k; ++v) {
@@ -1352,7 +1358,7 @@ int soft_run_list(soft_ctx *c, const uint64_t *shots_dev, uint64_t n_shots, uint
 
 int soft_read_counters(soft_ctx *c, soft_counters *out) {
     if (!c || !out) return fail(c, SOFT_EINVAL, "null argument");
-    return read_rows(c, 0, (uint32_t)c->vars.size(), out);
+    return read_rows(c, 0, c->last_vars, out);
 }
 
 int soft_read_variant_counters(soft_ctx *c, uint32_t variant, soft_counters *out) {
