@@ -67,6 +67,10 @@ void build_signs(const Program &P, SignProgram &out) {
     uint32_t last = 0;  // the event the signs stop at
     while (last < n && P.events[last].kind != EV_END && !stops(P.events[last])) ++last;
     if (last >= n) return;
+    // past the limits nothing below is worth its time: a list has a test mask
+    // of all record words for each of its tests
+    const uint32_t rw = (P.n_rec + 31u) / 32u;
+    if (rw + 1u > kMaxOutWords) return;
     out.complete = P.events[last].kind == EV_END;
     std::vector<uint32_t> flip_of(P.n_rec, kNone);  // the noise slot that flips a record
     for (uint32_t s = 0; s < P.n_noise; ++s) {
@@ -96,7 +100,6 @@ void build_signs(const Program &P, SignProgram &out) {
     std::vector<Test> tests;
     std::vector<uint32_t> ref_bits;       // of the tests
     std::vector<Vec> mask;
-    const uint32_t rw = (P.n_rec + 31u) / 32u;
     Vec written(rw + 1u, 0u);             // records and observables so far
     uint32_t obs = 0, ne = 0;
     auto parity = [&](const Event &E) {
@@ -126,6 +129,7 @@ void build_signs(const Program &P, SignProgram &out) {
         const Event &E = P.events[e];
         if (E.noise_end < ne) return;  // (slots come in list order)
         ne = E.noise_end;
+        if (tests.size() > 32u * kMaxTestWords || out.coin_slot.size() > kMaxCoins) return;
         if (e == last) {
             if (!out.complete) add_test(e, -1, 1u, SGT_HAND, 0u);
             break;
@@ -194,7 +198,8 @@ void build_signs(const Program &P, SignProgram &out) {
         while (S.meas < out.meas.size() && out.meas[S.meas].gamma != ~0ull && !par64(out.meas[S.meas].gamma & S.beta))
             ++S.meas;
     const uint32_t nt = (uint32_t)tests.size(), tw = (nt + 31u) / 32u;
-    if (tw > kMaxTestWords || rw + 1u > kMaxOutWords || out.coin_slot.size() > kMaxCoins) return;
+    if (tw > kMaxTestWords || out.coin_slot.size() > kMaxCoins) return;
+    if ((uint64_t)P.n_noise * kSignVecs * (tw + rw + 1u) * sizeof(uint32_t) > kMaxSignBytes) return;
     out.tests.push_back(SignTest{P.n_noise, 0xFFFFFFFFu, SGT_NONE, 0u});
     mask.push_back(written);
     out.mask.swap(mask);

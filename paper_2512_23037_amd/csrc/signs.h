@@ -33,9 +33,14 @@ struct SignProgram {
     double breaks = 0.0;                      // about the T pairs that noise breaks per shot
 };
 
+// Signature vectors take at most this much: of a list here, of all lists of a
+// context in its launch's layout (16 words a vector: 350 000 noise slots; the
+// 42-qubit circuit has 2800).
+constexpr uint64_t kMaxSignBytes = 128ull << 20;
+
 // Build the sign program of the list P.  `on` stays false when the list has
-// more tests, records or coins than the tables hold, or a T pair whose two
-// gates are not the same Pauli in the frame.
+// more tests, records, coins or noise slots than the tables hold, or a T pair
+// whose two gates are not the same Pauli in the frame.  Throws std::bad_alloc.
 void build_signs(const Program &P, SignProgram &out);
 
 }  // namespace soft

@@ -297,7 +297,7 @@ constexpr double kSignFewBreaks = 1.0;
 
 // The sign pass's tables: every variant's sign program in the smallest common
 // vector size.
-int prepare_signs(soft_ctx *c) {
+int build_sign_tables(soft_ctx *c) {
     const size_t nv = c->vars.size();
     std::vector<SignProgram> sp(nv);
     c->sign_on = 0;
@@ -306,16 +306,36 @@ int prepare_signs(soft_ctx *c) {
     auto fits = [](const SignProgram &S, uint32_t k) {
         return S.need.tests <= kSignTestWords[k] && S.need.out() <= kSignOutWords[k];
     };
+    // (a mixture often holds one circuit at several rates: only the
+    // thresholds differ)
+    auto same_vecs = [](const SignProgram &A, const SignProgram &B) {
+        return A.on && A.need.tests == B.need.tests && A.vecs == B.vecs;
+    };
     for (size_t v = 0; v < nv; ++v) {
         const Variant &V = c->vars[v];
-        // (a mixture often holds one circuit at several rates: only the
-        // thresholds differ)
         build_signs(V.has_fast ? V.fast : V.prog, sp[v]);
         SignProgram &S = sp[v];
         S.on = S.on && fits(S, 3u) && (S.complete || S.ends >= kSignEndsGaps);
         if (!S.on || !S.complete || S.breaks > kSignFewBreaks) c->sign_few = false;
         if (!S.on) continue;
         while (!fits(S, c->sign_size)) ++c->sign_size;
+        c->sign_on = 1u;
+    }
+    if (!c->sign_on) return SOFT_OK;
+    // variants past the tables' limit run without it
+    uint64_t left = kMaxSignBytes;
+    c->sign_on = 0;
+    for (size_t v = 0; v < nv; ++v) {
+        SignProgram &S = sp[v];
+        if (!S.on) continue;
+        const bool shared = v > 0 && same_vecs(sp[v - 1], S);
+        const uint64_t bytes = shared ? 0u : S.slots.size() * kSignVecs * 4ull * (kSignTestWords[c->sign_size] + kSignOutWords[c->sign_size]);
+        S.on = bytes <= left;
+        if (!S.on) {
+            c->sign_few = false;
+            continue;
+        }
+        left -= bytes;
         c->sign_on |= 1u | ((S.complete || S.ends >= kSignEndsSlots) ? 2u : 0u);
     }
     if (!c->sign_on) return SOFT_OK;
@@ -357,8 +377,8 @@ int prepare_signs(soft_ctx *c) {
             d[RO - 1u] = m.back();
         }
         D.ref_vec = put(S.ref);
-        if (v > 0 && sp[v - 1].on && sp[v - 1].vecs == S.vecs && sp[v - 1].need.tests == S.need.tests) {
-            D.vec_off = desc[v - 1].vec_off;  // the same circuit at another rate
+        if (v > 0 && same_vecs(sp[v - 1], S)) {
+            D.vec_off = desc[v - 1].vec_off;
         } else {
             D.vec_off = (uint32_t)(vec.size() / W);
             const size_t w0 = S.ref.size(), k = S.vecs.size() / w0;
@@ -391,8 +411,7 @@ int prepare_signs(soft_ctx *c) {
                           put(test.data(), test.size() * sizeof(SignTest)), put(mask.data(), mask.size() * sizeof(uint32_t)),
                           put(coin.data(), coin.size() * sizeof(uint2)), put(desc.data(), nv * sizeof(SignDesc)),
                           put(pair.data(), pair.size() * sizeof(SignPair)), put(meas.data(), meas.size() * sizeof(SignMeas))};
-    int rc = renew(c, c->d_signs, all.size());
-    if (rc) return rc;
+    if (int rc = renew(c, c->d_signs, all.size())) return rc;
     HIPCHK(c, hipMemcpy(c->d_signs.p, all.data(), all.size(), hipMemcpyHostToDevice));
     SignParams &T = c->sign_tables;
     T.vecs = reinterpret_cast<const uint4 *>(c->d_signs.p + at[0]);
@@ -404,6 +423,21 @@ int prepare_signs(soft_ctx *c) {
     T.pairs = reinterpret_cast<const SignPair *>(c->d_signs.p + at[6]);
     T.meas = reinterpret_cast<const SignMeas *>(c->d_signs.p + at[7]);
     return SOFT_OK;
+}
+
+// The circuit runs without the sign pass too: where its tables find no memory,
+// on the host or the device, it does.
+void prepare_signs(soft_ctx *c) {
+    int rc = SOFT_ECAPACITY;
+    try {
+        rc = build_sign_tables(c);
+    } catch (const std::bad_alloc &) {
+    }
+    if (rc == SOFT_OK) return;
+    (void)hipGetLastError();
+    c->err.clear();
+    c->sign_on = 0;
+    c->sign_few = false;
 }
 
 // Upload the compiled variants as one set of tables: each variant's events,
@@ -495,7 +529,7 @@ int prepare(soft_ctx *c) {
     if (!bm.empty()) HIPCHK(c, hipMemcpy(c->d_bm.p, bm.data(), bm.size() * sizeof(BatchMember), hipMemcpyHostToDevice));
     if (!dg.empty()) HIPCHK(c, hipMemcpy(c->d_diag.p, dg.data(), dg.size() * sizeof(DiagInfo), hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(c->d_vars.p, vd.data(), vd.size() * sizeof(VariantDesc), hipMemcpyHostToDevice));
-    if ((rc = prepare_signs(c))) return rc;
+    prepare_signs(c);
     c->dirty = false;
     c->prefix_key.clear();
     return SOFT_OK;

@@ -246,3 +246,25 @@ def test_record_planes_of_a_longer_variant(mode):
     assert got[0][0].shape[0] > 4 and got[0][4] < got[1][4]
     for a, b in zip(got[0][:4], got[1][:4]):
         assert (a == b).all()
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_signature_tables_past_their_limit(mode):
+    # three circuits of 60 000 slots with the largest vectors, 46 MB each of
+    # the 134 allowed: the last one is left to the sampler
+    # (few hits: the signs decide nearly every shot of the others)
+    checks = rounds(100).split("MPP")[0]
+    texts = [checks + "H 5\n" * (60_000 + 10 * v) for v in range(3)]
+
+    def build():
+        ctx = soft.Context(0)
+        ctx.load_mixture(texts, [{k: 1e-5 if k == "p1" else 1e-7 for k in NOISE}] * 3, [700, 1400, 2000])
+        ctx.set_rng(3)
+        ctx.set_noise_mode(mode)
+        return ctx
+
+    both(build, 0, 2000)
+    ctx = build()
+    run_gpu(ctx, 0, 2000)
+    a, b, c = (ctx.counters(v)["events"] for v in range(3))
+    assert max(a, b) < 0.02 * c
