@@ -164,6 +164,14 @@ int fail(soft_ctx *c, int code, const std::string &msg) {
     return code;
 }
 
+// No C++ exception crosses the C boundary: what a call cannot hold on the host
+// is a capacity error (its text fits a string without allocation).
+int no_memory(soft_ctx *c) {
+    if (c) c->err = "no host memory";
+    return SOFT_ECAPACITY;
+}
+#define SOFT_GUARD(ctx) catch (const std::bad_alloc &) { return no_memory(ctx); }
+
 #define HIPCHK(ctx, expr)                                                                          \
     do {                                                                                           \
         hipError_t e_ = (expr);                                                                    \
@@ -1057,7 +1065,7 @@ void soft_destroy(soft_ctx *c) {
 
 const char *soft_last_error(const soft_ctx *c) { return c ? c->err.c_str() : g_create_error.c_str(); }
 
-int soft_load_circuit(soft_ctx *c, const char *text, size_t len) {
+int soft_load_circuit(soft_ctx *c, const char *text, size_t len) try {
     if (!c || (!text && len)) return fail(c, SOFT_EINVAL, "null argument");
     Variant V;
     V.text.assign(text ? text : "", len);
@@ -1071,9 +1079,9 @@ int soft_load_circuit(soft_ctx *c, const char *text, size_t len) {
     c->dirty = true;
     (void)hipSetDevice(c->device);
     return prepare(c);
-}
+} SOFT_GUARD(c)
 
-int soft_load_noise(soft_ctx *c, const soft_noise *m) {
+int soft_load_noise(soft_ctx *c, const soft_noise *m) try {
     if (!c || !m) return fail(c, SOFT_EINVAL, "null argument");
     if (c->mixture) return fail(c, SOFT_ESTATE, "a mixture carries one noise model per variant; load it again instead");
     NoiseModel nm;
@@ -1099,10 +1107,10 @@ int soft_load_noise(soft_ctx *c, const soft_noise *m) {
     if (!c->have_text) return SOFT_OK;
     (void)hipSetDevice(c->device);
     return prepare(c);
-}
+} SOFT_GUARD(c)
 
 int soft_load_mixture(soft_ctx *c, uint32_t n_variants, const char *const *texts, const size_t *lens,
-                      const soft_noise *models, const uint64_t *shot_ends) {
+                      const soft_noise *models, const uint64_t *shot_ends) try {
     if (!c || !texts || !lens || !models || !shot_ends) return fail(c, SOFT_EINVAL, "null argument");
     if (n_variants < 1 || n_variants > kMaxVariants)
         return fail(c, SOFT_EINVAL, "n_variants must be in 1.." + std::to_string(kMaxVariants));
@@ -1131,7 +1139,7 @@ int soft_load_mixture(soft_ctx *c, uint32_t n_variants, const char *const *texts
     c->dirty = true;
     (void)hipSetDevice(c->device);
     return prepare(c);
-}
+} SOFT_GUARD(c)
 
 int soft_set_rng(soft_ctx *c, uint64_t seed) {
     if (!c) return SOFT_EINVAL;
@@ -1225,7 +1233,7 @@ int soft_set_keep(soft_ctx *c, uint64_t shot_lo, uint32_t count) {
 }
 
 int soft_run(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes, uint32_t *status, uint32_t *abort_op,
-             uint32_t *obs, void *hip_stream) {
+             uint32_t *obs, void *hip_stream) try {
     if (!c) return SOFT_EINVAL;
     if (!status && n_shots) return fail(c, SOFT_EINVAL, "status_dev is required");
     HIPCHK(c, hipSetDevice(c->device));
@@ -1245,10 +1253,10 @@ int soft_run(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes, 
     Shape s = current_shape(c);
     if ((rc = check_shape(c, s))) return rc;
     return run_impl(c, shot0, n_shots, outcomes, status, abort_op, obs, (hipStream_t)hip_stream, s);
-}
+} SOFT_GUARD(c)
 
 int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes, uint32_t *status,
-                     uint32_t *abort_op, uint32_t *obs, void *hip_stream) {
+                     uint32_t *abort_op, uint32_t *obs, void *hip_stream) try {
     if (!c) return SOFT_EINVAL;
     if (!status && n_shots) return fail(c, SOFT_EINVAL, "status_dev is required");
     HIPCHK(c, hipSetDevice(c->device));
@@ -1330,7 +1338,7 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
     c->last_n = n_shots;
     c->last_list = false;
     return SOFT_OK;
-}
+} SOFT_GUARD(c)
 
 namespace {
 // Sum of the last run's counters over its variants [v0, v1) (maximum for the
@@ -1375,7 +1383,7 @@ int read_rows(soft_ctx *c, uint32_t v0, uint32_t v1, soft_counters *out) {
 }  // namespace
 
 int soft_run_list(soft_ctx *c, const uint64_t *shots_dev, uint64_t n_shots, uint32_t *outcomes, uint32_t *status,
-                  uint32_t *abort_op, uint32_t *obs, void *hip_stream) {
+                  uint32_t *abort_op, uint32_t *obs, void *hip_stream) try {
     if (!c) return SOFT_EINVAL;
     if (!status && n_shots) return fail(c, SOFT_EINVAL, "status_dev is required");
     if (!shots_dev && n_shots) return fail(c, SOFT_EINVAL, "shots_dev is required");
@@ -1388,20 +1396,20 @@ int soft_run_list(soft_ctx *c, const uint64_t *shots_dev, uint64_t n_shots, uint
     Shape s = current_shape(c, true);
     if ((rc = check_shape(c, s))) return rc;
     return run_impl(c, 0, n_shots, outcomes, status, abort_op, obs, (hipStream_t)hip_stream, s, shots_dev);
-}
+} SOFT_GUARD(c)
 
-int soft_read_counters(soft_ctx *c, soft_counters *out) {
+int soft_read_counters(soft_ctx *c, soft_counters *out) try {
     if (!c || !out) return fail(c, SOFT_EINVAL, "null argument");
     return read_rows(c, 0, c->last_vars, out);
-}
+} SOFT_GUARD(c)
 
-int soft_read_variant_counters(soft_ctx *c, uint32_t variant, soft_counters *out) {
+int soft_read_variant_counters(soft_ctx *c, uint32_t variant, soft_counters *out) try {
     if (!c || !out) return fail(c, SOFT_EINVAL, "null argument");
     if (variant >= c->vars.size()) return fail(c, SOFT_EINVAL, "no such variant");
     return read_rows(c, variant, variant + 1, out);
-}
+} SOFT_GUARD(c)
 
-int soft_read_coeffs(soft_ctx *c, uint64_t shot, uint64_t *alpha, double *re, double *im, uint32_t cap, uint32_t *count) {
+int soft_read_coeffs(soft_ctx *c, uint64_t shot, uint64_t *alpha, double *re, double *im, uint32_t cap, uint32_t *count) try {
     if (!c || !count) return fail(c, SOFT_EINVAL, "null argument");
     HIPCHK(c, hipSetDevice(c->device));
     std::vector<unsigned long long> meta;
@@ -1410,9 +1418,9 @@ int soft_read_coeffs(soft_ctx *c, uint64_t shot, uint64_t *alpha, double *re, do
     const Frame *f = kept_frame(c, shot, meta, tile, rc);
     if (!f) return rc;
     return decode_coeffs(c, *f, meta, tile, alpha, re, im, cap, count);
-}
+} SOFT_GUARD(c)
 
-int soft_read_tableau(soft_ctx *c, uint64_t shot, uint64_t *x, uint64_t *z, uint8_t *r) {
+int soft_read_tableau(soft_ctx *c, uint64_t shot, uint64_t *x, uint64_t *z, uint8_t *r) try {
     if (!c) return SOFT_EINVAL;
     HIPCHK(c, hipSetDevice(c->device));
     std::vector<unsigned long long> meta;
@@ -1422,7 +1430,7 @@ int soft_read_tableau(soft_ctx *c, uint64_t shot, uint64_t *x, uint64_t *z, uint
     if (!f) return rc;
     decode_tableau(*f, meta, x, z, r);
     return SOFT_OK;
-}
+} SOFT_GUARD(c)
 
 int soft_set_trace(soft_ctx *c, uint64_t shot, uint32_t steps) {
     if (!c) return SOFT_EINVAL;
@@ -1433,7 +1441,7 @@ int soft_set_trace(soft_ctx *c, uint64_t shot, uint32_t steps) {
 }
 
 int soft_read_trace(soft_ctx *c, uint32_t step, uint64_t info[6], uint64_t *x, uint64_t *z, uint8_t *r,
-                    uint64_t *alpha, double *re, double *im, uint32_t cap, uint32_t *count) {
+                    uint64_t *alpha, double *re, double *im, uint32_t cap, uint32_t *count) try {
     if (!c || !info) return fail(c, SOFT_EINVAL, "null argument");
     if (!c->ran || !c->trace_n || !c->trace_tile) return fail(c, SOFT_ESTATE, "no traced run");
     if (step >= c->trace_n) return fail(c, SOFT_EINVAL, "step beyond the traced range");
@@ -1463,7 +1471,7 @@ int soft_read_trace(soft_ctx *c, uint32_t step, uint64_t info[6], uint64_t *x, u
     rc = decode_coeffs(c, *f, meta, tile, alpha, re, im, cap, &cnt);
     if (count) *count = cnt;
     return rc;
-}
+} SOFT_GUARD(c)
 
 namespace {
 void program_info(const Program &P, uint64_t info[8]) {
@@ -1478,7 +1486,7 @@ void program_info(const Program &P, uint64_t info[8]) {
 }
 }  // namespace
 
-int soft_circuit_info(soft_ctx *c, uint64_t info[8]) {
+int soft_circuit_info(soft_ctx *c, uint64_t info[8]) try {
     if (!c || !info) return fail(c, SOFT_EINVAL, "null argument");
     (void)hipSetDevice(c->device);
     int rc = prepare(c);
@@ -1490,15 +1498,15 @@ int soft_circuit_info(soft_ctx *c, uint64_t info[8]) {
         for (int i = 0; i < 8; ++i) info[i] = std::max(info[i], vi[i]);
     }
     return SOFT_OK;
-}
+} SOFT_GUARD(c)
 
-int soft_variant_info(soft_ctx *c, uint32_t variant, uint64_t info[8]) {
+int soft_variant_info(soft_ctx *c, uint32_t variant, uint64_t info[8]) try {
     if (!c || !info) return fail(c, SOFT_EINVAL, "null argument");
     if (!c->have_text) return fail(c, SOFT_ESTATE, "no circuit loaded");
     if (variant >= c->vars.size()) return fail(c, SOFT_EINVAL, "no such variant");
     program_info(c->vars[variant].prog, info);
     return SOFT_OK;
-}
+} SOFT_GUARD(c)
 
 int soft_graph_info(soft_ctx *c, uint64_t out[2]) {
     if (!c || !out) return fail(c, SOFT_EINVAL, "null argument");
@@ -1507,7 +1515,7 @@ int soft_graph_info(soft_ctx *c, uint64_t out[2]) {
     return SOFT_OK;
 }
 
-int soft_launch_shape(soft_ctx *c, uint32_t out[5]) {
+int soft_launch_shape(soft_ctx *c, uint32_t out[5]) try {
     if (!c || !out) return fail(c, SOFT_EINVAL, "null argument");
     (void)hipSetDevice(c->device);
     int rc = prepare(c);
@@ -1519,9 +1527,9 @@ int soft_launch_shape(soft_ctx *c, uint32_t out[5]) {
     out[3] = wave_bytes(c, s);
     out[4] = s.gt;
     return SOFT_OK;
-}
+} SOFT_GUARD(c)
 
-int soft_autotune(soft_ctx *c, uint64_t sample_shots, void *hip_stream) {
+int soft_autotune(soft_ctx *c, uint64_t sample_shots, void *hip_stream) try {
     if (!c) return SOFT_EINVAL;
     if (sample_shots == 0) return fail(c, SOFT_EINVAL, "sample_shots must be > 0");
     HIPCHK(c, hipSetDevice(c->device));
@@ -1647,6 +1655,6 @@ int soft_autotune(soft_ctx *c, uint64_t sample_shots, void *hip_stream) {
     }
     c->ran = false;  // counters of the last sample run are not a user run
     return SOFT_OK;
-}
+} SOFT_GUARD(c)
 
 }  // extern "C"
