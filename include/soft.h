@@ -321,11 +321,14 @@ int soft_set_tile_memory(soft_ctx *ctx, int mode);
  * a grid of others (and, in automatic tile
  * mode, both tile placements) on `sample_shots` shots spread over the
  * variants, in one launch each (outputs discarded; the better of two timings
- * counts), and keep the fastest for this circuit, noise model and precision.
- * The result is cached for the process, keyed by the device (architecture
+ * counts), and keep the fastest for this circuit, noise model and precision:
+ * one shape for launches that sample every shot by its coefficients (shot
+ * lists, kept states, ...) and, where the sign pass runs
+ * (soft_set_shared_prefix), one for launches that take it.
+ * The results are cached for the process, keyed by the device (architecture
  * name and compute-unit count), the circuit (with a mixture's shot ranges),
- * precision, pruning threshold, support cap, tile placement and noise draws:
- * every context on such a device that loads the same circuit uses it.
+ * precision, pruning threshold, support cap, tile placement, noise draws and
+ * whether the sign pass runs: every context on such a device that loads the same circuit uses it.
  * Samples of 10^6 shots or more rank shapes reliably; small samples measure
  * launch overhead.  Runs on hip_stream and synchronizes it. */
 int soft_autotune(soft_ctx *ctx, uint64_t sample_shots, void *hip_stream);

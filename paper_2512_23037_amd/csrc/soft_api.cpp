@@ -59,8 +59,9 @@ constexpr uint64_t kMaxKeepBytes = 4ull << 30;
 // Autotuned launch shapes, shared by every context of the process: keyed by
 // the device (architecture name and compute-unit count) and by what changes
 // the timing of a circuit (its hash with the shot ranges, precision, pruning
-// threshold, support cap, tile placement and noise draws).
-typedef std::tuple<std::string, int, uint64_t, int, double, uint32_t, int, int> TuneKey;
+// threshold, support cap, tile placement, noise draws, and whether the sign
+// pass runs before the sampler: what is left to it then asks for other shapes).
+typedef std::tuple<std::string, int, uint64_t, int, double, uint32_t, int, int, bool> TuneKey;
 std::mutex g_tune_mu;
 std::map<TuneKey, Shape> g_tuned;
 
@@ -622,16 +623,16 @@ Shape default_shape(const soft_ctx *c, bool list) {
     return s;
 }
 
-TuneKey tune_key(const soft_ctx *c) {
+TuneKey tune_key(const soft_ctx *c, bool list) {
     return TuneKey(c->arch, c->num_cus, c->hash, c->bits, tau_of(c), c->support_cap,
-                   c->tile_mode | (int)(c->split_log2 << 8), c->noise_mode);
+                   c->tile_mode | (int)(c->split_log2 << 8), c->noise_mode, use_signs(c, list));
 }
 
 Shape current_shape(const soft_ctx *c, bool list = false) {
     Shape s = default_shape(c, list);
     {
         std::lock_guard<std::mutex> lock(g_tune_mu);
-        auto it = g_tuned.find(tune_key(c));
+        auto it = g_tuned.find(tune_key(c, list));
         if (it != g_tuned.end()) s = it->second;
     }
     if (c->tile_mode) {  // an explicit placement overrides a tuned one
@@ -880,11 +881,14 @@ int make_params(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcome
     return SOFT_OK;
 }
 
+// (`vars`: other shot ranges than the loaded ones)
 int run_impl(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes, uint32_t *status, uint32_t *abort_op,
-             uint32_t *obs, hipStream_t stream, const Shape &s, const uint64_t *shot_list = nullptr) {
+             uint32_t *obs, hipStream_t stream, const Shape &s, const uint64_t *shot_list = nullptr,
+             const VariantDesc *vars = nullptr) {
     RunParams rp;
     int rc = make_params(c, shot0, n_shots, outcomes, status, abort_op, obs, rp);
     if (rc) return rc;
+    if (vars) rp.vars = vars;
     rp.grab = s.grab;
     rp.shot_list = shot_list;
     if (c->trace_n)  // mark every trace step unwritten
@@ -994,6 +998,88 @@ void decode_tableau(const Frame &f, const std::vector<unsigned long long> &meta,
         }
     }
 }
+
+// Candidate shapes of a launch: the default first, then a grid of shapes per
+// tile placement (in automatic mode LDS when it fits, device memory, and splits
+// whose LDS part is 1/2, 1/4 or 1/8 of the tile).
+std::vector<Shape> shape_candidates(const soft_ctx *c, bool list) {
+    std::vector<Shape> cands;
+    cands.push_back(default_shape(c, list));
+    const uint32_t wpbs[3] = {1, 2, 4};
+    // (after the sign pass the groups follow from the launch: group_size)
+    std::vector<uint32_t> grabs = {16, 64};
+    if (use_signs(c, list)) grabs.resize(1);
+    std::vector<Shape> places;
+    if (c->tile_mode != 0) {
+        places.push_back(placement(c, list));
+        if (places[0].gt == TM_SPLIT && !c->split_log2)  // other LDS parts of the split
+            for (uint32_t d = 1; d <= 3; ++d) {
+                Shape p = places[0];
+                p.lds_log2 = c->kmax - d;
+                if (p.lds_log2 >= kSplitMinLog2 && p.lds_log2 != places[0].lds_log2) places.push_back(p);
+            }
+    } else {
+        const Shape lds_p;  // the whole tile in LDS, when a block holds it
+        if (wave_bytes(c, lds_p) <= (uint32_t)c->max_lds_block) places.push_back(lds_p);
+        Shape m;
+        m.gt = TM_MEM;
+        places.push_back(m);
+        for (uint32_t d = 1; d <= 3 && split_possible(c); ++d) {
+            Shape p;
+            p.gt = TM_SPLIT;
+            p.lds_log2 = c->kmax - d;
+            if (p.lds_log2 >= kSplitMinLog2) places.push_back(p);
+        }
+    }
+    for (const Shape &place : places) {
+        const uint32_t wb = wave_bytes(c, place);
+        for (uint32_t wpb : wpbs) {
+            if (wpb * wb > (uint32_t)c->max_lds_block) continue;
+            const uint32_t cap = place.gt == TM_MEM ? kMemTileWavesPerCu : kMaxWavesPerCu;
+            const uint32_t occ = std::max<uint32_t>(1u, std::min<uint32_t>(kLdsPerCu / (wpb * wb), cap / wpb));
+            std::vector<uint32_t> bpcs;
+            for (uint32_t d : {4u, 2u, 1u}) {
+                uint32_t v = std::max<uint32_t>(1u, occ / d);
+                if (std::find(bpcs.begin(), bpcs.end(), v) == bpcs.end()) bpcs.push_back(v);
+            }
+            for (uint32_t bpc : bpcs)
+                for (uint32_t grab : grabs) {
+                    Shape sh = place;
+                    sh.wpb = wpb;
+                    sh.bpc = bpc;
+                    sh.grab = grab;
+                    cands.push_back(sh);
+                }
+        }
+    }
+    return cands;
+}
+
+// What a tuning holds while it runs; given back at its end.
+struct TuneScope {
+    soft_ctx *c;
+    uint32_t keep_n;
+    uint32_t *status = nullptr;
+    uint64_t *list = nullptr;
+    VariantDesc *vars = nullptr;
+    hipEvent_t t0 = nullptr, t1 = nullptr;
+    hipStream_t st;
+    TuneScope(soft_ctx *c_, hipStream_t st_) : c(c_), keep_n(c_->keep_n), st(st_) { c->keep_n = 0; }
+    ~TuneScope() {
+        c->keep_n = keep_n;
+        (void)hipStreamSynchronize(st);
+        if (t0) (void)hipEventDestroy(t0);
+        if (t1) (void)hipEventDestroy(t1);
+        if (status) (void)hipFree(status);
+        if (list) (void)hipFree(list);
+        if (vars) (void)hipFree(vars);
+    }
+};
+
+// After the sign pass a launch is short, and what is left to the sampler a
+// small part of it: a shape replaces the default only where it is faster by
+// more than the runs of one shape differ (0.1 to 0.7%).
+constexpr float kTuneGain = 0.98f;
 
 }  // namespace
 
@@ -1536,123 +1622,73 @@ int soft_autotune(soft_ctx *c, uint64_t sample_shots, void *hip_stream) try {
     int rc = prepare(c);
     if (rc) return rc;
     if (c->words_dev) return fail(c, SOFT_ESTATE, "autotune runs on Philox draws; clear explicit uniforms first");
-    uint32_t *d_status_holder = nullptr;
     hipStream_t st = (hipStream_t)hip_stream;
+    TuneScope T(c, st);
     // The sample: the first shots of each variant's range, sample_shots in all,
-    // as one shot list so that every timing is a single launch.
+    // as one shot list so that every timing is a single launch.  Runs that take
+    // the sign pass, which lists do not, are timed with the variants' ranges
+    // shortened to the same numbers of shots.
     std::vector<uint64_t> list;
+    std::vector<uint64_t> ends;
     {
         const uint64_t per = std::max<uint64_t>(1, sample_shots / c->vars.size());
         uint64_t lo = 0;
         for (const Variant &V : c->vars) {
             const uint64_t n = std::min<uint64_t>(per, V.shot_end - lo);
             for (uint64_t i = 0; i < n; ++i) list.push_back(lo + i);
+            ends.push_back(list.size());
             lo = V.shot_end;
         }
     }
-    uint32_t *d_status = nullptr;
-    uint64_t *d_list = nullptr;
-    HIPCHK(c, hipMalloc((void **)&d_status, list.size() * sizeof(uint32_t)));
-    d_status_holder = d_status;
-    if (hipMalloc((void **)&d_list, list.size() * sizeof(uint64_t)) != hipSuccess ||
-        hipMemcpy(d_list, list.data(), list.size() * sizeof(uint64_t), hipMemcpyHostToDevice) != hipSuccess) {
-        (void)hipFree(d_status);
-        if (d_list) (void)hipFree(d_list);
-        return fail(c, SOFT_EDEVICE, "autotune: could not stage the shot list");
-    }
-    auto sample_pass = [&](const Shape &s) {
-        return run_impl(c, 0, list.size(), nullptr, d_status_holder, nullptr, nullptr, st, s, d_list);
-    };
-    hipEvent_t t0 = nullptr, t1 = nullptr;
-    HIPCHK(c, hipEventCreate(&t0));
-    HIPCHK(c, hipEventCreate(&t1));
-    const uint32_t keep_n = c->keep_n;
-    c->keep_n = 0;
-    // Candidates: the default shape first, then a grid of shapes per tile
-    // placement.  Each is run once untimed and twice timed; the faster timing
-    // counts, so one noisy launch cannot pick a worse shape than the default.
-    std::vector<Shape> cands;
-    cands.push_back(default_shape(c, true));
-    const uint32_t wpbs[3] = {1, 2, 4};
-    const uint32_t grabs[2] = {16, 64};
-    // placements: the one asked for; in auto mode LDS (when it fits), device
-    // memory, and splits whose LDS part is 1/2, 1/4 or 1/8 of the tile
-    std::vector<Shape> places;
-    if (c->tile_mode != 0) {
-        places.push_back(placement(c, true));
-        if (places[0].gt == TM_SPLIT && !c->split_log2)  // other LDS parts of the split
-            for (uint32_t d = 1; d <= 3; ++d) {
-                Shape p = places[0];
-                p.lds_log2 = c->kmax - d;
-                if (p.lds_log2 >= kSplitMinLog2 && p.lds_log2 != places[0].lds_log2) places.push_back(p);
-            }
-    } else {
-        const Shape lds_p;  // the whole tile in LDS, when a block holds it
-        if (wave_bytes(c, lds_p) <= (uint32_t)c->max_lds_block) places.push_back(lds_p);
-        Shape m;
-        m.gt = TM_MEM;
-        places.push_back(m);
-        for (uint32_t d = 1; d <= 3 && split_possible(c); ++d) {
-            Shape p;
-            p.gt = TM_SPLIT;
-            p.lds_log2 = c->kmax - d;
-            if (p.lds_log2 >= kSplitMinLog2) places.push_back(p);
-        }
-    }
-    for (const Shape &place : places) {
-        const uint32_t wb = wave_bytes(c, place);
-        for (uint32_t wpb : wpbs) {
-            if (wpb * wb > (uint32_t)c->max_lds_block) continue;
-            const uint32_t cap = place.gt == TM_MEM ? kMemTileWavesPerCu : kMaxWavesPerCu;
-            const uint32_t occ = std::max<uint32_t>(1u, std::min<uint32_t>(kLdsPerCu / (wpb * wb), cap / wpb));
-            std::vector<uint32_t> bpcs;
-            for (uint32_t d : {4u, 2u, 1u}) {
-                uint32_t v = std::max<uint32_t>(1u, occ / d);
-                if (std::find(bpcs.begin(), bpcs.end(), v) == bpcs.end()) bpcs.push_back(v);
-            }
-            for (uint32_t bpc : bpcs)
-                for (uint32_t grab : grabs) {
-                    Shape sh = place;
-                    sh.wpb = wpb;
-                    sh.bpc = bpc;
-                    sh.grab = grab;
-                    cands.push_back(sh);
-                }
-        }
-    }
-    Shape best = cands[0];
-    float best_ms = 1e30f;
-    for (const Shape &sh : cands) {
-        if (check_shape(c, sh) != SOFT_OK) continue;
-        rc = sample_pass(sh);  // untimed: caches
-        float ms = 1e30f;
-        for (int rep = 0; rep < 2 && !rc; ++rep) {
-            float t = 0.0f;
-            hipError_t e = hipEventRecord(t0, st);
-            if (e == hipSuccess) rc = sample_pass(sh);
-            if (!rc && e == hipSuccess) e = hipEventRecord(t1, st);
-            if (!rc && e == hipSuccess) e = hipEventSynchronize(t1);
-            if (!rc && e == hipSuccess) e = hipEventElapsedTime(&t, t0, t1);
-            if (!rc && e != hipSuccess) rc = fail(c, SOFT_EDEVICE, std::string("autotune timing: ") + hipGetErrorString(e));
-            if (!rc) ms = std::min(ms, t);
-        }
-        if (rc) break;
-        if (ms < best_ms) {
-            best_ms = ms;
-            best = sh;
-        }
-    }
-    c->keep_n = keep_n;
-    (void)hipEventDestroy(t0);
-    (void)hipEventDestroy(t1);
-    (void)hipStreamSynchronize(st);
-    (void)hipFree(d_status);
-    (void)hipFree(d_list);
-    if (rc) return rc;
+    const size_t nv = c->vars.size();
+    HIPCHK(c, hipMalloc((void **)&T.status, list.size() * sizeof(uint32_t)));
+    HIPCHK(c, hipMalloc((void **)&T.list, list.size() * sizeof(uint64_t)));
+    HIPCHK(c, hipMemcpy(T.list, list.data(), list.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
     {
-        std::lock_guard<std::mutex> lock(g_tune_mu);
-        g_tuned[tune_key(c)] = best;
+        std::vector<VariantDesc> vd(nv);
+        HIPCHK(c, hipMemcpy(vd.data(), c->d_vars.p, nv * sizeof(VariantDesc), hipMemcpyDeviceToHost));
+        for (size_t v = 0; v < nv; ++v) vd[v].shot_end = ends[v];
+        HIPCHK(c, hipMalloc((void **)&T.vars, nv * sizeof(VariantDesc)));
+        HIPCHK(c, hipMemcpy(T.vars, vd.data(), nv * sizeof(VariantDesc), hipMemcpyHostToDevice));
     }
+    HIPCHK(c, hipEventCreate(&T.t0));
+    HIPCHK(c, hipEventCreate(&T.t1));
+    auto sample_pass = [&](const Shape &s, bool by_list) {
+        return by_list ? run_impl(c, 0, list.size(), nullptr, T.status, nullptr, nullptr, st, s, T.list)
+                       : run_impl(c, 0, list.size(), nullptr, T.status, nullptr, nullptr, st, s, nullptr, T.vars);
+    };
+    // Each candidate is run once untimed and twice timed; the faster timing
+    // counts, so one noisy launch cannot pick a worse shape than the default.
+    auto tune = [&](bool by_list) {
+        const std::vector<Shape> cands = shape_candidates(c, by_list);
+        Shape best = cands[0];
+        float best_ms = 1e30f;
+        for (size_t i = 0; i < cands.size(); ++i) {
+            const Shape &sh = cands[i];
+            if (check_shape(c, sh) != SOFT_OK) continue;
+            int e = sample_pass(sh, by_list);  // untimed: caches
+            float ms = 1e30f;
+            for (int rep = 0; rep < 2 && !e; ++rep) {
+                float t = 0.0f;
+                HIPCHK(c, hipEventRecord(T.t0, st));
+                if ((e = sample_pass(sh, by_list))) break;
+                HIPCHK(c, hipEventRecord(T.t1, st));
+                HIPCHK(c, hipEventSynchronize(T.t1));
+                HIPCHK(c, hipEventElapsedTime(&t, T.t0, T.t1));
+                ms = std::min(ms, t);
+            }
+            if (e) return e;
+            if (ms < best_ms) {
+                best_ms = i == 0 && !by_list ? kTuneGain * ms : ms;
+                best = sh;
+            }
+        }
+        std::lock_guard<std::mutex> lock(g_tune_mu);
+        g_tuned[tune_key(c, by_list)] = best;
+        return (int)SOFT_OK;
+    };
+    if ((rc = tune(true))) return rc;
+    if (use_signs(c, false) && (rc = tune(false))) return rc;
     c->ran = false;  // counters of the last sample run are not a user run
     return SOFT_OK;
 } SOFT_GUARD(c)

@@ -119,8 +119,9 @@ hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCre
 hipError_t hipEventDestroy(hipEvent_t e) { std::free((void *)e); return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { ++g_clock; return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-// the first candidate is the fastest: later ones take longer
-hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { static float t = 1.0f; *ms = t += 0.001f; return hipSuccess; }
+// each timing takes g_step times the one before it
+static float g_ms = 1.0f, g_step = 1.001f;
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = g_ms *= g_step; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "hip error"; }
 }
@@ -312,6 +313,63 @@ int main(int argc, char **argv) {
         OK(soft_run(c, 0, 1000, nullptr, st.data(), nullptr, nullptr, nullptr));
         CHECK(kinds() == "brgs");
     }
+    else if (what == "autotune") {
+        // runs that take the sign pass are tuned with it, over the variants'
+        // first shots, and keep a shape of their own
+        OK(soft_set_noise_mode(c, 1));
+        OK(soft_set_precision(c, 64));
+        const bool single = std::atoi(argv[4]) == 1;
+        if (single) load(big);
+        else OK(mixture(8));
+        auto shape = [&](bool list) {  // grid, waves a block, tile placement of a run
+            g_launches.clear();
+            std::vector<uint64_t> which(800);
+            for (size_t i = 0; i < which.size(); ++i) which[i] = i;
+            if (list) OK(soft_run_list(c, which.data(), 800, nullptr, st.data(), nullptr, nullptr, nullptr));
+            else OK(soft_run(c, 0, 800, nullptr, st.data(), nullptr, nullptr, nullptr));
+            const Launch &L = g_launches.back();
+            CHECK(L.what == 's' && (kinds().find('g') != std::string::npos) != list);
+            CHECK((L.p.shot_list != nullptr) == list);
+            return std::vector<uint32_t>{L.grid, L.block, L.p.tile_mode, L.p.lds_entries};
+        };
+        const auto run0 = shape(false), list0 = shape(true);
+        // timings that get slower: the default stays, for each route
+        g_launches.clear();
+        OK(soft_autotune(c, 800, nullptr));
+        size_t with = 0, without = 0;
+        std::vector<uint32_t> first;
+        for (size_t i = 0; i < g_launches.size(); ++i) {
+            const Launch &L = g_launches[i];
+            if (L.what != 's') continue;
+            const bool signs = g_launches[i - 1].what == 'g';
+            CHECK(signs == (L.p.shot_list == nullptr) && signs == (L.p.signs != 0));
+            if (signs && first.empty()) first = {L.grid, L.block, L.p.tile_mode, L.p.lds_entries};
+            (signs ? with : without)++;
+            CHECK(L.p.n_shots == 800);
+            if (signs && !single) {
+                CHECK(g_launches[i - 1].sp.vars == L.p.vars);
+            }
+        }
+        CHECK(with >= 30 && without >= 30 && first == run0);
+        CHECK(shape(false) == run0 && shape(true) == list0);
+        // a gain within the noise of a timing: the default stays where the pass runs
+        g_step = 0.99995f;
+        OK(soft_autotune(c, 800, nullptr));
+        CHECK(shape(false) == run0 && shape(true) != list0);
+        // timings that get faster: the last candidate of each route
+        g_step = 0.99f;
+        g_ms = 1.0f;
+        OK(soft_autotune(c, 800, nullptr));
+        const auto run1 = shape(false), list1 = shape(true);
+        CHECK(run1 != run0 && list1 != list0);
+        // kept states leave the pass out: the shape of the other route
+        OK(soft_set_keep(c, 0, 4));
+        OK(soft_run(c, 0, 800, nullptr, st.data(), nullptr, nullptr, nullptr));
+        const Launch &L = g_launches.back();
+        CHECK((std::vector<uint32_t>{L.grid, L.block, L.p.tile_mode, L.p.lds_entries}) == list1);
+        OK(soft_set_keep(c, 0, 0));
+        CHECK(shape(false) == run1);
+    }
     soft_destroy(c);
     CHECK(g_live.empty());
     return 0;
@@ -353,6 +411,11 @@ def test_recorded_addresses_stay(driver, how, tiles):
 
 def test_counter_reads_stay_in_the_last_runs_rows(driver):
     go(driver, "counters")
+
+
+@pytest.mark.parametrize("single", ["0", "1"])
+def test_autotune_times_the_routes_that_runs_take(driver, single):
+    go(driver, "autotune", single)
 
 
 def test_failing_host_allocations(driver):
