@@ -8,9 +8,12 @@ every input resident on the GPU.  The headline runs FP32 coefficients (FP64
 probabilities and renormalisation); the FP64-coefficient run of the same
 workload is reported beside it.
 
-Outside the timed region each precision also samples shots 0..9999 with their
-final states kept; the CPU-baseline leg times the oracle on the host and
-compares those shots with it (records, statuses, tableaux, coefficient error).
+Outside the timed region each precision runs the timed launch once more from
+shot 0 and keeps its first outputs, and samples shots 0..9999 with their final
+states kept (a launch without the sign pass: every shot by its coefficients).
+The CPU-baseline leg times the oracle on the host and compares both with it:
+records, statuses, abort ops and observables of the timed launch's shots, and
+with the kept states also tableaux and the coefficient error.
 
 Prints one JSON line.  --gpus N > 1 is refused: the benchmark runs on one GPU.
 """
@@ -50,7 +53,7 @@ FP_M_PAIR = 4            # per representative pair of a beta != 0 measurement: w
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "sampler_cultivation_42q_traffic.json")
 PROFILE_ISSUE = os.path.join(ROOT, "profiles", "sampler_cultivation_42q_issue.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2512_23037_amd", "csrc", f)
-                  for f in ("sampler.hip", "signs.hip", "device.h", "program.h", "sampler.h")]
+                  for f in ("sampler.hip", "signs.hip", "device.h", "queue.h", "program.h", "sampler.h")]
 
 
 def kernel_hash() -> str:
@@ -98,13 +101,26 @@ def time_steps(torch, ctx, shots, steps, warmup, bufs):
     return e0.elapsed_time(e1) / steps, wall
 
 
+def first_outputs(torch, bufs, n):
+    """The first n shots of a launch's outputs, on the host."""
+    torch.cuda.synchronize()
+    outcomes, status, abort_op, obs = (b[..., :n].cpu().numpy().view(np.uint32) for b in bufs)
+    return {"outcomes": outcomes, "status": status, "abort_op": abort_op, "obs": obs}
+
+
+def timed_subset(torch, ctx, shots, bufs, n):
+    """Shots 0..n-1 as a timed step computes them: the same launch, from shot 0."""
+    for b in bufs:
+        b.fill_(-7)
+    ctx.run(0, shots, *bufs, stream=torch.cuda.current_stream())
+    return first_outputs(torch, bufs, n)
+
+
 def sample_subset(torch, soft, ctx, n):
     """Shots 0..n-1 with their final states kept (outside the timed region)."""
     ctx.set_keep(0, n)
-    outcomes, status, abort_op, obs = soft.sample(ctx, 0, n)
-    torch.cuda.synchronize()
-    sub = {"status": status.cpu().numpy().view(np.uint32), "abort_op": abort_op.cpu().numpy().view(np.uint32),
-           "obs": obs.cpu().numpy().view(np.uint32), "outcomes": outcomes.cpu().numpy().view(np.uint32)}
+    sub = first_outputs(torch, soft.sample(ctx, 0, n), n)
+    sub["max_norm_dev"] = ctx.counters()["max_norm_dev"]
     sub["coeffs"] = [ctx.read_coeffs(s) for s in range(n)]
     sub["tableau"] = [ctx.read_tableau(s) for s in range(n)]
     ctx.set_keep(0, 0)
@@ -118,22 +134,20 @@ def coeff_error(got: dict, ref: dict) -> float:
     return max([abs(got.get(k, 0) - ref.get(k, 0)) for k in keys] + [0.0]) / norm
 
 
-def compare_with_oracle(oracle, circ, ref, sub, bits, threads):
-    """The GPU's shots 0..n-1 against the oracle's: records, statuses, abort
-    ops and observables bit for bit (FP32: a shot may take the other branch
-    only where a draw lies within 1e-5 of the oracle's probability), tableaux
-    bit for bit and the coefficient error on every shot that agrees."""
-    from concurrent.futures import ThreadPoolExecutor
+def differing(sub, ref):
+    """Mask of the shots whose record, status, abort op or observables differ."""
     n = len(sub["status"])
     nw = ref["outcomes"].shape[0]
-    diff = ((sub["status"] != ref["status"][:n]) | (sub["abort_op"] != ref["abort_op"][:n]) |
+    return ((sub["status"] != ref["status"][:n]) | (sub["abort_op"] != ref["abort_op"][:n]) |
             (sub["obs"] != ref["obs"][:n]) | (sub["outcomes"][:nw] != ref["outcomes"][:, :n]).any(axis=0))
-    tau = 1e-12 if bits == 64 else 1e-6
-    with ThreadPoolExecutor(max_workers=threads) as pool:
-        shots = list(pool.map(lambda s: circ.shot(SEED_RNG, s, tau=tau), range(n)))
+
+
+def in_guard_band(oracle, circ, diff, shot):
+    """Differing shots with a draw within 1e-5 of the oracle's probability,
+    where an FP32 run may take the other branch."""
     in_band = 0
     for s in np.nonzero(diff)[0]:
-        r = shots[s]
+        r = shot(int(s))
         near = False
         for slot in range(circ.n_meas_slots):
             if np.isnan(r.p0[slot]):
@@ -141,6 +155,30 @@ def compare_with_oracle(oracle, circ, ref, sub, bits, threads):
             blk = oracle.philox([slot >> 2, int(s), 0, 1], [SEED_RNG & 0xFFFFFFFF, SEED_RNG >> 32])
             near |= abs((float(blk[slot & 3]) + 0.5) / 2 ** 32 - r.p0[slot]) < 1e-5
         in_band += int(near)
+    return in_band
+
+
+def compare_timed(oracle, circ, ref, sub, bits):
+    """The timed launch's first shots against the oracle's, bit for bit (FP32:
+    but for the other branch of a draw in the guard band)."""
+    diff = differing(sub, ref)
+    tau = 1e-12 if bits == 64 else 1e-6
+    in_band = in_guard_band(oracle, circ, diff, lambda s: circ.shot(SEED_RNG, s, tau=tau))
+    return {"shots": len(diff), "shots_identical": int((~diff).sum()), "outcome_flips": int(diff.sum()),
+            "outcome_flips_outside_guard_band": int(diff.sum()) - in_band, "passed": int((sub["status"] == 0).sum())}
+
+
+def compare_with_oracle(oracle, circ, ref, sub, bits, threads):
+    """The GPU's kept shots 0..n-1 against the oracle's: records, statuses,
+    abort ops and observables bit for bit (FP32: but for the guard band),
+    tableaux bit for bit and the coefficient error on every shot that agrees."""
+    from concurrent.futures import ThreadPoolExecutor
+    n = len(sub["status"])
+    diff = differing(sub, ref)
+    tau = 1e-12 if bits == 64 else 1e-6
+    with ThreadPoolExecutor(max_workers=threads) as pool:
+        shots = list(pool.map(lambda s: circ.shot(SEED_RNG, s, tau=tau), range(n)))
+    in_band = in_guard_band(oracle, circ, diff, lambda s: shots[s])
     errs, tab_bad = [], 0
     for s in range(n):
         if diff[s]:
@@ -155,16 +193,17 @@ def compare_with_oracle(oracle, circ, ref, sub, bits, threads):
     return {"shots": n, "shots_identical": int(ok.sum()), "outcome_flips": int(diff.sum()),
             "outcome_flips_in_guard_band": in_band, "outcome_flips_outside_guard_band": int(diff.sum()) - in_band,
             "tableau_mismatches": tab_bad, "kept_shots_compared": len(errs),
-            "max_coeff_err": float(max(errs)) if errs else None,
+            "max_coeff_err": float(max(errs)) if errs else None, "max_norm_dev": sub["max_norm_dev"],
             "ler": float((passed_g & (sub["obs"] != 0)).sum() / max(1, passed_g.sum())),
             "ler_oracle": float((passed_o & (ref["obs"][:n] != 0)).sum() / max(1, passed_o.sum())),
             "passed": int(passed_g.sum())}
 
 
-def cpu_baseline(w, shots_sample: int, noise_mode: int, subsets: dict):
+def cpu_baseline(w, shots_sample: int, noise_mode: int, subsets: dict, timed: dict):
     """The oracle on the host: its throughput on shots 0..shots_sample-1 (the
     baseline), its work counts and their shared-trajectory part (the
-    roofline's units), and the comparison of the GPU's kept subsets with it."""
+    roofline's units), and the comparison of the GPU's shots with it, the timed
+    launch's and the kept ones."""
     import oracle
     oracle.build(force=False)
     circ = oracle.Circuit(w.text, w.noise, noise_mode=noise_mode)
@@ -176,6 +215,8 @@ def cpu_baseline(w, shots_sample: int, noise_mode: int, subsets: dict):
             "sample": "shots 0..%d of the same workload (seed %d), %d host threads, %.1f s wall"
                       % (shots_sample - 1, SEED_RNG, threads, dt)}
     checks = {bits: compare_with_oracle(oracle, circ, r, sub, bits, threads) for bits, sub in subsets.items()}
+    for bits, sub in timed.items():
+        checks[bits]["timed_launch"] = compare_timed(oracle, circ, r, sub, bits)
     return base, (r["work"], r["shared_work"]), shots_sample, checks
 
 
@@ -433,6 +474,8 @@ def main():
         ms, wall = time_steps(torch, ctx, shots, args.steps, args.warmup, bufs)
         c = ctx.counters()   # counters of the last timed step
         results[bits] = {"ms": ms, "wall": wall, "counters": c, "shape": ctx.launch_shape()}
+        if subset:
+            results[bits]["timed"] = timed_subset(torch, ctx, shots, bufs, min(args.cpu_sample, shots))
         del bufs
         if subset:
             results[bits]["subset"] = sample_subset(torch, soft, ctx, subset)
@@ -475,8 +518,9 @@ def main():
                    "circuit": stats_tab, "launch": r32["shape"]},
         "stats": {"passed": c["passed"], "discarded": c["discarded"], "overflow": c["overflow"],
                   "numeric": c["numeric"], "logical_errors": c["logical_errors"],
-                  "discard_rate": c["discarded"] / max(1, c["shots"]), "max_norm_dev": c["max_norm_dev"],
-                  "restarts": c["restarts"]},
+                  "discard_rate": c["discarded"] / max(1, c["shots"]), "restarts": c["restarts"],
+                  # over the shots that the sampler kernel ran: the sign pass computes no coefficients
+                  "max_norm_dev_sampler_shots": c["max_norm_dev"], "coefficient_entries": c["entries_t"] + c["entries_m"]},
     }
     if long_leg is not None:
         out["fp32_at_paper_discard_rate"] = long_leg
@@ -485,12 +529,16 @@ def main():
         v64 = shots / (r64["ms"] / 1e3)
         c64 = r64["counters"]
         out["fp64"] = {"value": v64, "ms_per_step": r64["ms"], "launch": r64["shape"], "fp32_speedup": value / v64,
-                       "ler": c64["logical_errors"] / max(1, c64["passed"]), "max_norm_dev": c64["max_norm_dev"]}
+                       "ler": c64["logical_errors"] / max(1, c64["passed"]), "max_norm_dev_sampler_shots": c64["max_norm_dev"],
+                       "coefficient_entries": c64["entries_t"] + c64["entries_m"],
+                       "fp32_speedup_note": "both launches touch coefficients only in the shots that the sign pass leaves "
+                                            "to the sampler (coefficient_entries)"}
         out["stats"]["ler"] = c["logical_errors"] / max(1, c["passed"])
 
     if not args.no_cpu_baseline:
         subsets = {bits: r["subset"] for bits, r in results.items() if "subset" in r}
-        base, work, nsample, checks = cpu_baseline(w, args.cpu_sample, args.noise_mode, subsets)
+        timed = {bits: r["timed"] for bits, r in results.items() if "timed" in r}
+        base, work, nsample, checks = cpu_baseline(w, args.cpu_sample, args.noise_mode, subsets, timed)
         out["cpu_baseline"] = base
         out["fp32_vs_oracle"] = checks.get(32)
         if 64 in checks:

@@ -79,7 +79,9 @@ typedef struct {
                                     T run skipped counts the supports it computed, and one
                                     that the tableau signs decide the checkpoint's before its
                                     first noise hit) */
-    double max_norm_dev;         /* max over shots of |sum |v|^2 - 1| at the end */
+    double max_norm_dev;         /* max of |sum |v|^2 - 1| at the end over the shots that the
+                                    sampler ran (a shot that the tableau signs decide has no
+                                    coefficients; soft_set_keep samples every shot by them) */
     uint64_t restarts;           /* shots where noise broke a T / T-dagger cancellation of the
                                     speculative list: re-run on the full event list, its
                                     span truncation having found amplitude left, or
