@@ -568,26 +568,39 @@ __device__ __forceinline__ uint32_t t_double(const Tile<C, TM> &v, uint32_t lane
     (((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)evx, (int)(offsetof(Event, f) / 4u + 1u)) << 32) | \
      (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)evx, (int)(offsetof(Event, f) / 4u)))
 
-// LEAN: a launch with no kept states, no trace, no support cap and no shot
-// list (and never the prefix build); those paths compile out, which frees
-// scalar registers in the event loop.
+// What every sampling and build kernel takes, and where the last argument of
+// such a kernel lies in its argument segment (each on its own alignment, one
+// after the other).
+typedef void SampleKernel(const Event *, const NoiseLoc *, const uint32_t *, const uint32_t *, const uint32_t *,
+                          const BatchMember *, RunParams);
+template <typename... A> constexpr size_t last_argument(void (*)(A...)) {
+    size_t at = 0, last = 0;
+    ((last = (at + alignof(A) - 1u) / alignof(A) * alignof(A), at = last + sizeof(A)), ...);
+    return last;
+}
+constexpr size_t kRunParamsAt = last_argument((SampleKernel *)nullptr);
+// Kernel addresses are only taken through this, so that one with other
+// arguments does not compile.
+const void *address_of(SampleKernel *k) { return (const void *)k; }
+
 // The launch's parameters, read again where they are used: kept in scalar
 // registers over a shot they spilled to lanes, which every use then reads back
 // with vector instructions.
 typedef const __attribute__((address_space(4))) RunParams ConstRun;
 __device__ __forceinline__ ConstRun &args() {
-    // the kernels' seventh argument, after six pointers
     typedef const __attribute__((address_space(4))) unsigned char ConstByte;
-    ConstByte *p = (ConstByte *)__builtin_amdgcn_kernarg_segment_ptr() + 6u * sizeof(void *);
+    ConstByte *p = (ConstByte *)__builtin_amdgcn_kernarg_segment_ptr() + kRunParamsAt;
     asm volatile("" : "+s"(p));
     return *(ConstRun *)p;
 }
 
+// LEAN: a launch with no kept states, no trace, no support cap and no shot
+// list (and never the prefix build); those paths compile out, which frees
+// scalar registers in the event loop.
 template <typename R, uint32_t NS, uint32_t TM, bool LEAN = false>
 __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz,
                                              const uint32_t *__restrict__ tm1, const uint32_t *__restrict__ det,
-                                             const uint32_t *__restrict__ words, const BatchMember *__restrict__ bm,
-                                             const RunParams &) {
+                                             const uint32_t *__restrict__ words, const BatchMember *__restrict__ bm) {
     typedef typename Cx<R>::T C;
     constexpr bool EXPL = NS == NS_EXPLICIT, GAPS = NS == NS_GAPS;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1971,16 +1984,16 @@ template <uint32_t NS, uint32_t TM, bool LEAN>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8)))
 k_sample_f32(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz, const uint32_t *__restrict__ tm1,
              const uint32_t *__restrict__ det, const uint32_t *__restrict__ words, const BatchMember *__restrict__ bm,
-             RunParams P) {
-    sample_shots<float, NS, TM, LEAN>(ev, nz, tm1, det, words, bm, P);
+             RunParams) {
+    sample_shots<float, NS, TM, LEAN>(ev, nz, tm1, det, words, bm);
 }
 
 template <uint32_t NS, uint32_t TM, bool LEAN>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves64<NS, TM, LEAN>, 8)))
 k_sample_f64(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz, const uint32_t *__restrict__ tm1,
              const uint32_t *__restrict__ det, const uint32_t *__restrict__ words, const BatchMember *__restrict__ bm,
-             RunParams P) {
-    sample_shots<double, NS, TM, LEAN>(ev, nz, tm1, det, words, bm, P);
+             RunParams) {
+    sample_shots<double, NS, TM, LEAN>(ev, nz, tm1, det, words, bm);
 }
 
 // The shared-prefix build (RunParams::prefix_build): the same per-shot code
@@ -1990,16 +2003,16 @@ template <uint32_t TM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8)))
 k_prefix_f32(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz, const uint32_t *__restrict__ tm1,
              const uint32_t *__restrict__ det, const uint32_t *__restrict__ words, const BatchMember *__restrict__ bm,
-             RunParams P) {
-    sample_shots<float, NS_SLOTS, TM>(ev, nz, tm1, det, words, bm, P);
+             RunParams) {
+    sample_shots<float, NS_SLOTS, TM>(ev, nz, tm1, det, words, bm);
 }
 
 template <uint32_t TM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_prefix_f64(const Event *__restrict__ ev, const NoiseLoc *__restrict__ nz, const uint32_t *__restrict__ tm1,
              const uint32_t *__restrict__ det, const uint32_t *__restrict__ words, const BatchMember *__restrict__ bm,
-             RunParams P) {
-    sample_shots<double, NS_SLOTS, TM>(ev, nz, tm1, det, words, bm, P);
+             RunParams) {
+    sample_shots<double, NS_SLOTS, TM>(ev, nz, tm1, det, words, bm);
 }
 
 __global__ void k_reset(unsigned long long *counters, uint32_t n, unsigned long long *next) {
@@ -2012,8 +2025,8 @@ __global__ void k_clear(unsigned long long *p, uint64_t n) {
 }
 
 template <typename R, uint32_t NS, uint32_t TM, bool LEAN> const void *kernel_ptr() {
-    if (sizeof(R) == 4) return (const void *)k_sample_f32<NS, TM, LEAN>;
-    return (const void *)k_sample_f64<NS, TM, LEAN>;
+    if (sizeof(R) == 4) return address_of(k_sample_f32<NS, TM, LEAN>);
+    return address_of(k_sample_f64<NS, TM, LEAN>);
 }
 
 // The 18 full instantiations, indexed by fp64 * 9 + source * 3 + tile mode,
@@ -2079,9 +2092,9 @@ const void *sampler_kernel(bool fp64, uint32_t ns, uint32_t tm, bool lean) {
 }
 
 const void *prefix_kernel(bool fp64, uint32_t tm) {
-    const void *ks[6] = {(const void *)k_prefix_f32<TM_LDS>, (const void *)k_prefix_f32<TM_MEM>,
-                         (const void *)k_prefix_f32<TM_SPLIT>, (const void *)k_prefix_f64<TM_LDS>,
-                         (const void *)k_prefix_f64<TM_MEM>, (const void *)k_prefix_f64<TM_SPLIT>};
+    const void *ks[6] = {address_of(k_prefix_f32<TM_LDS>), address_of(k_prefix_f32<TM_MEM>),
+                         address_of(k_prefix_f32<TM_SPLIT>), address_of(k_prefix_f64<TM_LDS>),
+                         address_of(k_prefix_f64<TM_MEM>), address_of(k_prefix_f64<TM_SPLIT>)};
     return ks[(fp64 ? 3 : 0) + (tm > TM_SPLIT ? TM_LDS : tm)];
 }
 
