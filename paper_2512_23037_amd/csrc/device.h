@@ -91,22 +91,24 @@ __device__ __forceinline__ uint32_t quot16(uint64_t x, uint64_t d) {
     return m;
 }
 
-// The next of a launch's items [0, n) for this wave (queue.h; all lanes
-// active); false when there is none.  `started` is its state, false at first.
+// The next of a launch's items [0, n) for this wave (queue.h, 2^shift() cursors,
+// asked for where one is drawn from; all lanes active); false when there is
+// none.  `started` is its state, false at first.
+template <typename S>
 __device__ __forceinline__ bool take_item(unsigned long long *cursors, uint64_t n, uint32_t wave, uint32_t waves,
-                                          uint32_t lane, bool &started, uint64_t &item) {
+                                          S shift, uint32_t lane, bool &started, uint64_t &item) {
     if (!started) {
         started = true;
         item = wave;
         return item < n;
     }
     if (n <= waves) return false;
-    const uint32_t id = queue_cursor(wave, waves);
+    const uint32_t s = shift(), id = queue_cursor(wave, s);
     unsigned long long c = 0;
     if (lane == 0) c = atomicAdd(cursors + id * kCursorStride, 1ull);
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)c);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(c >> 32));
-    item = queue_item(id, ((uint64_t)hi << 32) | lo, waves);
+    item = queue_item(id, ((uint64_t)hi << 32) | lo, waves, s);
     return item < n;
 }
 

@@ -58,6 +58,7 @@ struct RunParams {
     uint32_t prefix_stride;   // bytes per prefix slot
     uint32_t signs;           // 1: the sign pass ran; only the shots whose status is pending are left
     uint32_t defer;           // 1: skip deferrable T runs (EVF_DEFER) until an event needs their tile
+    uint32_t queue_shift;     // log2 of the work cursors drawn from (queue.h)
     double tau2;              // pruning threshold squared
 };
 

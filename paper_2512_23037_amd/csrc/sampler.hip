@@ -704,7 +704,7 @@ __device__ __forceinline__ void sample_shots(const Event *__restrict__ ev, const
             if (group_rest == 0u) {
                 uint64_t item;
                 if (!take_item(args().next, (args().n_shots + args().grab - 1u) / args().grab, uni((uint32_t)gwave),
-                               gridDim.x * (blockDim.x >> 6), lane, started, item))
+                               gridDim.x * (blockDim.x >> 6), []() { return args().queue_shift; }, lane, started, item))
                     break;
                 group_base = item * args().grab;
                 group_rest = (uint32_t)min((uint64_t)args().grab, args().n_shots - group_base);

@@ -369,7 +369,9 @@ __global__ void __launch_bounds__(kSignBlock) __attribute__((amdgpu_waves_per_eu
             if (rest == 0u && !dry) {
                 ConstParams *A = args();
                 uint64_t got;
-                dry = !take_item(A->next, (A->n_shots + A->chunk - 1u) / A->chunk, blockIdx.x, gridDim.x, lane, started, got);
+                // (more chunks than waves only where the grid fills the device: sign_params)
+                dry = !take_item(A->next, (A->n_shots + A->chunk - 1u) / A->chunk, blockIdx.x, gridDim.x,
+                                 []() { return kQueueShift; }, lane, started, got);
                 if (!dry) {
                     cur = got * A->chunk;
                     rest = (uint32_t)min((uint64_t)A->chunk, A->n_shots - cur);

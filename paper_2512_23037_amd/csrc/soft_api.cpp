@@ -250,6 +250,7 @@ RunParams build_params(const RunParams &rp) {
     b.trace_v = nullptr;
     b.trace_n = 0;
     b.grab = 1;
+    b.queue_shift = 0;
     b.next = rp.next + kBuildCursor;
     return b;
 }
@@ -713,6 +714,8 @@ uint32_t sign_params(const soft_ctx *c, const RunParams &rp, SignParams &sp) {
     const bool gaps = rp.noise_mode == 1u;
     const uint64_t held = gaps ? 64u : 4u, share = rp.n_shots / (most * held);
     sp.chunk = (uint32_t)(held * std::max<uint64_t>(1u, gaps ? std::min<uint64_t>(4u, share) : std::min<uint64_t>(16u, share / 8u)));
+    // (the kernel draws from eight cursors where the chunks outnumber its waves)
+    static_assert(kSignWavesPerCu[3] >= kQueueCursors, "a wave on every cursor");
     return (uint32_t)std::min<uint64_t>(most, (rp.n_shots + sp.chunk - 1u) / sp.chunk);
 }
 
@@ -734,6 +737,18 @@ uint32_t group_size(const soft_ctx *c, const Shape &s, uint64_t grid, uint64_t n
     }
     if (signs) return (uint32_t)each;
     return (uint32_t)(each < 4u ? each : std::min<uint64_t>(s.grab, each / 4u));
+}
+
+// Cursors of the sampler's queue.  Without the sign pass a shot takes long, and
+// groups of eight or more (32 shots a wave) come from one cursor, which keeps
+// every wave at work to the end: span-12 lists in circuit order 16.2 -> 15.3 ms
+// (2.4 10^5 shots), 42 qubits in device-memory tiles 29.6 -> 27.8 (10^6), 15
+// qubits with kept states 1.58 -> 1.56 (6.6 10^5), 8 qubits the same.  Below
+// that its atomics count: 15 qubits 0.28 -> 0.34 ms at 15 shots a wave, 8
+// qubits 0.23 -> 0.29.
+constexpr uint32_t kOneCursorGroup = 8;
+uint32_t cursor_shift(const RunParams &rp, uint64_t waves, bool signs) {
+    return !signs && rp.grab >= kOneCursorGroup ? 0u : queue_shift((uint32_t)std::min<uint64_t>(waves, kQueueCursors));
 }
 
 // The launches of a run, one after the other on `stream`: the checkpoint build
@@ -785,6 +800,7 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
     if (captured) mark_recorded(c);
     const bool sgn = use_signs(c, rp.shot_list != nullptr);
     rp.grab = group_size(c, s, grid, n_shots, sgn);
+    rp.queue_shift = cursor_shift(rp, grid * s.wpb, sgn);
     // another stream than the last launch's: after it, for the states it built
     if (!captured && c->done && stream != c->done_stream) HIPCHK(c, hipStreamWaitEvent(stream, c->done, 0));
     if (build) {
@@ -1407,6 +1423,7 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
                                  dim3(64u * s.wpb), (size_t)s.wpb * wave_bytes(c, s), stream));
     const bool sgn = use_signs(c, rp.shot_list != nullptr);
     rp.grab = group_size(c, s, grid, n_shots, sgn);
+    rp.queue_shift = cursor_shift(rp, grid * s.wpb, sgn);
     if (sgn) {
         rp.signs = 1;
         SignParams sp;

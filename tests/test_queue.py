@@ -23,15 +23,19 @@ DRIVER = r"""
 static uint32_t cursor(uint32_t w, uint32_t) { return w % 8u; }
 static uint64_t nth(uint32_t id, uint64_t c, uint32_t waves) { return ((waves - id + 7u) / 8u + c) * 8u + id; }
 #else
-static uint32_t cursor(uint32_t w, uint32_t waves) { return soft::queue_cursor(w, waves); }
-static uint64_t nth(uint32_t id, uint64_t c, uint32_t waves) { return soft::queue_item(id, c, waves); }
+static uint32_t g_shift;
+static uint32_t cursor(uint32_t w, uint32_t) { return soft::queue_cursor(w, g_shift); }
+static uint64_t nth(uint32_t id, uint64_t c, uint32_t waves) { return soft::queue_item(id, c, waves, g_shift); }
 #endif
-// args: waves, items, seed; prints the items taken, and those taken more than once
+// args: waves, items, seed, one (1: one cursor); prints the items taken, and those taken more than once
 int main(int, char **argv) {
     const uint32_t waves = (uint32_t)atoi(argv[1]);
     const uint64_t n = (uint64_t)atoll(argv[2]);
     uint64_t x = 0x9E3779B97F4A7C15ull * (uint64_t)(atoi(argv[3]) + 1);
     std::vector<uint32_t> taken(n, 0u), live;
+#ifndef ALWAYS_EIGHT
+    g_shift = atoi(argv[4]) ? 0u : soft::queue_shift(waves);
+#endif
     std::vector<char> started(waves, 0);
     unsigned long long cursors[soft::kQueueCursors] = {};
     for (uint32_t w = 0; w < waves; ++w) live.push_back(w);
@@ -67,8 +71,8 @@ def drivers(tmp_path_factory):
     return exes
 
 
-def taken(exe, waves, n, seed):
-    out = subprocess.run([exe, str(waves), str(n), str(seed)], capture_output=True, text=True, check=True)
+def taken(exe, waves, n, seed, one=0):
+    out = subprocess.run([exe, str(waves), str(n), str(seed), str(one)], capture_output=True, text=True, check=True)
     return tuple(int(v) for v in out.stdout.split())
 
 
@@ -77,6 +81,7 @@ def test_every_item_once(drivers, waves):
     for n in (1, 2, 7, 8, 9, 63, 64, 1000, waves, waves + 1, 3 * waves + 5):
         for seed in range(3):
             assert taken(drivers[0], waves, n, seed) == (n, 0), (n, seed)
+        assert taken(drivers[0], waves, n, 3, one=1) == (n, 0), n
 
 
 @pytest.mark.parametrize("waves", [2, 4, 6])

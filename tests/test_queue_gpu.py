@@ -72,3 +72,20 @@ def test_states_of_every_variant_on_one_block():
             for a, b in zip(ref[0], got[0]):
                 assert (a == b).all(), (v, n)
             assert ref[1] == got[1]
+
+
+@pytest.mark.parametrize("grab", [0, 1, 7, 8, 64])
+def test_one_cursor_and_eight(grab):
+    # groups around the size from which one cursor serves all waves (256 or
+    # 512 of them), without the sign pass
+    w = workloads.config("cultivation_15q", seed=1)
+    ref = make_ctx(w.text, w.noise, seed=5)
+    ref.set_shared_prefix(False)
+    for wpb in (1, 2):
+        ctx = make_ctx(w.text, w.noise, seed=5, shape=(wpb, 1, grab))
+        ctx.set_shared_prefix(False)
+        for n in (256 * wpb * 31, 256 * wpb * 32 - 1, 256 * wpb * 32, 256 * wpb * 41 + 7):
+            a, b = outputs(ref.run, ref, 3, n), outputs(ctx.run, ctx, 3, n)
+            for x, y in zip(a[0], b[0]):
+                assert (x == y).all(), n
+            assert a[1] == b[1] and a[1][0] == n
