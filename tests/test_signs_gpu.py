@@ -268,3 +268,23 @@ def test_signature_tables_past_their_limit(mode):
     run_gpu(ctx, 0, 2000)
     a, b, c = (ctx.counters(v)["events"] for v in range(3))
     assert max(a, b) < 0.02 * c
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("n", [4097, 20_481, 163_841, 700_001])
+def test_lists_that_the_signs_do_not_decide(n, mode):
+    # a share of the shots ends by signs and the sampler runs the rest: groups
+    # from a wave's whole share to several for each, in one launch with a
+    # variant that is decided to its end
+    w = workloads.config("clifford_t_8q", seed=1)
+
+    def build(texts):
+        ctx = soft.Context(0)
+        ctx.load_mixture(texts, [NOISE] * len(texts), [n * (v + 1) // len(texts) for v in range(len(texts))])
+        ctx.set_rng(3)
+        ctx.set_noise_mode(mode)
+        return ctx
+
+    a, ca, cb = both(lambda: build([w.text]), 0, n)
+    assert 0 < ca["events"] < cb["events"]
+    both(lambda: build([rounds(4), w.text, workloads.config("cultivation_15q", seed=1).text]), 0, n)
