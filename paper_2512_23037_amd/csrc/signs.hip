@@ -50,14 +50,17 @@ constexpr uint32_t kLeft = 0xFFFFFFFFu;
 // Idle lanes take new shots once this many wait: a start costs about as much
 // as a step of one-lane shots, whether one lane or all take it.  With a word
 // per slot a step costs less than a start and a shot of n slots takes n / 64 of
-// them: long shots fill one group at a time (2800 slots: 937 us, 958 by twos),
-// short ones three (524 slots: 559 us, 581 by twos, 678 by ones).
+// them: long shots fill one group at a time, short ones three.  us by ones, twos
+// and threes: 524 slots 609, 510, 490; 861 298, 267, 264; 1125 422, 398, 401;
+// 1970 599, 574, 619; 2397 542, 537, 591; 5314 883, 917, 1051.
 template <bool GAPS> __device__ __forceinline__ uint32_t refill_at(uint32_t n_noise) {
-    return GAPS ? 32u : n_noise >= 1024u ? 16u : 48u;
+    return GAPS ? 32u : n_noise >= 1536u ? 16u : 48u;
 }
 
 // One-lane shots stopped at a broken pair wait until this many do: settling
-// takes longer than a step, however few lanes take part.
+// takes longer than a step, however few lanes take part (4 10^6 shots of 42
+// qubits at p = 1e-3: 237 us at once, 219 at 8, 218 at 12, 220 at 16, 225 at 32;
+// 15 qubits 219, 202, 201, 199, 201).
 constexpr uint32_t kSettle = 12;
 
 // The launch's arguments, read again where they are used: everything outside
