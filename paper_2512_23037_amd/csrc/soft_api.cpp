@@ -147,9 +147,12 @@ struct soft_ctx {
     hipEvent_t done = nullptr;           // after the last launch, and its stream
     hipStream_t done_stream = nullptr;
 
+    template <typename F> void each_table(F f) {
+        f(d_ev), f(d_nz), f(d_tm1), f(d_det), f(d_gap), f(d_bm), f(d_diag), f(d_vars), f(d_ckpt), f(d_signs);
+    }
     template <typename F> void each_buffer(F f) {
-        f(d_ev), f(d_nz), f(d_tm1), f(d_det), f(d_gap), f(d_bm), f(d_diag), f(d_vars), f(d_gtile), f(d_prefix), f(d_prefix_rec);
-        f(d_ckpt), f(d_signs), f(d_keep_meta), f(d_keep_v), f(d_trace_meta), f(d_trace_v);
+        each_table(f);
+        f(d_gtile), f(d_prefix), f(d_prefix_rec), f(d_keep_meta), f(d_keep_v), f(d_trace_meta), f(d_trace_v);
     }
 
     bool ran = false;
@@ -194,11 +197,17 @@ bool capturing(hipStream_t stream) {
     return st != hipStreamCaptureStatusNone;
 }
 
-// A recording holds the context's buffers from here on (but for the states
-// that stay between runs: a recorded launch has its own).
-void mark_recorded(soft_ctx *c) {
-    c->each_buffer([](auto &b) { b.recorded = b.p != nullptr; });
-    c->d_prefix.recorded = false;
+// A recording holds the context's tables from here on, and of its other
+// buffers those that these parameters name.
+void mark_recorded(soft_ctx *c, const RunParams &rp) {
+    c->each_table([](auto &b) { b.recorded = b.p != nullptr; });
+    auto mark = [](auto &b, const void *p) { b.recorded = b.recorded || (p != nullptr && (const void *)b.p == p); };
+    mark(c->d_gtile, rp.gtile);
+    mark(c->d_prefix_rec, rp.prefix);
+    mark(c->d_keep_meta, rp.keep_meta);
+    mark(c->d_keep_v, rp.keep_v);
+    mark(c->d_trace_meta, rp.trace_meta);
+    mark(c->d_trace_v, rp.trace_v);
 }
 
 double tau_of(const soft_ctx *c) { return c->tau >= 0.0 ? c->tau : (c->bits == 32 ? 1e-6 : 1e-12); }
@@ -830,7 +839,7 @@ int launch(soft_ctx *c, RunParams rp, const Shape &s, uint64_t n_shots, hipStrea
         pkey = {(uint64_t)(uintptr_t)slots.p, (uint64_t)c->bits, tb, rp.support_cap};
         build = captured || pkey != c->prefix_key;
     }
-    if (captured) mark_recorded(c);
+    if (captured) mark_recorded(c, rp);
     const bool sgn = use_signs(c, rp.shot_list != nullptr);
     rp.grab = group_size(c, s, grid, n_shots, sgn);
     rp.queue_shift = cursor_shift(rp, grid * s.wpb, sgn);
@@ -1444,7 +1453,7 @@ int soft_run_noalloc(soft_ctx *c, uint64_t shot0, uint64_t n_shots, uint32_t *ou
     }
     const hipStream_t stream = (hipStream_t)hip_stream;
     if (capturing(stream)) {
-        mark_recorded(c);
+        mark_recorded(c, rp);
     } else {
         c->noalloc_stream = stream;
         c->noalloc_pending = true;

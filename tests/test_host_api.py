@@ -221,6 +221,22 @@ int main(int argc, char **argv) {
         OK(soft_set_noise_mode(c, 1));
         OK(soft_set_tile_memory(c, tiles));
         auto run = [&](uint64_t n) { OK(soft_run(c, 0, n, nullptr, st.data(), nullptr, nullptr, nullptr)); };
+        if (tiles == 2) {
+            // a buffer that a recording names stays beside the larger one, one
+            // that none does is freed
+            run(100);
+            g_capture = true;
+            if (noalloc) OK(soft_run_noalloc(c, 0, 100, nullptr, st.data(), nullptr, nullptr, nullptr));
+            else run(100);
+            g_capture = false;
+            if (!noalloc) run(100);  // (eager checkpoint slots again)
+            const size_t blocks = g_live.size();
+            run(1000000);
+            CHECK(g_live.size() == blocks + (noalloc ? 0 : 1));
+            run(3000000);
+            CHECK(g_live.size() == blocks + (noalloc ? 0 : 1));
+            g_launches.clear();
+        }
         auto record = [&](uint64_t n) {
             run(n);
             g_capture = true;
