@@ -156,10 +156,9 @@ int soft_load_circuit(soft_ctx *ctx, const char *text, size_t len);
 int soft_load_noise(soft_ctx *ctx, const soft_noise *model);
 
 /* Load a mixture: n_variants (1..64) circuits, each with its own noise model,
- * sampled together in one launch by soft_run (the batching of many shots per
- * launch of Sec. IV-B, across circuits and noise rates as in the noise scans
- * of Sec. V).  Variant v owns the global
- * shot indices [shot_ends[v-1], shot_ends[v]) (shot_ends[-1] = 0; the ends
+ * sampled together by one soft_run (the batching of many shots per launch of
+ * Sec. IV-B, across circuits and noise rates as in the noise scans of Sec. V).
+ * Variant v owns the global shot indices [shot_ends[v-1], shot_ends[v]) (shot_ends[-1] = 0; the ends
  * strictly increase), and a shot of variant v has the same result as the
  * same shot index of a context holding only that circuit and model.
  * texts[v] (lens[v] bytes, copied) use the soft_load_circuit format;
@@ -247,7 +246,7 @@ int soft_set_speculation(soft_ctx *ctx, int on);
  * word of stream 2 and the gap table floor((1 - p_max)^g 2^32), and a second
  * word accepts the candidate with probability floor(p / p_max 2^32) 2^-32,
  * its Pauli picked from that word.  Mode 1 draws about 2 n p_max words per
- * shot instead of n.  Explicit words (soft_set_words) always use mode 0.
+ * shot instead of n.  Explicit words (soft_set_uniforms) always use mode 0.
  * Returns SOFT_EINVAL for another mode. */
 int soft_set_noise_mode(soft_ctx *ctx, int mode);
 
@@ -330,7 +329,8 @@ int soft_set_tile_memory(soft_ctx *ctx, int mode);
  * The results are cached for the process, keyed by the device (architecture
  * name and compute-unit count), the circuit (with a mixture's shot ranges),
  * precision, pruning threshold, support cap, tile placement, noise draws and
- * whether the sign pass runs: every context on such a device that loads the same circuit uses it.
+ * whether the sign pass runs: every context on such a device that loads the
+ * same circuit uses them.
  * Samples of 10^6 shots or more rank shapes reliably; small samples measure
  * launch overhead.  Runs on hip_stream and synchronizes it. */
 int soft_autotune(soft_ctx *ctx, uint64_t sample_shots, void *hip_stream);
@@ -343,8 +343,10 @@ int soft_set_keep(soft_ctx *ctx, uint64_t shot_lo, uint32_t count);
 /* Sample shots shot0 .. shot0 + n_shots - 1: each shot is one independent
  * pure-state trajectory of the Monte-Carlo model of Sec. II-C (Cliffords by
  * Theorem 1 part 1, T by Eqs. 1-2 with Eq. 4, measurements by Theorem 1
- * part 2), stopped at the first failed postselection check (Sec. V-A), all in
- * one persistent launch (Sec. IV-B).  Indices are global: a shot's result
+ * part 2), stopped at the first failed postselection check (Sec. V-A), in a
+ * few launches one after the other (Sec. IV-B): the counter reset, where they
+ * are needed the checkpoint build and the sign pass (soft_set_shared_prefix),
+ * and the persistent sampler.  Indices are global: a shot's result
  * depends only on seed, shot index, circuit and noise, not on batching.
  * Asynchronous on hip_stream (a hipStream_t; NULL = default stream).
  *   outcomes_dev: uint32 [ceil(records/32)][n_shots], bit r%32 of word r/32
@@ -371,10 +373,10 @@ int soft_run(soft_ctx *ctx, uint64_t shot0, uint64_t n_shots, uint32_t *outcomes
  * arguments, outputs and results as soft_run; the caller owns the outputs.
  * This call allocates nothing: no hipMalloc / hipFree, no graph is built.
  * It launches the counter reset, the checkpoint build, the sign pass and the
- * sampler directly on hip_stream (so a caller may capture them) and takes its counters, work cursors,
- * checkpoint slots (soft_set_shared_prefix; at most 4 MiB, else shots run
- * from the start with the same results) and any device-memory tiles from a static
- * scratch array of 36 MiB + 64 KiB per GPU, which the library holds on each
+ * sampler directly on hip_stream (so a caller may capture them) and takes its
+ * counters, work cursors, checkpoint slots (soft_set_shared_prefix; at most
+ * 4 MiB, else shots run from the start with the same results) and any
+ * device-memory tiles from a static scratch array of 36 MiB + 64 KiB per GPU, which the library holds on each
  * GPU it runs on until the process ends.
  * Device-memory tiles and the device-memory parts of split tiles
  * (soft_set_tile_memory) get at most 32 MiB of slabs, so such a launch may

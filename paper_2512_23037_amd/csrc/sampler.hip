@@ -120,8 +120,9 @@ __device__ __forceinline__ double wave_sum(double x) {
     return unid(x);
 }
 
-// x^-1/2 for a normal x: the hardware's estimate and two corrections, the last
-// from a residual that carries the rounding of x y.  A division by a square
+// x^-1/2 for a normal x: the hardware's estimate y and two corrections by the
+// binomial series of y (1 - e)^-1/2 with e = 1 - x y^2, y (1 + e/2 + 3 e^2/8) and
+// then y (1 + e/2), the last e a residual that carries the rounding of x y.  A division by a square
 // root is twice as many FP64 operations one after the other, in every
 // measurement, and further off (1 ulp; this is within 0.51).
 __device__ __forceinline__ double rsqrt64(double x) {

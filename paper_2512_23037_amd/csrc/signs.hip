@@ -11,10 +11,10 @@
 // lanes when half of them have ended: 50 of 64 busy in a step, fewer in the
 // shots' ends and starts) and the reads' latency between: a step waits for its
 // gaps, its slots and their signatures.  A launch of 10^7 shots of the 42-qubit
-// circuit at p = 1e-3 takes 0.47 ms, 21 G shots/s (48.4 ms with the sampler
+// circuit at p = 1e-3 takes 0.47 ms, 21 G shots/s (47.3 ms with the sampler
 // kernel alone).  With a word per slot it is bound by the Philox blocks, 222
 // cycles each of about 350 a step takes: 5 10^5 shots at p = 5e-4 (1.4 G words)
-// take 0.91 ms (3.2 with the sampler kernel alone).
+// take 0.91 ms (3.0 with the sampler kernel alone).
 #include <hip/hip_runtime.h>
 
 #include "device.h"
